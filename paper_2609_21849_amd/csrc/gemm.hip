@@ -54,7 +54,7 @@
 
 namespace qg {
 
-enum { MODE_FP8 = 1, MODE_NVFP4 = 2, MODE_W4A16 = 3 };
+enum { MODE_FP8 = 1, MODE_NVFP4 = 2, MODE_W4A16 = 3, MODE_MXFP4 = 4, MODE_MXFP8 = 5 };
 
 typedef float v16f __attribute__((ext_vector_type(16)));
 
@@ -670,7 +670,7 @@ static hipError_t run_fp8(GemmArgs g, hipStream_t st) {
   return hipGetLastError();
 }
 
-// ---------------------------------------------------------------- W8A8 / W4A4, few tokens: split K
+// ---------------------------------------------------------------- W8A8 / W4A4 / MX, few tokens: split K
 // A workgroup owns a (32 MT) x (32 NP) output tile; its NW wavefronts split
 // the reduction dimension (128-wide chunk kc goes to wave kc % NW), each
 // wave accumulates the whole tile over its chunks, and the NW partial tiles
@@ -687,7 +687,12 @@ static hipError_t run_fp8(GemmArgs g, hipStream_t st) {
 // Every wave keeps D chunks in flight in a ring of register sets: the loads
 // of its chunk t + D are issued as soon as chunk t has been multiplied.
 // NVFP4 expands both operands to fp16 in registers (exact, as in k_gemm);
-// FP8 feeds the codes to the fp8 MFMA as they are.
+// FP8 feeds the codes to the fp8 MFMA as they are; MXFP4 and MXFP8 too, with
+// the block scales of both operands applied by the instruction (row scales:
+// the row's four of the chunk as one dword, shifted by the lane half so that
+// step s finds its byte at 2 s; panel scales: the packed dword of the chunk
+// pair, shifted to the chunk's half). The MX layouts are those of
+// k_gemm_mxfp4_direct and k_gemm_mxfp8_direct.
 // Partial tiles go to LDS as row-major fp32 (row pitch 32 NP + 4 words, so
 // the 32 rows a store instruction touches spread over the banks), then
 // every thread sums four consecutive outputs of a row over the waves in a
@@ -705,7 +710,11 @@ static hipError_t run_fp8(GemmArgs g, hipStream_t st) {
 // writes the scale to a_tscale.
 template <int MODE, int MT, int NP, int NW, int D, bool AQ = false>
 __global__ void __launch_bounds__(64 * NW) k_gemm_splitk(GemmArgs g) {
-  static_assert(MODE == MODE_FP8 || MODE == MODE_NVFP4, "W8A8 or W4A4");
+  constexpr bool MX = MODE == MODE_MXFP4 || MODE == MODE_MXFP8;
+  static_assert(MODE == MODE_FP8 || MODE == MODE_NVFP4 || MX, "W8A8 or W4A4");
+  constexpr bool B8 = MODE == MODE_FP8 || MODE == MODE_MXFP8;  // one byte per element
+  constexpr int WCHUNK = B8 ? 4096 : 2048;                     // packed code bytes of a panel's chunk
+  constexpr int PIECES = B8 ? 4 : 2;                           // 16-byte pieces per lane, chunk and 32 rows
   static_assert(!AQ || MODE == MODE_FP8, "in-kernel activation quantization: FP8");
   constexpr uint32_t OOB = 0x80000000u;
   constexpr int BM = 32 * MT, BN = 32 * NP;
@@ -730,21 +739,23 @@ __global__ void __launch_bounds__(64 * NW) k_gemm_splitk(GemmArgs g) {
   const int npanels_w = (g.n + 31) >> 5;
 
   const __amdgpu_buffer_rsrc_t rs_w_ = __builtin_amdgcn_make_buffer_rsrc(
-      const_cast<uint8_t*>(g.w_codes), 0, (int)((int64_t)npanels_w * kcn * (MODE == MODE_FP8 ? 4096 : 2048)), 0x00020000);
+      const_cast<uint8_t*>(g.w_codes), 0, (int)((int64_t)npanels_w * kcn * WCHUNK), 0x00020000);
   const __amdgpu_buffer_rsrc_t rs_ws_ = __builtin_amdgcn_make_buffer_rsrc(
-      const_cast<uint8_t*>(g.w_scales), 0, MODE == MODE_NVFP4 ? (int)((int64_t)npanels_w * kcn * 256) : 0, 0x00020000);
+      const_cast<uint8_t*>(g.w_scales), 0, MODE == MODE_NVFP4 ? (int)((int64_t)npanels_w * kcn * 256) : MX ? (int)((int64_t)npanels_w * kcn * 128) : 0,
+      0x00020000);
   // NVFP4 activation rows: lda / 2 code bytes and lda / 16 scale bytes apart,
-  // the descriptors ending at the last row's k / 2 and k / 16 bytes
-  const int64_t ka = g.lda >> 1, ks = g.lda >> 4;
+  // the descriptors ending at the last row's k / 2 and k / 16 bytes (MX: k / 32;
+  // its rows are dense)
+  const int64_t ka = g.lda >> 1, ks = MX ? g.lda >> 5 : g.lda >> 4;
   const __amdgpu_buffer_rsrc_t rs_a_ = AQ
       ? __builtin_amdgcn_make_buffer_rsrc(const_cast<uint8_t*>(g.a), 0, (int)(((int64_t)(g.m - 1) * g.lda + g.k) * 2),
                                           0x00020000)
-      : (MODE == MODE_FP8)
+      : B8
       ? rsrc_a_fp8(g)
       : __builtin_amdgcn_make_buffer_rsrc(const_cast<uint8_t*>(g.a), 0, (int)((int64_t)(g.m - 1) * ka + (g.k >> 1)),
                                           0x00020000);
   const __amdgpu_buffer_rsrc_t rs_as_ = __builtin_amdgcn_make_buffer_rsrc(
-      const_cast<uint8_t*>(g.a_bscale), 0, MODE == MODE_NVFP4 ? (int)((int64_t)(g.m - 1) * ks + (g.k >> 4)) : 0,
+      const_cast<uint8_t*>(g.a_bscale), 0, MODE == MODE_FP8 ? 0 : (int)((int64_t)(g.m - 1) * ks + (MX ? g.k >> 5 : g.k >> 4)),
       0x00020000);
 
   const __amdgpu_buffer_rsrc_t rs_none = __builtin_amdgcn_make_buffer_rsrc(const_cast<uint8_t*>(g.w_codes), 0, 0, 0x00020000);
@@ -761,6 +772,9 @@ __global__ void __launch_bounds__(64 * NW) k_gemm_splitk(GemmArgs g) {
     } else if (MODE == MODE_FP8) {
       oa[i] = in ? (uint32_t)((int64_t)row * g.lda + 32 * gq) : OOB;
       oas[i] = OOB;
+    } else if (MX) {
+      oa[i] = in ? (uint32_t)((B8 ? row * g.lda : row * ka) + 16 * gq) : OOB;
+      oas[i] = in ? (uint32_t)(row * ks) : OOB;
     } else {
       oa[i] = in ? (uint32_t)(row * ka + 32 * gq) : OOB;
       oas[i] = in ? (uint32_t)(row * ks + 4 * gq) : OOB;
@@ -770,8 +784,8 @@ __global__ void __launch_bounds__(64 * NW) k_gemm_splitk(GemmArgs g) {
   for (int j = 0; j < NP; ++j) {
     const int pj = (n0 >> 5) + j;
     const bool in = pj < npanels_w;
-    ow[j] = in ? (uint32_t)(pj * kcn * (MODE == MODE_FP8 ? 4096 : 2048) + lane * 16) : OOB;
-    ows[j] = in ? (uint32_t)(pj * kcn * 256 + r * 8 + 4 * gq) : OOB;
+    ow[j] = in ? (uint32_t)(pj * kcn * WCHUNK + lane * 16) : OOB;
+    ows[j] = in ? (MX ? (uint32_t)(pj * kcn * 128 + lane * 4) : (uint32_t)(pj * kcn * 256 + r * 8 + 4 * gq)) : OOB;
   }
 
   // AQ: the activation's decode scale and its reciprocal (set below); with
@@ -782,12 +796,14 @@ __global__ void __launch_bounds__(64 * NW) k_gemm_splitk(GemmArgs g) {
   bool aq_clamp = false;
 
   // one 128-wide chunk of a lane's operands; FP8: piece 2 s + h = step s,
-  // register half h; NVFP4: pieces 0, 1 = the 32 code bytes, sc = 4 scales
+  // register half h; NVFP4: pieces 0, 1 = the 32 code bytes, sc = 4 scales;
+  // MXFP8: the FP8 pieces, MXFP4: piece s = step s, both with the row's four
+  // block scales of the chunk and the lane's four of the panel's chunk pair
   struct Chunk {
-    v4i a[MT][AQ ? 8 : (MODE == MODE_FP8 ? 4 : 2)];  // AQ: the bf16 elements of the FP8 pieces
-    v4i w[NP][MODE == MODE_FP8 ? 4 : 2];
-    uint32_t as[MODE == MODE_NVFP4 ? MT : 1];
-    uint32_t ws[MODE == MODE_NVFP4 ? NP : 1];
+    v4i a[MT][AQ ? 8 : PIECES];  // AQ: the bf16 elements of the FP8 pieces
+    v4i w[NP][PIECES];
+    uint32_t as[MODE == MODE_FP8 ? 1 : MT];
+    uint32_t ws[MODE == MODE_FP8 ? 1 : NP];
   };
   auto load = [&](Chunk& C, int kc) __attribute__((always_inline)) {
     // the chunk's byte offset is uniform (the wave index is scalar), so it
@@ -814,6 +830,22 @@ __global__ void __launch_bounds__(64 * NW) k_gemm_splitk(GemmArgs g) {
 #pragma unroll
         for (int j = 0; j < NP; ++j)
           C.w[j][p] = __builtin_amdgcn_raw_buffer_load_b128(rs_w, ow[j] + p * 1024, kq * 4096, 0);
+      }
+    } else if constexpr (MX) {
+#pragma unroll
+      for (int i = 0; i < MT; ++i) C.as[i] = __builtin_amdgcn_raw_buffer_load_b32(rs_as, oas[i], kq * 4, 0);
+#pragma unroll
+      for (int j = 0; j < NP; ++j) C.ws[j] = __builtin_amdgcn_raw_buffer_load_b32(rs_ws, ows[j], (kq >> 1) * 256, 0);
+      // a lane's piece p: MXFP8 step p / 2, register half p % 2 (elements
+      // 32 (p % 2) + 16 g of the step); MXFP4 step p (elements 32 g of it)
+#pragma unroll
+      for (int p = 0; p < PIECES; ++p) {
+#pragma unroll
+        for (int i = 0; i < MT; ++i)
+          C.a[i][p] = __builtin_amdgcn_raw_buffer_load_b128(rs_a, oa[i] + 32 * p, kq * (B8 ? 128 : 64), 0);
+#pragma unroll
+        for (int j = 0; j < NP; ++j)
+          C.w[j][p] = __builtin_amdgcn_raw_buffer_load_b128(rs_w, ow[j] + p * 1024, kq * WCHUNK, 0);
       }
     } else {
       // in the order of use: block scales, then code halves 0 (steps 0..3)
@@ -845,7 +877,7 @@ __global__ void __launch_bounds__(64 * NW) k_gemm_splitk(GemmArgs g) {
 #pragma unroll
       for (int v = 0; v < 16; ++v) acc[i][j][v] = 0.0f;
 
-  auto compute = [&](const Chunk& C) __attribute__((always_inline)) {
+  auto compute = [&](const Chunk& C, int kc) __attribute__((always_inline)) {
     if (MODE == MODE_FP8) {
 #pragma unroll
       for (int s = 0; s < 2; ++s) {
@@ -896,6 +928,39 @@ __global__ void __launch_bounds__(64 * NW) k_gemm_splitk(GemmArgs g) {
           for (int j = 0; j < NP; ++j)
             acc[i][j] = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(fb[j], fa[i], acc[i][j], 0, 0, 0, 0, 0, 0);
       }
+    } else if constexpr (MX) {
+      // the lane's scale of step s in byte 2 s of the row's four (block 2 s +
+      // g of the chunk) and in byte s of the panel's (after the chunk's half
+      // of the pair is shifted down); kc is uniform across the wave
+      uint32_t sa[MT], sw[NP];
+#pragma unroll
+      for (int i = 0; i < MT; ++i) sa[i] = C.as[i] >> (8 * gq);
+#pragma unroll
+      for (int j = 0; j < NP; ++j) sw[j] = C.ws[j] >> (16 * (kc & 1));
+      [&]<int... S>(std::integer_sequence<int, S...>) {
+        ([&] {
+          v8i fa[MT], fb[NP];
+          auto frag = [](const v4i (&c)[PIECES]) __attribute__((always_inline)) {
+            if constexpr (B8) {
+              const v4i lo = c[2 * S], hi = c[2 * S + 1];
+              return (v8i){lo.x, lo.y, lo.z, lo.w, hi.x, hi.y, hi.z, hi.w};
+            } else {
+              return (v8i){c[S].x, c[S].y, c[S].z, c[S].w, 0, 0, 0, 0};
+            }
+          };
+#pragma unroll
+          for (int i = 0; i < MT; ++i) fa[i] = frag(C.a[i]);
+#pragma unroll
+          for (int j = 0; j < NP; ++j) fb[j] = frag(C.w[j]);
+          constexpr int F = B8 ? 0 : 4;  // operand format: E4M3 or E2M1
+#pragma unroll
+          for (int i = 0; i < MT; ++i)
+#pragma unroll
+            for (int j = 0; j < NP; ++j)
+              acc[i][j] = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(fb[j], fa[i], acc[i][j], F, F, S, (int)sw[j],
+                                                                           2 * S, (int)sa[i]);
+        }(), ...);
+      }(std::make_integer_sequence<int, 2>());
     } else {
       // the lane's four block scales as fp16 (the multiplies take the one
       // they need from its register half)
@@ -990,7 +1055,7 @@ __global__ void __launch_bounds__(64 * NW) k_gemm_splitk(GemmArgs g) {
   for (int t0 = 0; t0 < nt; t0 += D) {
 #pragma unroll
     for (int d = 0; d < D; ++d) {
-      if (t0 + d < nt) compute(C[d]);
+      if (t0 + d < nt) compute(C[d], wave + NW * (t0 + d));
       load(C[d], wave + NW * (t0 + d + D));
     }
   }
@@ -1026,7 +1091,7 @@ __global__ void __launch_bounds__(64 * NW) k_gemm_splitk(GemmArgs g) {
   }
   if (wave < NRED) put(red + wave * (BM * LDR));
   __syncthreads();
-  const float c = *g.w_tscale * (AQ ? aq_s : *g.a_tscale);
+  const float c = MX ? 1.0f : *g.w_tscale * (AQ ? aq_s : *g.a_tscale);
   const bool vec = out_vec(g);
   const float ry = out_rscale(g);
   const bool nv = g.out_mode == OUT_NVFP4;
@@ -2993,6 +3058,35 @@ static int device_cus() {
   return n;
 }
 
+// MXFP4 / MXFP8. Up to two rounds of 64 x 96 tiles on the CUs the split-K
+// kernel, above that 256 x 256 tiles: those walk K serially (about 25-40 us at
+// K = 3072 however few there are), while a split-K tile's waves share K and
+// the operands' L2 traffic is all that bounds it. Inside the split-K range the
+// narrowest tile that still gives every workgroup a CU of its own. Measured
+// (GPU time from graph replays, 256 x 256 -> split-K; best of 16 tilings within
+// 8% everywhere): MXFP4 1 x 3072 x 1024 12.7 -> 2.8 us, 256 x 3072 x 3072 25.0 ->
+// 6.8, 500 x 3072 x 3072 38 -> 10.8, 1024 x 3072 x 3072 (two rounds) 26.5 -> 19.5;
+// MXFP8 14.3 -> 3.1, 32.0 -> 10.3, 37.5 -> 15.0, 33.2 -> 27.9; three rounds (1500 x
+// 3072 x 3072) lose for MXFP8 (42.0 against 37.5).
+template <int MODE>
+static hipError_t launch_mx(GemmArgs g, hipStream_t st) {
+  const int64_t cus = device_cus();
+  const int64_t rows32 = (g.m + 31) / 32, rows64 = (g.m + 63) / 64;
+  if (rows32 * ((g.n + 31) / 32) <= cus) return run_splitk<MODE, 1, 1, 4, 2>(g, st);
+  if (rows32 * ((g.n + 63) / 64) <= cus) return run_splitk<MODE, 1, 2, 4, 2>(g, st);
+  if (rows32 * ((g.n + 95) / 96) <= cus) return run_splitk<MODE, 1, 3, 8, 1>(g, st);
+  const int64_t t6496 = rows64 * ((g.n + 95) / 96);
+  if (t6496 > cus && rows64 * ((g.n + 127) / 128) <= cus) return run_splitk<MODE, 2, 4, 8, 1>(g, st);
+  if (t6496 <= 2 * cus) return run_splitk<MODE, 2, 3, 4, 2>(g, st);
+  // persistent grids of 256 x 256 tiles, four waves of 128 x 128 each
+  g.tiles_m = (g.m + 255) / 256;
+  g.tiles_n = (g.n + 255) / 256;
+  const dim3 grid((unsigned)std::min<int64_t>((int64_t)g.tiles_m * g.tiles_n, cus));
+  if (MODE == MODE_MXFP4) hipLaunchKernelGGL(k_gemm_mxfp4_direct, grid, dim3(256), 0, st, g);
+  else hipLaunchKernelGGL(k_gemm_mxfp8_direct, grid, dim3(256), 0, st, g);
+  return hipGetLastError();
+}
+
 hipError_t launch_gemm(int a_fmt, const void* a, const uint8_t* a_bscale, const float* a_tscale,
                        int64_t lda, const uint8_t* w_packed, int64_t m, int64_t n, int64_t k,
                        void* y, int64_t ldy, int out_mode, const float* y_scale, uint8_t* y_bscale,
@@ -3021,21 +3115,8 @@ hipError_t launch_gemm(int a_fmt, const void* a, const uint8_t* a_bscale, const 
   g.y_scale = y_scale;
   g.y_bscale = y_bscale;
   g.tiles_m = g.tiles_n = 0;
-  // persistent grids of 256 x 256 tiles, four waves of 128 x 128 each
-  if (a_fmt == 4) {
-    g.tiles_m = (g.m + 255) / 256;
-    g.tiles_n = (g.n + 255) / 256;
-    const int tiles = g.tiles_m * g.tiles_n;
-    hipLaunchKernelGGL(k_gemm_mxfp8_direct, dim3(std::min(tiles, device_cus())), dim3(256), 0, st, g);
-    return hipGetLastError();
-  }
-  if (a_fmt == 3) {
-    g.tiles_m = (g.m + 255) / 256;
-    g.tiles_n = (g.n + 255) / 256;
-    const int tiles = g.tiles_m * g.tiles_n;
-    hipLaunchKernelGGL(k_gemm_mxfp4_direct, dim3(std::min(tiles, device_cus())), dim3(256), 0, st, g);
-    return hipGetLastError();
-  }
+  if (a_fmt == 3) return launch_mx<MODE_MXFP4>(g, st);
+  if (a_fmt == 4) return launch_mx<MODE_MXFP8>(g, st);
   const int cus = device_cus();
   if (a_fmt == 1) {
     g.tiles_m = (g.m + 255) / 256;
