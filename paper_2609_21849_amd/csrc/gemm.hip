@@ -147,19 +147,19 @@ __device__ __attribute__((always_inline)) inline uint32_t nv_block(uint32_t amax
   return sb;
 }
 
-// One 16-block of row m held by a lane pair in the MFMA output layout: lane
-// half g holds columns n16 + 4 g + [0, 4) in v[0..3] and n16 + 8 + 4 g +
-// [0, 4) in v[4..7]. Both lanes of the pair (l, l ^ 32) call this together.
-// Lane half 0 stores bytes 0..3 of the block's codes, half 1 bytes 4..7.
-__device__ __attribute__((always_inline)) inline void store_nv_pair(const GemmArgs& g, int m, int n16,
-                                                                    const float (&v)[8], int gq, float st,
-                                                                    float d) {
+// One 16-block of a row held by a lane pair in the MFMA output layout: lane
+// half g holds columns 4 g + [0, 4) of the block in v[0..3] and 8 + 4 g +
+// [0, 4) in v[4..7]. Both lanes of the pair (l, l ^ 32) call this together;
+// returns bytes 0..3 of the block's codes in lane half 0 and bytes 4..7 in
+// half 1, and the block scale in sb.
+__device__ __attribute__((always_inline)) inline uint32_t nv_pair_codes(const float (&v)[8], int gq, float st, float d,
+                                                                        uint32_t& sb) {
   uint32_t am = 0;
 #pragma unroll
   for (int j = 0; j < 8; ++j) am = max(am, f2u(v[j]) & 0x7FFFFFFFu);
   am = max(am, (uint32_t)__shfl_xor((int)am, 32));
   float r;
-  const uint32_t sb = nv_block(am, st, d, r);
+  sb = nv_block(am, st, d, r);
   float y[8];
 #pragma unroll
   for (int j = 0; j < 8; ++j) y[j] = __fmul_rn(v[j], r);
@@ -167,7 +167,15 @@ __device__ __attribute__((always_inline)) inline void store_nv_pair(const GemmAr
   // those of 4-7 and 12-15 ([b2 b3 b6 b7]); one exchange makes them runs
   const uint32_t w = hw_e2m1x8(y);
   const uint32_t x = (uint32_t)__shfl_xor((int)w, 32);
-  const uint32_t out = gq ? ((x >> 16) | (w & 0xFFFF0000u)) : ((w & 0xFFFFu) | (x << 16));
+  return gq ? ((x >> 16) | (w & 0xFFFF0000u)) : ((w & 0xFFFFu) | (x << 16));
+}
+
+// The same for row m and columns n16 .. n16 + 15, stored.
+__device__ __attribute__((always_inline)) inline void store_nv_pair(const GemmArgs& g, int m, int n16,
+                                                                    const float (&v)[8], int gq, float st,
+                                                                    float d) {
+  uint32_t sb;
+  const uint32_t out = nv_pair_codes(v, gq, st, d, sb);
   uint8_t* row = reinterpret_cast<uint8_t*>(g.y) + (int64_t)m * (g.ldy >> 1);
   *reinterpret_cast<uint32_t*>(row + (n16 >> 1) + 4 * gq) = out;
   if (gq == 0) g.y_bscale[(int64_t)m * (g.ldy >> 4) + (n16 >> 4)] = (uint8_t)sb;
@@ -1124,42 +1132,184 @@ static hipError_t run_splitk(GemmArgs g, hipStream_t st) {
   return hipGetLastError();
 }
 
-// ---------------------------------------------------------------- FP8, 256 x 256 tiles
-// Epilogue fast path: bf16 output, whole tile inside the output, 16-byte
-// aligned rows. Stored straight from the MFMA layout, every store
-// instruction would scatter 8-byte pieces over 32 rows, which the memory
-// pipeline takes one cache line at a time; here each 32-row block of the
-// wave's tile is converted into the wave's private LDS area in the MFMA
-// layout (row pitch padded by 16 bytes so the 32 rows spread over all
-// banks) and read back 16 bytes per lane in row order, so that every store
-// instruction writes four whole 256-byte row segments. Each wave reads back
-// only what it wrote, so no barrier is needed; all addresses are one base
-// register plus immediate offsets. `stage` holds 32 * (64 TN + 16) bytes.
-template <int TM, int TN>
-__device__ __attribute__((always_inline)) inline void store_tiles_fast(const GemmArgs& g, const v16f (&acc)[TM][TN],
-                                                                       uint8_t* stage, int mw, int nw, int lane,
-                                                                       float c) {
-  constexpr int RB = 64 * TN, PITCH = RB + 16, PPR = RB / 16, ROWS_PER_IT = 64 / PPR;
-  static_assert(64 % PPR == 0, "a wave reads whole rows per instruction");
-  uint8_t* wr = stage + (lane & 31) * PITCH + 8 * (lane >> 5);
+// ---------------------------------------------------------------- large tiles: staged epilogue
+// Stored straight from the MFMA layout, every store instruction scatters 4-
+// to 16-byte pieces over 32 rows, which the memory pipeline takes one cache
+// line at a time. Here each 32-row block of the wave's tile is converted into
+// the wave's private LDS area in the MFMA layout (row pitch padded by 16
+// bytes so that the rows spread over the banks) and read back 16 bytes per
+// lane in row order, so that every store instruction writes whole row
+// segments of the tile (256 bytes of bf16 or fp32, 128 of FP8 codes, 64 of
+// NVFP4 codes). Each wave reads back only what it wrote, so no barrier is
+// needed. Rows and columns past the output are masked per 16-byte piece (N is
+// a multiple of 16, so a piece lies wholly inside or outside): ragged tiles
+// take the same path. `stage` holds 32 * (64 TN + 16) bytes.
+// Element-wise stores for ragged tiles and for every output but bf16 cost, per
+// launch (element-wise -> staged): FP8 codes 4608 x 9216 x 3072 121 -> 104 us,
+// 4608 x 3072 x 3072 41.5 -> 35.7; ragged bf16 MXFP4 500 x 9216 x 3072 39.0 -> 23.0,
+// FP8 2800 x 9216 x 3072 77 -> 71; MXFP4 fp32 4608 x 9216 x 3072 112 -> 93.
+
+// Whether the staged epilogue's 16-byte stores (and 8-byte ones of NVFP4
+// block scales) are aligned in every row of this output; otherwise
+// store_tiles writes it element by element where it must.
+inline bool out_staged(const GemmArgs& g) {
+  const uintptr_t base = reinterpret_cast<uintptr_t>(g.y);
+  if (g.out_mode == OUT_NVFP4)  // (ldy / 2) % 16 == 0, (ldy / 16) % 8 == 0
+    return (base & 15) == 0 && (reinterpret_cast<uintptr_t>(g.y_bscale) & 7) == 0 && (g.ldy & 127) == 0;
+  const int esz = g.out_mode == OUT_F32 ? 4 : g.out_mode == OUT_FP8 ? 1 : 2;
+  return (base & 15) == 0 && ((g.ldy * esz) & 15) == 0;
+}
+
+// The lane or thread index as a value the compiler cannot trace back: what a
+// tile's prologue or epilogue derives from it is then computed there, and not
+// hoisted out of the loop over tiles and kept across the K loop, whose
+// accumulators and fragments fill the register file: it spilled, and every
+// reload from scratch in the prologue waited for the operand loads issued
+// before it. With this and the wave index in a scalar register (no spills in
+// most instances, where there were 21 to 103): MXFP4 4608 x 9216 x 3072 93 -> 75 us,
+// MXFP8 2800 x 9216 x 3072 83 -> 72, W4A4 2800 x 9216 x 3072 134 -> 128.
+__device__ __attribute__((always_inline)) inline int opaque_lane(int lane) {
+  asm volatile("" : "+v"(lane));
+  return lane;
+}
+
+// Four consecutive outputs in the stage's element type (out_mode: bf16, fp32
+// or E4M3 codes; the conversions of store4).
+template <int OUT>
+__device__ __attribute__((always_inline)) inline void stage4(uint8_t* p, float v0, float v1, float v2, float v3, float r) {
+  if (OUT == OUT_F32) {
+    *reinterpret_cast<float4*>(p) = make_float4(v0, v1, v2, v3);
+  } else if (OUT == OUT_FP8) {
+    const float y[4] = {__fmul_rn(v0, r), __fmul_rn(v1, r), __fmul_rn(v2, r), __fmul_rn(v3, r)};
+    *reinterpret_cast<uint32_t*>(p) = hw_e4m3x4(y);
+  } else {
+    *reinterpret_cast<uint2*>(p) = make_uint2(pk_bf16(v0, v1), pk_bf16(v2, v3));
+  }
+}
+
+template <int OUT, bool FULL, int TM, int TN>
+__device__ __attribute__((always_inline)) inline void store_staged_as(const GemmArgs& g, const v16f (&acc)[TM][TN],
+                                                                      uint8_t* stage, int mw, int nw, int lane,
+                                                                      float c, float r) {
+  constexpr int ESZ = OUT == OUT_F32 ? 4 : OUT == OUT_FP8 ? 1 : 2;
+  constexpr int JN = OUT == OUT_F32 ? TN / 2 : TN;  // 32-column blocks staged at once
+  constexpr int RB = 32 * JN * ESZ, PITCH = RB + 16, PPR = RB / 16, ROWS_PER_IT = 64 / PPR;
+  static_assert(64 % PPR == 0 && TN % JN == 0 && PITCH <= 64 * TN + 16, "a wave reads whole rows per instruction");
+  lane = opaque_lane(lane);
+  uint8_t* wr = stage + (lane & 31) * PITCH + 4 * ESZ * (lane >> 5);
   const uint8_t* rd = stage + (lane / PPR) * PITCH + 16 * (lane % PPR);
-  uint8_t* out = reinterpret_cast<uint8_t*>(g.y) + ((int64_t)(mw + lane / PPR) * g.ldy + nw + 8 * (lane % PPR)) * 2;
-  const int64_t it_stride = (int64_t)ROWS_PER_IT * g.ldy * 2;
+  const int nl = nw + (16 / ESZ) * (lane % PPR), ml = mw + lane / PPR;
+  uint8_t* out = reinterpret_cast<uint8_t*>(g.y) + ((int64_t)ml * g.ldy + nl) * ESZ;
+  const int64_t it_stride = (int64_t)ROWS_PER_IT * g.ldy * ESZ;
+#pragma unroll
+  for (int i = 0; i < TM; ++i) {
+#pragma unroll
+    for (int j0 = 0; j0 < TN; j0 += JN) {
+#pragma unroll
+      for (int j = 0; j < JN; ++j)
+#pragma unroll
+        for (int qd = 0; qd < 4; ++qd) {
+          const v16f& a = acc[i][j0 + j];
+          stage4<OUT>(wr + (32 * j + 8 * qd) * ESZ, a[4 * qd] * c, a[4 * qd + 1] * c, a[4 * qd + 2] * c, a[4 * qd + 3] * c, r);
+        }
+      uint8_t* o = out + ((int64_t)i * 32 * g.ldy + 32 * j0) * ESZ;
+#pragma unroll
+      for (int it = 0; it < 32 / ROWS_PER_IT; ++it) {
+        const uint4 v = *reinterpret_cast<const uint4*>(rd + it * ROWS_PER_IT * PITCH);
+        if (FULL || (ml + 32 * i + it * ROWS_PER_IT < g.m && nl + 32 * j0 < g.n))
+          *reinterpret_cast<uint4*>(o + it * it_stride) = v;
+      }
+    }
+  }
+}
+
+// NVFP4 output: codes and block scales of a 32-row block staged side by side
+// (16 TN code bytes and 2 TN scales per row).
+template <int TM, int TN>
+__device__ __attribute__((always_inline)) inline void store_staged_nv(const GemmArgs& g, const v16f (&acc)[TM][TN],
+                                                                      uint8_t* stage, int mw, int nw, int lane,
+                                                                      float c) {
+  static_assert(TN == 4, "64 code bytes and 8 block scales per row");
+  constexpr int PITCH = 64 + 16;
+  lane = opaque_lane(lane);
+  const float st = *g.y_scale, d = nv_out_d(g);
+  const int gq = lane >> 5;
+  uint8_t* wr = stage + (lane & 31) * PITCH + 4 * gq;
+  const int mc = mw + (lane >> 2), nc = nw + 32 * (lane & 3);  // read back: four lanes per row of codes
 #pragma unroll
   for (int i = 0; i < TM; ++i) {
 #pragma unroll
     for (int j = 0; j < TN; ++j)
 #pragma unroll
-      for (int qd = 0; qd < 4; ++qd)
-        *reinterpret_cast<uint2*>(wr + (32 * j + 8 * qd) * 2) =
-            make_uint2(pk_bf16(acc[i][j][4 * qd] * c, acc[i][j][4 * qd + 1] * c),
-                       pk_bf16(acc[i][j][4 * qd + 2] * c, acc[i][j][4 * qd + 3] * c));
-    uint8_t* o = out + (int64_t)i * 32 * 2 * g.ldy;
+      for (int b = 0; b < 2; ++b) {
+        float v[8];
 #pragma unroll
-    for (int it = 0; it < 32 / ROWS_PER_IT; ++it)
-      *reinterpret_cast<uint4*>(o + it * it_stride) = *reinterpret_cast<const uint4*>(rd + it * ROWS_PER_IT * PITCH);
+        for (int e = 0; e < 8; ++e) v[e] = acc[i][j][8 * b + e] * c;
+        uint32_t sb;
+        *reinterpret_cast<uint32_t*>(wr + 16 * j + 8 * b) = nv_pair_codes(v, gq, st, d, sb);
+        if (gq == 0) wr[64 + 2 * j + b] = (uint8_t)sb;
+      }
+#pragma unroll
+    for (int it = 0; it < 2; ++it) {
+      const uint4 v = *reinterpret_cast<const uint4*>(stage + ((lane >> 2) + 16 * it) * PITCH + 16 * (lane & 3));
+      const int m = mc + 32 * i + 16 * it;
+      if (m < g.m && nc < g.n) {
+        uint8_t* o = reinterpret_cast<uint8_t*>(g.y) + (int64_t)m * (g.ldy >> 1) + (nc >> 1);
+        if (nc + 32 <= g.n) *reinterpret_cast<uint4*>(o) = v;
+        else *reinterpret_cast<uint2*>(o) = make_uint2(v.x, v.y);  // the last 16 columns
+      }
+    }
+    const int m = mw + 32 * i + (lane & 31);
+    if (gq == 0 && m < g.m) {
+      const uint8_t* s = stage + (lane & 31) * PITCH + 64;
+      uint8_t* o = g.y_bscale + (int64_t)m * (g.ldy >> 4) + (nw >> 4);
+      if (nw + 128 <= g.n) *reinterpret_cast<uint2*>(o) = *reinterpret_cast<const uint2*>(s);
+      else
+        for (int b = 0; b < 8 && nw + 16 * b < g.n; ++b) o[b] = s[b];
+    }
   }
 }
+
+// A wave's TM x TN accumulator tiles (layout as in store_tiles), first output
+// row mw and column nw, by epilogue EPI: an output mode staged, or EPI_DIRECT.
+// The large kernels are instantiated per epilogue: with all of them behind
+// run-time branches in one kernel the register allocation of the main loop
+// suffered (W4A4 4608 x 9216 x 3072 204 -> 227 us).
+constexpr int EPI_DIRECT = 4;
+template <int EPI, int TM, int TN>
+__device__ __attribute__((always_inline)) inline void store_tiles_epi(const GemmArgs& g, const v16f (&acc)[TM][TN],
+                                                                      uint8_t* stage, int mw, int nw, int lane,
+                                                                      float c) {
+  if constexpr (EPI == EPI_DIRECT) {
+    store_tiles<TM, TN>(g, acc, mw, nw, lane, c);
+  } else if constexpr (EPI == OUT_NVFP4) {
+    store_staged_nv<TM, TN>(g, acc, stage, mw, nw, lane, c);
+  } else if constexpr (EPI == OUT_BF16) {
+    if (mw + 32 * TM <= g.m && nw + 32 * TN <= g.n)
+      store_staged_as<EPI, true, TM, TN>(g, acc, stage, mw, nw, lane, c, 0.0f);
+    else
+      store_staged_as<EPI, false, TM, TN>(g, acc, stage, mw, nw, lane, c, 0.0f);
+  } else {
+    store_staged_as<EPI, false, TM, TN>(g, acc, stage, mw, nw, lane, c, EPI == OUT_FP8 ? out_rscale(g) : 0.0f);
+  }
+}
+
+// The epilogue instance of an output.
+inline int epilogue_of(const GemmArgs& g) { return out_staged(g) ? g.out_mode : EPI_DIRECT; }
+#define QG_LAUNCH_EPI_NO_NVFP4(KERNEL, grid, st, g)                                                    \
+  do {                                                                                                 \
+    switch (epilogue_of(g)) {                                                                          \
+      case OUT_BF16: hipLaunchKernelGGL(KERNEL<OUT_BF16>, grid, dim3(256), 0, st, g); break;           \
+      case OUT_F32: hipLaunchKernelGGL(KERNEL<OUT_F32>, grid, dim3(256), 0, st, g); break;             \
+      case OUT_FP8: hipLaunchKernelGGL(KERNEL<OUT_FP8>, grid, dim3(256), 0, st, g); break;             \
+      default: hipLaunchKernelGGL(KERNEL<EPI_DIRECT>, grid, dim3(256), 0, st, g);                      \
+    }                                                                                                  \
+  } while (0)
+#define QG_LAUNCH_EPI(KERNEL, grid, st, g)                                                             \
+  do {                                                                                                 \
+    if (epilogue_of(g) == OUT_NVFP4) hipLaunchKernelGGL(KERNEL<OUT_NVFP4>, grid, dim3(256), 0, st, g); \
+    else QG_LAUNCH_EPI_NO_NVFP4(KERNEL, grid, st, g);                                                  \
+  } while (0)
 
 // Activation staging shared by the 256 x 256 FP8 kernels: 256 rows x one
 // 128-byte chunk, read row-contiguously (8 lanes per row) and stored in LDS
@@ -1216,6 +1366,7 @@ __device__ __attribute__((always_inline)) inline v8i read_a_frag(const uint8_t* 
 // loading while the stores of its previous tile drain. Prefetches that would
 // run past the last chunk of a tile are turned into out-of-range loads,
 // which return zeros without touching memory.
+template <int EPI>
 __global__ void __launch_bounds__(256) k_gemm_fp8_direct(GemmArgs g) {
   constexpr int A_STAGE = 8 * 4096;
   constexpr int RA = AStage256::RA;
@@ -1224,13 +1375,13 @@ __global__ void __launch_bounds__(256) k_gemm_fp8_direct(GemmArgs g) {
   __shared__ __attribute__((aligned(16))) uint8_t smem[2 * A_STAGE];
   __shared__ __attribute__((aligned(16))) uint8_t sout[4 * OUT_STAGE];
 
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int wm = wave >> 1, wn = wave & 1;
   const int kcn = g.k >> 7;
   const int npanels_w = (g.n + 31) >> 5;
   const int total = g.tiles_m * g.tiles_n;
   const float scale = *g.w_tscale * *g.a_tscale;
-  const bool fast_out = g.out_mode == OUT_BF16 && ((reinterpret_cast<uintptr_t>(g.y) & 15) == 0) && ((g.ldy & 7) == 0);
   const __amdgpu_buffer_rsrc_t rs_a = rsrc_a_fp8(g);
   const __amdgpu_buffer_rsrc_t rs_b = __builtin_amdgcn_make_buffer_rsrc(
       const_cast<uint8_t*>(g.w_codes), 0, (int)((int64_t)npanels_w * kcn * 4096), 0x00020000);
@@ -1337,6 +1488,8 @@ __global__ void __launch_bounds__(256) k_gemm_fp8_direct(GemmArgs g) {
   };
 
   for (int tile = blockIdx.x; tile < total; tile += gridDim.x) {
+    tid = opaque_lane(threadIdx.x);
+    lane = tid & 63;
     int bm, bn;
     tile_coords(tile, g.tiles_m, g.tiles_n, bm, bn);
     const int m0 = bm * 256, n0 = bn * 256;
@@ -1387,10 +1540,7 @@ __global__ void __launch_bounds__(256) k_gemm_fp8_direct(GemmArgs g) {
     // Every operand write of this tile happened before its last barrier; the
     // next tile's first write to stage 0 can only race with the discarded
     // fragment read after that barrier.
-    if (fast_out && m0 + 256 <= g.m && n0 + 256 <= g.n)
-      store_tiles_fast<4, 4>(g, acc, sout + wave * OUT_STAGE, m0 + wm * 128, n0 + wn * 128, lane, scale);
-    else
-      store_tiles<4, 4>(g, acc, m0 + wm * 128, n0 + wn * 128, lane, scale);
+    store_tiles_epi<EPI, 4, 4>(g, acc, sout + wave * OUT_STAGE, m0 + wm * 128, n0 + wn * 128, lane, scale);
   }
 }
 
@@ -1443,22 +1593,55 @@ __device__ __attribute__((always_inline)) inline v8i read_a16(const uint8_t* st,
   return (v8i){lo.x, lo.y, lo.z, lo.w, hi.x, hi.y, hi.z, hi.w};
 }
 
+// The staged epilogue of a wave's 144 x 96 outputs as 9 x 6 MFMA tiles of 16 x
+// 16: each 16-row block through the wave's private LDS area (fp32: half of
+// its columns at a time), read back in row order so that every store writes
+// whole row segments (192 bytes; 96 of FP8 codes).
+constexpr int kT288Pitch = 96 * 2 + 16;
+template <int OUT, bool FULL>
+__device__ __attribute__((always_inline)) inline void store_t288(const GemmArgs& g, const v4f (&acc)[9][6], uint8_t* st,
+                                                                 int mw, int nw, int lane, float c, float r) {
+  constexpr int ESZ = OUT == OUT_F32 ? 4 : OUT == OUT_FP8 ? 1 : 2;
+  constexpr int JN = OUT == OUT_F32 ? 3 : 6;  // 16-column blocks staged at once
+  constexpr int RB = 16 * JN * ESZ, PITCH = RB + 16, PPR = RB / 16, PIECES = 16 * PPR;
+  static_assert(PITCH <= kT288Pitch, "the wave's staging area");
+  uint8_t* wr = st + (lane & 15) * PITCH + 4 * ESZ * (lane >> 4);
+#pragma unroll
+  for (int i = 0; i < 9; ++i)
+#pragma unroll
+    for (int j0 = 0; j0 < 6; j0 += JN) {
+#pragma unroll
+      for (int jj = 0; jj < JN; ++jj) {
+        const v4f& a = acc[i][j0 + jj];
+        stage4<OUT>(wr + 16 * jj * ESZ, a[0] * c, a[1] * c, a[2] * c, a[3] * c, r);
+      }
+#pragma unroll
+      for (int it = 0; it < (PIECES + 63) / 64; ++it) {
+        const int idx = it * 64 + lane, row = idx / PPR, pc = idx - PPR * (idx / PPR);
+        if (PIECES % 64 != 0 && idx >= PIECES) continue;
+        const uint4 v = *reinterpret_cast<const uint4*>(st + row * PITCH + pc * 16);
+        const int m = mw + 16 * i + row, n = nw + 16 * j0 + (16 / ESZ) * pc;
+        if (FULL || (m < g.m && n < g.n))
+          *reinterpret_cast<uint4*>(reinterpret_cast<uint8_t*>(g.y) + ((int64_t)m * g.ldy + n) * ESZ) = v;
+      }
+    }
+}
+
+template <int EPI>
 __global__ void __launch_bounds__(256) k_gemm_fp8_t288(GemmArgs g) {
   constexpr int A_STAGE = 18 * 2048;
   constexpr int RA = AStage288::RA;
   constexpr uint32_t OOB = 0x80000000u;
-  constexpr int OPITCH = 96 * 2 + 16;           // output staging: 16 rows of 96 bf16 + pad
-  constexpr int OUT_STAGE = 16 * OPITCH;
+  constexpr int OUT_STAGE = 16 * kT288Pitch;    // output staging: 16 rows of 96 bf16 + pad
   __shared__ __attribute__((aligned(16))) uint8_t smem[2 * A_STAGE];
   __shared__ __attribute__((aligned(16))) uint8_t sout[4 * OUT_STAGE];
 
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int wm = wave >> 1, wn = wave & 1;
   const int kcn = g.k >> 7;
   const int npanels_w = (g.n + 31) >> 5;
   const int total = g.tiles_m * g.tiles_n;
   const float scale = *g.w_tscale * *g.a_tscale;
-  const bool fast_out = g.out_mode == OUT_BF16 && ((reinterpret_cast<uintptr_t>(g.y) & 15) == 0) && ((g.ldy & 7) == 0);
   const __amdgpu_buffer_rsrc_t rs_a = rsrc_a_fp8(g);
   const __amdgpu_buffer_rsrc_t rs_b = __builtin_amdgcn_make_buffer_rsrc(
       const_cast<uint8_t*>(g.w_codes), 0, (int)((int64_t)npanels_w * kcn * 4096), 0x00020000);
@@ -1604,26 +1787,12 @@ __global__ void __launch_bounds__(256) k_gemm_fp8_t288(GemmArgs g) {
       }
     }
     const int mw = m0 + wm * 144, nw = n0 + wn * 96;
-    if (fast_out && m0 + 288 <= g.m && n0 + 192 <= g.n) {
-      // each 16-row block of the wave through its private LDS area, read back
-      // in row order so that every store writes whole 192-byte row segments
+    if constexpr (EPI != EPI_DIRECT) {
       uint8_t* st = sout + wave * OUT_STAGE;
-      uint8_t* wr = st + (lane & 15) * OPITCH + 8 * (lane >> 4);
-#pragma unroll
-      for (int i = 0; i < 9; ++i) {
-#pragma unroll
-        for (int jj = 0; jj < 6; ++jj)
-          *reinterpret_cast<uint2*>(wr + 32 * jj) =
-              make_uint2(pk_bf16(acc[i][jj][0] * scale, acc[i][jj][1] * scale),
-                         pk_bf16(acc[i][jj][2] * scale, acc[i][jj][3] * scale));
-#pragma unroll
-        for (int it = 0; it < 3; ++it) {
-          const int idx = it * 64 + lane, row = idx / 12, pc = idx - 12 * (idx / 12);
-          const uint4 v = *reinterpret_cast<const uint4*>(st + row * OPITCH + pc * 16);
-          *reinterpret_cast<uint4*>(reinterpret_cast<uint8_t*>(g.y) +
-                                    ((int64_t)(mw + 16 * i + row) * g.ldy + nw + 8 * pc) * 2) = v;
-        }
-      }
+      if (EPI == OUT_BF16 && m0 + 288 <= g.m && n0 + 192 <= g.n)
+        store_t288<EPI, true>(g, acc, st, mw, nw, lane, scale, 0.0f);
+      else
+        store_t288<EPI, false>(g, acc, st, mw, nw, lane, scale, EPI == OUT_FP8 ? out_rscale(g) : 0.0f);
     } else {
       const bool vec = out_vec(g);
       const float ry = out_rscale(g);
@@ -1659,6 +1828,7 @@ __global__ void __launch_bounds__(256) k_gemm_fp8_t288(GemmArgs g) {
 //                 lane and panel.
 // K must be a multiple of 256 (whole chunk pairs, no odd first chunk); no
 // tensor scales.
+template <int EPI>
 __global__ void __launch_bounds__(256) k_gemm_mxfp8_direct(GemmArgs g) {
   constexpr int A_CODES = 8 * 4096;
   constexpr int A_STAGE = A_CODES + 256 * 4;
@@ -1668,13 +1838,13 @@ __global__ void __launch_bounds__(256) k_gemm_mxfp8_direct(GemmArgs g) {
   __shared__ __attribute__((aligned(16))) uint8_t smem[2 * A_STAGE];
   __shared__ __attribute__((aligned(16))) uint8_t sout[4 * OUT_STAGE];
 
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int wm = wave >> 1, wn = wave & 1;
-  const int r = lane & 31, gq = lane >> 5;
+  int r = lane & 31, gq = lane >> 5;
   const int kcn = g.k >> 7;
   const int npanels_w = (g.n + 31) >> 5;
   const int total = g.tiles_m * g.tiles_n;
-  const bool fast_out = g.out_mode == OUT_BF16 && ((reinterpret_cast<uintptr_t>(g.y) & 15) == 0) && ((g.ldy & 7) == 0);
   const uint32_t ks = (uint32_t)(g.k >> 5);  // A scale bytes per row
   const __amdgpu_buffer_rsrc_t rs_a = rsrc_a_fp8(g);
   const __amdgpu_buffer_rsrc_t rs_as = __builtin_amdgcn_make_buffer_rsrc(
@@ -1812,6 +1982,10 @@ __global__ void __launch_bounds__(256) k_gemm_mxfp8_direct(GemmArgs g) {
   };
 
   for (int tile = blockIdx.x; tile < total; tile += gridDim.x) {
+    tid = opaque_lane(threadIdx.x);
+    lane = tid & 63;
+    r = lane & 31;
+    gq = lane >> 5;
     int bm, bn;
     tile_coords(tile, g.tiles_m, g.tiles_n, bm, bn);
     const int m0 = bm * 256, n0 = bn * 256;
@@ -1848,10 +2022,7 @@ __global__ void __launch_bounds__(256) k_gemm_mxfp8_direct(GemmArgs g) {
       chunk(std::integral_constant<int, 0>(), kc);
       chunk(std::integral_constant<int, 1>(), kc + 1);
     }
-    if (fast_out && m0 + 256 <= g.m && n0 + 256 <= g.n)
-      store_tiles_fast<4, 4>(g, acc, sout + wave * OUT_STAGE, m0 + wm * 128, n0 + wn * 128, lane, 1.0f);
-    else
-      store_tiles<4, 4>(g, acc, m0 + wm * 128, n0 + wn * 128, lane, 1.0f);
+    store_tiles_epi<EPI, 4, 4>(g, acc, sout + wave * OUT_STAGE, m0 + wm * 128, n0 + wn * 128, lane, 1.0f);
   }
 }
 
@@ -1874,6 +2045,7 @@ __global__ void __launch_bounds__(256) k_gemm_mxfp8_direct(GemmArgs g) {
 // code half and scales, a whole step before step 7 expands them (read one
 // MFMA before their use, their latency stalled the wave). Persistent grid and
 // staged epilogue as in k_gemm_fp8_direct.
+template <int EPI>
 __global__ void __launch_bounds__(256) k_gemm_nvfp4_direct(GemmArgs g) {
   constexpr int A_CODES = 8 * 2048;              // 256 rows x 64 B of codes
   constexpr int A_STAGE = A_CODES + 256 * 16;    // + 256 rows x 8 fp16 scales
@@ -1882,14 +2054,14 @@ __global__ void __launch_bounds__(256) k_gemm_nvfp4_direct(GemmArgs g) {
   __shared__ __attribute__((aligned(16))) uint8_t smem[2 * A_STAGE];
   __shared__ __attribute__((aligned(16))) uint8_t sout[4 * OUT_STAGE];
 
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int wm = wave >> 1, wn = wave & 1;
-  const int r = lane & 31, gq = lane >> 5;
+  int r = lane & 31, gq = lane >> 5;
   const int kcn = g.k >> 7;
   const int npanels_w = (g.n + 31) >> 5;
   const int total = g.tiles_m * g.tiles_n;
   const float scale = *g.w_tscale * *g.a_tscale;
-  const bool fast_out = g.out_mode == OUT_BF16 && ((reinterpret_cast<uintptr_t>(g.y) & 15) == 0) && ((g.ldy & 7) == 0);
   // A rows: lda / 2 code bytes and lda / 16 scale bytes apart; the
   // descriptors end at the last row's k / 2 and k / 16 bytes
   const uint32_t ka = (uint32_t)(g.lda >> 1), ks = (uint32_t)(g.lda >> 4);
@@ -2042,6 +2214,10 @@ __global__ void __launch_bounds__(256) k_gemm_nvfp4_direct(GemmArgs g) {
   };
 
   for (int tile = blockIdx.x; tile < total; tile += gridDim.x) {
+    tid = opaque_lane(threadIdx.x);
+    lane = tid & 63;
+    r = lane & 31;
+    gq = lane >> 5;
     int bm, bn;
     tile_coords(tile, g.tiles_m, g.tiles_n, bm, bn);
     const int m0 = bm * 256, n0 = bn * 256;
@@ -2109,10 +2285,7 @@ __global__ void __launch_bounds__(256) k_gemm_nvfp4_direct(GemmArgs g) {
         chunk(std::integral_constant<int, 1>(), kc + 1);
       }
     }
-    if (fast_out && m0 + 256 <= g.m && n0 + 256 <= g.n)
-      store_tiles_fast<4, 4>(g, acc, sout + wave * OUT_STAGE, m0 + wm * 128, n0 + wn * 128, lane, scale);
-    else
-      store_tiles<4, 4>(g, acc, m0 + wm * 128, n0 + wn * 128, lane, scale);
+    store_tiles_epi<EPI, 4, 4>(g, acc, sout + wave * OUT_STAGE, m0 + wm * 128, n0 + wn * 128, lane, scale);
   }
 }
 
@@ -2141,6 +2314,7 @@ __global__ void __launch_bounds__(256) k_gemm_nvfp4_direct(GemmArgs g) {
 //                 of 4 fp4 MFMAs lasts about one LDS read latency, so the
 //                 fragments are read two groups ahead.
 // K must be a multiple of 256 (checked by the caller).
+template <int EPI>
 __global__ void __launch_bounds__(256) k_gemm_mxfp4_direct(GemmArgs g) {
   constexpr int A_CODES = 8 * 4096;              // 8 panels x 4 steps x 1 KiB
   constexpr int A_STAGE = A_CODES + 256 * 8;     // + 8 scale bytes per row
@@ -2149,14 +2323,14 @@ __global__ void __launch_bounds__(256) k_gemm_mxfp4_direct(GemmArgs g) {
   __shared__ __attribute__((aligned(16))) uint8_t smem[2 * A_STAGE];
   __shared__ __attribute__((aligned(16))) uint8_t sout[4 * OUT_STAGE];
 
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int wm = wave >> 1, wn = wave & 1;
-  const int r = lane & 31, gq = lane >> 5;
+  int r = lane & 31, gq = lane >> 5;
   const int kcn = g.k >> 8;                      // chunks of 256
   const int steps = g.k >> 6;
   const int npanels_w = (g.n + 31) >> 5;
   const int total = g.tiles_m * g.tiles_n;
-  const bool fast_out = g.out_mode == OUT_BF16 && ((reinterpret_cast<uintptr_t>(g.y) & 15) == 0) && ((g.ldy & 7) == 0);
   const uint32_t ka = (uint32_t)(g.k >> 1), ks = (uint32_t)(g.k >> 5);  // A code / scale bytes per row
   const __amdgpu_buffer_rsrc_t rs_a = __builtin_amdgcn_make_buffer_rsrc(
       const_cast<uint8_t*>(g.a), 0, (int)((int64_t)g.m * ka), 0x00020000);
@@ -2301,6 +2475,10 @@ __global__ void __launch_bounds__(256) k_gemm_mxfp4_direct(GemmArgs g) {
   };
 
   for (int tile = blockIdx.x; tile < total; tile += gridDim.x) {
+    tid = opaque_lane(threadIdx.x);
+    lane = tid & 63;
+    r = lane & 31;
+    gq = lane >> 5;
     int bm, bn;
     tile_coords(tile, g.tiles_m, g.tiles_n, bm, bn);
     const int m0 = bm * 256, n0 = bn * 256;
@@ -2369,10 +2547,7 @@ __global__ void __launch_bounds__(256) k_gemm_mxfp4_direct(GemmArgs g) {
       }
     }
     // no tensor scales in MX: the block scales are applied inside the MFMAs
-    if (fast_out && m0 + 256 <= g.m && n0 + 256 <= g.n)
-      store_tiles_fast<4, 4>(g, acc, sout + wave * OUT_STAGE, m0 + wm * 128, n0 + wn * 128, lane, 1.0f);
-    else
-      store_tiles<4, 4>(g, acc, m0 + wm * 128, n0 + wn * 128, lane, 1.0f);
+    store_tiles_epi<EPI, 4, 4>(g, acc, sout + wave * OUT_STAGE, m0 + wm * 128, n0 + wn * 128, lane, 1.0f);
   }
 }
 
@@ -2401,6 +2576,7 @@ __global__ void __launch_bounds__(256) k_gemm_mxfp4_direct(GemmArgs g) {
 // stage 1, which no wave reads after the last chunk's barrier (a tile's
 // chunks run in pairs, stage 0 then 1), and the next tile writes it only
 // after its first barrier.
+template <int EPI>
 __global__ void __launch_bounds__(256) k_gemm_w4a16_direct(GemmArgs g) {
   constexpr int A_STAGE = 8 * 8192;              // 256 rows x 128 bf16
   constexpr int OUT_STAGE = 32 * (64 * 4 + 16);
@@ -2408,14 +2584,14 @@ __global__ void __launch_bounds__(256) k_gemm_w4a16_direct(GemmArgs g) {
   static_assert(4 * OUT_STAGE <= A_STAGE, "the output staging fits in one activation stage");
   __shared__ __attribute__((aligned(16))) uint8_t smem[2 * A_STAGE];
 
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int wm = wave >> 1, wn = wave & 1;
-  const int r = lane & 31, gq = lane >> 5;
+  int r = lane & 31, gq = lane >> 5;
   const int kcn = g.k >> 7;
   const int npanels_w = (g.n + 31) >> 5;
   const int total = g.tiles_m * g.tiles_n;
   const float scale = *g.w_tscale;
-  const bool fast_out = g.out_mode == OUT_BF16 && ((reinterpret_cast<uintptr_t>(g.y) & 15) == 0) && ((g.ldy & 7) == 0);
   const uint32_t lda2 = (uint32_t)(g.lda * 2);
   const __amdgpu_buffer_rsrc_t rs_a = __builtin_amdgcn_make_buffer_rsrc(
       const_cast<uint8_t*>(g.a), 0, (int)((int64_t)(g.m - 1) * lda2 + g.k * 2), 0x00020000);
@@ -2545,6 +2721,10 @@ __global__ void __launch_bounds__(256) k_gemm_w4a16_direct(GemmArgs g) {
   };
 
   for (int tile = blockIdx.x; tile < total; tile += gridDim.x) {
+    tid = opaque_lane(threadIdx.x);
+    lane = tid & 63;
+    r = lane & 31;
+    gq = lane >> 5;
     int bm, bn;
     tile_coords(tile, g.tiles_m, g.tiles_n, bm, bn);
     const int m0 = bm * 256, n0 = bn * 256;
@@ -2603,10 +2783,7 @@ __global__ void __launch_bounds__(256) k_gemm_w4a16_direct(GemmArgs g) {
         chunk(std::integral_constant<int, 1>(), kc + 1);
       }
     }
-    if (fast_out && m0 + 256 <= g.m && n0 + 256 <= g.n)
-      store_tiles_fast<4, 4>(g, acc, smem + A_STAGE + wave * OUT_STAGE, m0 + wm * 128, n0 + wn * 128, lane, scale);
-    else
-      store_tiles<4, 4>(g, acc, m0 + wm * 128, n0 + wn * 128, lane, scale);
+    store_tiles_epi<EPI, 4, 4>(g, acc, smem + A_STAGE + wave * OUT_STAGE, m0 + wm * 128, n0 + wn * 128, lane, scale);
   }
 }
 
@@ -3082,8 +3259,8 @@ static hipError_t launch_mx(GemmArgs g, hipStream_t st) {
   g.tiles_m = (g.m + 255) / 256;
   g.tiles_n = (g.n + 255) / 256;
   const dim3 grid((unsigned)std::min<int64_t>((int64_t)g.tiles_m * g.tiles_n, cus));
-  if (MODE == MODE_MXFP4) hipLaunchKernelGGL(k_gemm_mxfp4_direct, grid, dim3(256), 0, st, g);
-  else hipLaunchKernelGGL(k_gemm_mxfp8_direct, grid, dim3(256), 0, st, g);
+  if (MODE == MODE_MXFP4) QG_LAUNCH_EPI(k_gemm_mxfp4_direct, grid, st, g);
+  else QG_LAUNCH_EPI(k_gemm_mxfp8_direct, grid, st, g);
   return hipGetLastError();
 }
 
@@ -3158,10 +3335,11 @@ hipError_t launch_gemm(int a_fmt, const void* a, const uint8_t* a_bscale, const 
         ((t288 + cus - 1) / cus) * (288 * 192) < (int64_t)((tiles + cus - 1) / cus) * (256 * 256)) {
       g.tiles_m = t288_m;
       g.tiles_n = t288_n;
-      hipLaunchKernelGGL(k_gemm_fp8_t288, dim3((unsigned)std::min<int64_t>(t288, cus)), dim3(256), 0, st, g);
+      const dim3 grid((unsigned)std::min<int64_t>(t288, cus));
+      QG_LAUNCH_EPI_NO_NVFP4(k_gemm_fp8_t288, grid, st, g);
       return hipGetLastError();
     }
-    hipLaunchKernelGGL(k_gemm_fp8_direct, dim3(std::min(tiles, cus)), dim3(256), 0, st, g);
+    QG_LAUNCH_EPI(k_gemm_fp8_direct, dim3(std::min(tiles, cus)), st, g);
     return hipGetLastError();
   } else if (a_fmt == 2) {
     g.tiles_m = (g.m + 255) / 256;
@@ -3183,7 +3361,7 @@ hipError_t launch_gemm(int a_fmt, const void* a, const uint8_t* a_bscale, const 
       if (t6496 >= cus - cus / 4) return run_splitk<MODE_NVFP4, 2, 3, 8, 1>(g, st);
       return run_splitk<MODE_NVFP4, 1, 2, 8, 3>(g, st);
     }
-    hipLaunchKernelGGL(k_gemm_nvfp4_direct, dim3(std::min(tiles, cus)), dim3(256), 0, st, g);
+    QG_LAUNCH_EPI(k_gemm_nvfp4_direct, dim3(std::min(tiles, cus)), st, g);
     return hipGetLastError();
   } else {
     const int64_t npan_all = (n + 31) / 32;
@@ -3220,7 +3398,7 @@ hipError_t launch_gemm(int a_fmt, const void* a, const uint8_t* a_bscale, const 
     if (m > 128 && 2 * t256 >= device_cus()) {
       g.tiles_m = t256_m;
       g.tiles_n = t256_n;
-      hipLaunchKernelGGL(k_gemm_w4a16_direct, dim3((unsigned)std::min<int64_t>(t256, device_cus())), dim3(256), 0, st, g);
+      QG_LAUNCH_EPI_NO_NVFP4(k_gemm_w4a16_direct, dim3((unsigned)std::min<int64_t>(t256, device_cus())), st, g);
       return hipGetLastError();
     }
     if (m <= 1024) {
