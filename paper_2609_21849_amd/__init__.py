@@ -7,7 +7,10 @@ of the computation runs in the HIP kernels of ``libqgemm.so``; if the library
 is missing this module raises instead of computing anything elsewhere.
 
 A few helpers below (``quantize``, ``pack``, ``linear`` ...) allocate the
-output tensors with torch and then call the same entry points.
+output tensors with torch and then call the same entry points. The per-call
+ones (``quantize``, ``linear``, ``linear_fp8``) do so natively
+(``csrc/torch_binding.cpp``) for plain CUDA tensors that pass their checks;
+anything else takes the Python statements below, which raise what is wrong.
 """
 from __future__ import annotations
 
@@ -92,6 +95,29 @@ def lib() -> ctypes.CDLL:
         L.qg_abi_version.restype = I32
         _lib = L
     return _lib
+
+
+_host = None
+
+
+def _native():
+    """The native helpers (_qgemm_torch.so, built beside the library)."""
+    global _host
+    if _host is None:
+        lib()
+        import torch  # noqa: F401  (its libraries, before the extension that links them)
+        try:
+            from . import _qgemm_torch
+        except ImportError as e:
+            raise ImportError("_qgemm_torch.so is not built (run `python -m paper_2609_21849_amd.build` "
+                              "or __graft_entry__.build()): %s" % e) from e
+        _host = _qgemm_torch
+    return _host
+
+
+def _handle(stream):
+    """None (the current stream) or the stream's handle."""
+    return stream if stream is None or isinstance(stream, int) else stream.cuda_stream
 
 
 def _p(t) -> int | None:
@@ -254,6 +280,11 @@ def linear_fp8(x, w_packed, n: int, out_dtype: int = QG_OUT_BF16, stream=None):
     """Y = Q(x) . W^T from a bf16 activation x [m, k] (rows 16-byte aligned):
     the FP8 activation quantization inside the GEMM. Returns (y, the
     activation's decode scale as a one-element fp32 tensor)."""
+    r = (_host or _native()).linear_fp8(x, w_packed, n, out_dtype, _handle(stream))
+    if r is not None:
+        if type(r) is int:
+            _check(r, "qg_linear_fp8")
+        return r
     import torch
     _need(x, "x", torch.bfloat16, dense=False)
     _need(w_packed, "w_packed", torch.uint8, None, x.device)
@@ -359,6 +390,11 @@ def quantize(x, fmt: int, stream=None, static_scale=None) -> QTensor:
     """Quantize a [rows, cols] bf16 CUDA tensor (row stride may exceed cols).
     With static_scale (a one-element fp32 CUDA tensor holding a calibrated
     decode scale) the scale is used as given instead of derived from x."""
+    r = (_host or _native()).quantize(x, fmt, _handle(stream), static_scale)
+    if r is not None:
+        if type(r) is int:
+            _check(r, "qg_quantize_act" if static_scale is None else "qg_quantize_act_static")
+        return QTensor(fmt, *r)
     import torch
     _need(x, "x", torch.bfloat16, dense=False)
     rows, cols = x.shape
@@ -436,6 +472,16 @@ def _operands(a, w_packed):
 
 def linear(a, w_packed, w_fmt: int, n: int, out_dtype: int = QG_OUT_BF16, y=None, stream=None):
     """Y = A . W^T for a quantized A (QTensor) or a bf16 A (torch tensor)."""
+    if type(a) is QTensor:
+        r = (_host or _native()).linear(a.fmt, a.codes, a.block_scales, a.tensor_scale, a.rows, a.cols, w_packed, w_fmt,
+                                        n, out_dtype, y, _handle(stream))
+    else:
+        r = (_host or _native()).linear(QG_FMT_BF16, a, None, None, 0, 0, w_packed, w_fmt, n, out_dtype, y,
+                                        _handle(stream))
+    if r is not None:
+        if type(r) is int:
+            _check(r, "qg_gemm")
+        return r
     import torch
     m, k, a_fmt, a_data, a_bs, a_ts, lda, dev = _operands(a, w_packed)
     if out_dtype not in (QG_OUT_BF16, QG_OUT_F32):

@@ -1,9 +1,10 @@
-"""Build libqgemm.so (HIP, gfx950) in-tree.
+"""Build libqgemm.so (HIP, gfx950) and the torch binding in-tree.
 
     python -m paper_2609_21849_amd.build
 
 Each .hip file is compiled to an object in parallel, then linked into
-paper_2609_21849_amd/libqgemm.so next to this file.
+paper_2609_21849_amd/libqgemm.so next to this file; csrc/torch_binding.cpp
+(host code only) becomes _qgemm_torch.so beside it, linked against it.
 """
 from __future__ import annotations
 
@@ -12,6 +13,7 @@ import os
 import shutil
 import subprocess
 import sys
+import sysconfig
 from concurrent.futures import ThreadPoolExecutor
 
 HERE = os.path.dirname(os.path.abspath(__file__))
@@ -20,6 +22,7 @@ CSRC = os.path.join(HERE, "csrc")
 INCLUDE = os.path.join(ROOT, "include")
 BUILD_DIR = os.path.join(HERE, "_build")
 LIB = os.path.join(HERE, "libqgemm.so")
+BINDING = os.path.join(HERE, "_qgemm_torch.so")
 ARCH = "gfx950"
 
 HIPCC = shutil.which("hipcc") or "/opt/rocm/bin/hipcc"
@@ -37,6 +40,22 @@ def sources() -> list[str]:
     return sorted(glob.glob(os.path.join(CSRC, "*.hip")))
 
 
+def _compile_binding() -> str:
+    import torch
+    inc = os.path.join(os.path.dirname(torch.__file__), "include")
+    rocm = os.path.dirname(os.path.dirname(os.path.realpath(HIPCC)))
+    obj = os.path.join(BUILD_DIR, "torch_binding.o")
+    cmd = [shutil.which("g++") or "g++", "-O2", "-std=c++17", "-fPIC", "-fvisibility=hidden", "-D__HIP_PLATFORM_AMD__=1",
+           "-DUSE_ROCM", "-D_GLIBCXX_USE_CXX11_ABI=%d" % int(torch._C._GLIBCXX_USE_CXX11_ABI),
+           "-I" + INCLUDE, "-isystem", inc, "-isystem", os.path.join(inc, "torch", "csrc", "api", "include"),
+           "-isystem", sysconfig.get_paths()["include"], "-isystem", os.path.join(rocm, "include"),
+           "-isystem", "/opt/rocm/include", "-c", os.path.join(CSRC, "torch_binding.cpp"), "-o", obj]
+    r = subprocess.run(cmd, capture_output=True, text=True)
+    if r.returncode != 0:
+        raise RuntimeError("g++ failed for torch_binding.cpp:\n%s" % r.stderr)
+    return obj
+
+
 def _compile(src: str) -> str:
     obj = os.path.join(BUILD_DIR, os.path.basename(src) + ".o")
     cmd = [HIPCC, *COMMON, "-c", src, "-o", obj]
@@ -50,13 +69,24 @@ def build(verbose: bool = False) -> str:
     os.makedirs(BUILD_DIR, exist_ok=True)
     srcs = sources()
     with ThreadPoolExecutor(max(1, min(len(srcs), os.cpu_count() or 1))) as ex:
+        binding = ex.submit(_compile_binding)
         objs = list(ex.map(_compile, srcs))
+        binding_obj = binding.result()
     tmp = LIB + ".tmp%d" % os.getpid()
     cmd = [HIPCC, "--offload-arch=" + ARCH, "-shared", "-fPIC", "-o", tmp, *objs]
     r = subprocess.run(cmd, capture_output=True, text=True)
     if r.returncode != 0:
         raise RuntimeError("link failed:\n%s" % r.stderr)
     os.replace(tmp, LIB)
+    import torch
+    tl = os.path.join(os.path.dirname(torch.__file__), "lib")
+    tmp = BINDING + ".tmp%d" % os.getpid()
+    cmd = [shutil.which("g++") or "g++", "-shared", "-o", tmp, binding_obj, "-L" + HERE, "-l:libqgemm.so",
+           "-Wl,-rpath,$ORIGIN", "-L" + tl, "-lc10", "-lc10_hip", "-ltorch_cpu", "-ltorch_python"]
+    r = subprocess.run(cmd, capture_output=True, text=True)
+    if r.returncode != 0:
+        raise RuntimeError("link of the torch binding failed:\n%s" % r.stderr)
+    os.replace(tmp, BINDING)
     if verbose:
         print("built", LIB)
     return LIB
