@@ -36,13 +36,6 @@
 //   NVFP4, W4A16: elements [64 g, 64 g + 64) of its row over the chunk's
 //          eight 16-wide steps.
 //
-// Tiling of the large-M W4A16 kernel (k_gemm): a workgroup of WM x WN
-// wavefronts owns a (32 TM WM) x (32 TN WN) output tile; each wave owns
-// TM x TN tiles of 32 x 32. Chunks of 128 are staged in LDS in the packed
-// weight's lane-major order, so every LDS read is one contiguous 1 KiB wave
-// access. Global loads run one chunk ahead; LDS is double buffered with one
-// barrier per chunk.
-//
 // MFMA orientation: the weight panel is the MFMA A operand and the
 // activation panel the B operand, so a lane ends with runs of 4 consecutive
 // output columns of one output row.
@@ -54,7 +47,7 @@
 
 namespace qg {
 
-enum { MODE_FP8 = 1, MODE_NVFP4 = 2, MODE_W4A16 = 3, MODE_MXFP4 = 4, MODE_MXFP8 = 5 };
+enum { MODE_FP8 = 1, MODE_NVFP4 = 2, MODE_MXFP4 = 3, MODE_MXFP8 = 4 };  // format ids
 
 typedef float v16f __attribute__((ext_vector_type(16)));
 
@@ -201,11 +194,6 @@ __device__ __attribute__((always_inline)) inline void store_nv_quad(const GemmAr
   if ((n & 15) == 0) g.y_bscale[(int64_t)m * (g.ldy >> 4) + (n >> 4)] = (uint8_t)sb;
 }
 
-// LDS bytes per 32-row panel per 128-chunk of the large-M W4A16 kernel:
-// bf16 activations (A), weight codes (B) and decoded weight block scales.
-template <int MODE> struct Lds;
-template <> struct Lds<MODE_W4A16> { static constexpr int A = 8192, B = 2048, AS = 0, BS = 1024; };
-
 // 8 E2M1 codes (one dword) times an fp16 block scale -> 8 fp16 (exact).
 __device__ inline v8h dequant8_f16(uint32_t w, _Float16 sc) {
   const v2h s2 = {sc, sc};
@@ -248,225 +236,6 @@ __device__ inline void tile_coords(int id, int tiles_m, int tiles_n, int& bm, in
   const int in = t - grp * per_group;
   bm = first_m + in % rows;
   bn = in / rows;
-}
-
-template <int MODE, int WM, int WN, int TM, int TN, int DEPTH>
-__global__ void __launch_bounds__(64 * WM * WN) k_gemm(GemmArgs g) {
-  static_assert(MODE == MODE_W4A16, "W8A8 and W4A4 have kernels of their own");
-  constexpr int NT = 64 * WM * WN;
-  constexpr int PA = TM * WM, PB = TN * WN;  // 32-row panels per tile
-  constexpr int BM = 32 * PA, BN = 32 * PB;
-  constexpr int A_BYTES = PA * Lds<MODE>::A, B_BYTES = PB * Lds<MODE>::B;
-  constexpr int AS_BYTES = PA * Lds<MODE>::AS, BS_BYTES = PB * Lds<MODE>::BS;
-  constexpr int STAGE = A_BYTES + B_BYTES + AS_BYTES + BS_BYTES;
-  // 16-byte pieces per stage of each operand; one 8-byte scale run per weight row
-  constexpr int NPA = A_BYTES / 16, NPB = B_BYTES / 16;
-  static_assert(NPA % NT == 0 && NPB % NT == 0, "piece count must divide the thread count");
-  constexpr int RA = NPA / NT, RB = NPB / NT;
-  constexpr int NSB = BN;
-  constexpr int RSB = (NSB + NT - 1) / NT;
-  constexpr int PIECES_A = Lds<MODE>::A / 16, PIECES_B = Lds<MODE>::B / 16;  // per panel chunk
-
-  __shared__ __attribute__((aligned(16))) uint8_t smem[2 * STAGE];
-
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  const int wm = wave / WN, wn = wave % WN;
-  int bm, bn;
-  tile_coords(blockIdx.x, g.tiles_m, g.tiles_n, bm, bn);
-  const int m0 = bm * BM, n0 = bn * BN;
-  const int kcn = g.k >> 7;
-  const int npanels_w = (g.n + 31) >> 5;
-
-  // Global reads go through buffer descriptors (base + byte count in SGPRs):
-  // each piece a thread copies is one 32-bit offset, the chunk advance is the
-  // scalar offset, and rows or panels past the end fall outside the buffer's
-  // range, which the hardware turns into zeros -- no branches, no clamping.
-  const int64_t a_row_bytes = 2 * g.lda;
-  const __amdgpu_buffer_rsrc_t rs_a = __builtin_amdgcn_make_buffer_rsrc(
-      const_cast<uint8_t*>(g.a), 0, (int)((int64_t)g.m * a_row_bytes), 0x00020000);
-  const __amdgpu_buffer_rsrc_t rs_b = __builtin_amdgcn_make_buffer_rsrc(
-      const_cast<uint8_t*>(g.w_codes), 0, (int)((int64_t)npanels_w * kcn * Lds<MODE>::B), 0x00020000);
-  const __amdgpu_buffer_rsrc_t rs_sb = __builtin_amdgcn_make_buffer_rsrc(
-      const_cast<uint8_t*>(g.w_scales), 0, (int)((int64_t)npanels_w * kcn * 256), 0x00020000);
-
-  // Activation pieces are read row-contiguously (CPR 16-byte pieces cover a
-  // row's chunk bytes, so 64 lanes read 64 / CPR whole row runs) and written
-  // to the lane-major LDS image through an XOR swizzle: piece c of row r
-  // belongs to lane (r, g = c / HALF) as its piece h = c % HALF and lands in
-  // slot ((r + 32 g) ^ c) of LDS block h. The lanes of one row then hit
-  // distinct LDS banks, and the operand read of lane l (slot l ^ (h + HALF g))
-  // stays a conflict-free 1 KiB access.
-  constexpr int CPR = 16;
-  constexpr int HALF = CPR / 2;
-  uint32_t oa[RA];
-  uint32_t la[RA];
-#pragma unroll
-  for (int it = 0; it < RA; ++it) {
-    const int q = it * NT + tid;
-    const int p = q / (32 * CPR), rr = (q / CPR) % 32, c = q % CPR;
-    const uint32_t row = (uint32_t)(m0 + 32 * p + rr);
-    oa[it] = (row < (uint32_t)g.m) ? row * (uint32_t)a_row_bytes + 16u * c : 0x80000000u;
-    const int gg = c / HALF, h = c % HALF;
-    la[it] = (uint32_t)(p * Lds<MODE>::A + h * 1024 + (((rr + 32 * gg) ^ c) * 16));
-  }
-  uint32_t ob[RB];
-#pragma unroll
-  for (int it = 0; it < RB; ++it) {
-    const int q = it * NT + tid;
-    const int p = q / PIECES_B, s = q - p * PIECES_B;
-    const uint32_t panel = (uint32_t)((n0 >> 5) + p);
-    ob[it] = (panel < (uint32_t)npanels_w) ? panel * (uint32_t)(kcn * Lds<MODE>::B) + 16u * s : 0x80000000u;
-  }
-  uint32_t osb[RSB > 0 ? RSB : 1];
-#pragma unroll
-  for (int it = 0; it < RSB; ++it) {
-    const int q = it * NT + tid;
-    const uint32_t panel = (uint32_t)((n0 >> 5) + (q >> 5));
-    osb[it] = (q < NSB && panel < (uint32_t)npanels_w) ? panel * (uint32_t)(kcn * 256) + 8u * (q & 31) : 0x80000000u;
-  }
-
-  struct Regs {
-    v4i a[RA > 0 ? RA : 1];
-    v4i b[RB > 0 ? RB : 1];
-    v2i sb[RSB > 0 ? RSB : 1];
-  };
-
-  // ---- global -> registers for chunk kc
-  auto load_chunk = [&](Regs& R, int kc) {
-    const int sa_off = kc * 256;
-#pragma unroll
-    for (int it = 0; it < RA; ++it) R.a[it] = __builtin_amdgcn_raw_buffer_load_b128(rs_a, oa[it], sa_off, 0);
-#pragma unroll
-    for (int it = 0; it < RB; ++it) R.b[it] = __builtin_amdgcn_raw_buffer_load_b128(rs_b, ob[it], kc * Lds<MODE>::B, 0);
-#pragma unroll
-    for (int it = 0; it < RSB; ++it) R.sb[it] = __builtin_amdgcn_raw_buffer_load_b64(rs_sb, osb[it], kc * 256, 0);
-  };
-
-  // ---- registers -> LDS stage (block scales expanded once per workgroup)
-  auto store_chunk = [&](const Regs& R, uint8_t* st) {
-    uint8_t* sa = st;
-    uint8_t* sb = st + A_BYTES;
-    uint8_t* ssb = st + A_BYTES + B_BYTES + AS_BYTES;
-#pragma unroll
-    for (int it = 0; it < RA; ++it) *reinterpret_cast<v4i*>(sa + la[it]) = R.a[it];
-#pragma unroll
-    for (int it = 0; it < RB; ++it) reinterpret_cast<v4i*>(sb)[it * NT + tid] = R.b[it];
-#pragma unroll
-    for (int it = 0; it < RSB; ++it) {
-      const int q = it * NT + tid;
-      if (q < NSB) {
-        const uint32_t w[2] = {(uint32_t)R.sb[it].x, (uint32_t)R.sb[it].y};
-        float f[8];
-#pragma unroll
-        for (int j = 0; j < 8; ++j) f[j] = dec_e4m3((w[j >> 2] >> (8 * (j & 3))) & 0xFFu);
-        reinterpret_cast<float4*>(ssb)[2 * q] = make_float4(f[0], f[1], f[2], f[3]);
-        reinterpret_cast<float4*>(ssb)[2 * q + 1] = make_float4(f[4], f[5], f[6], f[7]);
-      }
-    }
-  };
-
-  v16f acc[TM][TN];
-#pragma unroll
-  for (int i = 0; i < TM; ++i)
-#pragma unroll
-    for (int j = 0; j < TN; ++j)
-#pragma unroll
-      for (int v = 0; v < 16; ++v) acc[i][j][v] = 0.0f;
-
-  // ---- MFMAs over one staged chunk
-  auto compute_chunk = [&](const uint8_t* st) {
-    const uint8_t* sa = st;
-    const uint8_t* sb = st + A_BYTES;
-    const uint8_t* ssb = st + A_BYTES + B_BYTES + AS_BYTES;
-    const int r = lane & 31, gq = lane >> 5;
-    {
-      uint4 cb[TN][2];
-      float4 scb[TN];
-#pragma unroll
-      for (int j = 0; j < TN; ++j) {
-        const int p = wn * TN + j;
-        cb[j][0] = *reinterpret_cast<const uint4*>(sb + p * 2048 + lane * 16);
-        cb[j][1] = *reinterpret_cast<const uint4*>(sb + p * 2048 + 1024 + lane * 16);
-        scb[j] = *reinterpret_cast<const float4*>(ssb + p * 1024 + r * 32 + 16 * gq);
-      }
-#pragma unroll
-      for (int s = 0; s < 8; ++s) {
-        v8bf fa[TM], fb[TN];
-#pragma unroll
-        for (int i = 0; i < TM; ++i)
-          fa[i] = __builtin_bit_cast(v8bf, *reinterpret_cast<const v4i*>(sa + (wm * TM + i) * 8192 + s * 1024 + ((lane ^ (s + 8 * gq)) * 16)));
-#pragma unroll
-        for (int j = 0; j < TN; ++j) {
-          const uint4 c = cb[j][s >> 2];
-          const uint32_t w = ((s & 3) == 0) ? c.x : ((s & 3) == 1) ? c.y : ((s & 3) == 2) ? c.z : c.w;
-          const float sc = ((s >> 1) == 0) ? scb[j].x : ((s >> 1) == 1) ? scb[j].y : ((s >> 1) == 2) ? scb[j].z : scb[j].w;
-          fb[j] = __builtin_bit_cast(v8bf, dequant8_bf16(w, sc));
-        }
-#pragma unroll
-        for (int i = 0; i < TM; ++i)
-#pragma unroll
-          for (int j = 0; j < TN; ++j)
-            acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fb[j], fa[i], acc[i][j], 0, 0, 0);
-      }
-    }
-  };
-
-  // ---- main loop. DEPTH 2: chunk kc+2 loads while chunk kc multiplies and
-  // chunk kc+1's registers (loaded one iteration earlier) go to the free LDS
-  // buffer. DEPTH 1: chunk kc+1 loads while chunk kc multiplies.
-  if (kcn > 0) {
-    if (DEPTH == 2) {
-      Regs R0, R1;
-      load_chunk(R0, 0);
-      if (kcn > 1) load_chunk(R1, 1);
-      store_chunk(R0, smem);
-      __syncthreads();
-      int kc = 0;
-      for (; kc + 1 < kcn; kc += 2) {
-        if (kc + 2 < kcn) load_chunk(R0, kc + 2);
-        compute_chunk(smem);
-        store_chunk(R1, smem + STAGE);
-        __syncthreads();
-        if (kc + 3 < kcn) load_chunk(R1, kc + 3);
-        compute_chunk(smem + STAGE);
-        if (kc + 2 < kcn) store_chunk(R0, smem);
-        __syncthreads();
-      }
-      if (kc < kcn) compute_chunk(smem);  // odd chunk count: the last one sits in buffer 0
-    } else {
-      Regs R;
-      load_chunk(R, 0);
-      store_chunk(R, smem);
-      __syncthreads();
-      for (int kc = 0; kc < kcn; ++kc) {
-        const bool more = kc + 1 < kcn;
-        if (more) load_chunk(R, kc + 1);
-        compute_chunk(smem + (kc & 1) * STAGE);
-        if (more) store_chunk(R, smem + ((kc + 1) & 1) * STAGE);
-        __syncthreads();
-      }
-    }
-  }
-
-  // ---- epilogue: scale, round, store. Lane holds Y[m][n + 8 q .. +3] for q = 0..3.
-  float c = *g.w_tscale;
-  const bool vec = out_vec(g);
-  const float ry = out_rscale(g);
-#pragma unroll
-  for (int i = 0; i < TM; ++i) {
-    const int m = m0 + (wm * TM + i) * 32 + (lane & 31);
-    if (m >= g.m) continue;
-#pragma unroll
-    for (int j = 0; j < TN; ++j) {
-#pragma unroll
-      for (int qd = 0; qd < 4; ++qd) {
-        const int n = n0 + (wn * TN + j) * 32 + 8 * qd + 4 * (lane >> 5);
-        if (n >= g.n) continue;
-        store4(g, m, n, acc[i][j][4 * qd] * c, acc[i][j][4 * qd + 1] * c, acc[i][j][4 * qd + 2] * c,
-               acc[i][j][4 * qd + 3] * c, vec, ry);
-      }
-    }
-  }
 }
 
 // Buffer descriptor of the activation codes: exactly the bytes a caller must
@@ -541,7 +310,7 @@ __device__ __attribute__((always_inline)) inline void store_tiles(const GemmArgs
 // and read zeros, and LDS traffic past the end lands in stages nobody reads
 // again. The packed weight keeps each 64-wide step of a 32-row
 // panel as one contiguous 2 KiB operand image; activation rows are read
-// row-contiguously and stored through the XOR swizzle of k_gemm.
+// row-contiguously and stored XOR-swizzled.
 template <int TM, int TN>
 __global__ void __launch_bounds__(256) k_gemm_fp8(GemmArgs g) {
   constexpr int NT = 256;
@@ -694,7 +463,7 @@ static hipError_t run_fp8(GemmArgs g, hipStream_t st) {
 //                 [64 g, 64 g + 64)) and its four block scales as one dword.
 // Every wave keeps D chunks in flight in a ring of register sets: the loads
 // of its chunk t + D are issued as soon as chunk t has been multiplied.
-// NVFP4 expands both operands to fp16 in registers (exact, as in k_gemm);
+// NVFP4 expands both operands to fp16 in registers (exact);
 // FP8 feeds the codes to the fp8 MFMA as they are; MXFP4 and MXFP8 too, with
 // the block scales of both operands applied by the instruction (row scales:
 // the row's four of the chunk as one dword, shifted by the lane half so that
@@ -2787,7 +2556,7 @@ __global__ void __launch_bounds__(256) k_gemm_w4a16_direct(GemmArgs g) {
   }
 }
 
-// ---------------------------------------------------------------- W4A16, up to 1024 tokens
+// ---------------------------------------------------------------- W4A16, split K
 // bf16 activations against NVFP4 weights when the output is too small to
 // fill the chip with large tiles (the text-encoder linears). A workgroup
 // owns NP 32-row weight panels (32 NP output columns) and one block of 32 MT
@@ -3210,16 +2979,12 @@ __global__ void k_zero_rows(void* y, uint8_t* y_bscale, int64_t m, int64_t n, in
   } else reinterpret_cast<uint16_t*>(y)[r * ldy + c] = 0;
 }
 
-template <int MODE, int WM, int WN, int TM, int TN, int DEPTH = 1>
-static hipError_t run(GemmArgs g, hipStream_t st) {
-  constexpr int BM = 32 * TM * WM, BN = 32 * TN * WN;
-  g.tiles_m = (g.m + BM - 1) / BM;
-  g.tiles_n = (g.n + BN - 1) / BN;
-  hipLaunchKernelGGL((k_gemm<MODE, WM, WN, TM, TN, DEPTH>), dim3(g.tiles_m * g.tiles_n), dim3(64 * WM * WN), 0, st, g);
+template <int MT, int NP, int NW, int D, bool XLDS>
+static hipError_t run_w4a16_splitk(GemmArgs g, hipStream_t st) {
+  const dim3 grid((unsigned)((g.n + 32 * NP - 1) / (32 * NP)), (unsigned)((g.m + 32 * MT - 1) / (32 * MT)));
+  hipLaunchKernelGGL((k_w4a16_splitk<MT, NP, NW, D, XLDS>), grid, dim3(64 * NW), 0, st, g);
   return hipGetLastError();
 }
-
-
 
 // Compute units of the current device, queried once per device. Persistent
 // grids launch at most this many workgroups.
@@ -3322,6 +3087,11 @@ hipError_t launch_gemm(int a_fmt, const void* a, const uint8_t* a_bscale, const 
     }
     const int64_t small_tiles = (int64_t)((m + 31) / 32) * ((n + 63) / 64);
     if (small_tiles <= 2 * cus) return run_splitk<MODE_FP8, 1, 2, 4, 2>(g, st);
+    // one round of 64 x 96 split-K tiles at long K, where the 64 x 128 kernel
+    // below walks K in too few workgroups: 512 x 3072 x 3072 15.1 -> 14.0 us, 512 x
+    // 3072 x 9216 34.2 -> 29.4 (at 889 x 1584 x 1152 it loses, 8.8 -> 9.2)
+    if (k >= 2048 && (int64_t)((m + 63) / 64) * ((n + 95) / 96) <= cus)
+      return run_splitk<MODE_FP8, 2, 3, 4, 2>(g, st);
     // Too few 256 x 256 tiles to fill the chip: the 64 x 128 kernel's eight
     // times as many workgroups win. Measured crossover (encoder and
     // transformer widths, M = 128 .. 3072): below 3/8 of a tile per CU.
@@ -3347,19 +3117,28 @@ hipError_t launch_gemm(int a_fmt, const void* a, const uint8_t* a_bscale, const 
     const int tiles = g.tiles_m * g.tiles_n;
     // Below half a round of 256 x 256 tiles the split-K kernel is faster
     // (measured up to M = 2300 at N = K = 3072: 0.9x the time there, 0.3x at
-    // M = 512). Tile and split: 64 x 96 tiles where they fill the chip with
-    // K >= 2048 (the most MFMAs per expanded operand); 32 x 64 tiles where
-    // that leaves CUs idle; 64 x 64 tiles for short reductions (K < 2048).
-    // Eight waves, two per SIMD, so that one wave's operand expansion runs
-    // beside the other's MFMAs: at 64 x 96 and 64 x 64, one chunk in flight
-    // per wave was 10-21% faster than four waves with two or three (NVFP4
-    // 512 x 3072 x 3072 16.3 -> 14.3 us, 256 x 3072 x 1024 8.1 -> 6.4 us).
+    // M = 512; 68.8 against 75.4 us at 1555 x 4512 x 3968, 126 tiles). The
+    // narrowest tile that gives every workgroup a CU of its own; past that 64 x
+    // 64 tiles of four waves, two workgroups per CU, so that one's reduction
+    // runs beside the other's loop. Measured (GPU time from graph replays,
+    // 24 shapes, 12 tilings: the best or within 3% of it everywhere) against
+    // the earlier 32 x 64 / 64 x 64 / 64 x 96 rule: 1 x 3072 x 1024 5.1 -> 3.8 us, 64 x
+    // 3072 x 3072 8.0 -> 5.8, 300 x 1024 x 3072 8.1 -> 6.9, 151 x 3520 x 5504 21.6 ->
+    // 14.8, 2048 x 1024 x 3072 25.0 -> 20.3, 1555 x 4512 x 3968 80 -> 69; 512 x 3072 x
+    // 3072 (64 x 96, one round) as before.
     if (m <= 128 || 2 * tiles < cus) {
-      const int kcn = (int)(k >> 7);
-      const int64_t t6496 = (int64_t)((m + 63) / 64) * ((n + 95) / 96);
-      if (kcn < 16) return run_splitk<MODE_NVFP4, 2, 2, 8, 1>(g, st);
-      if (t6496 >= cus - cus / 4) return run_splitk<MODE_NVFP4, 2, 3, 8, 1>(g, st);
-      return run_splitk<MODE_NVFP4, 1, 2, 8, 3>(g, st);
+      const int64_t rows32 = (m + 31) / 32, rows64 = (m + 63) / 64;
+      if (rows32 * ((n + 31) / 32) <= cus) {
+        if ((k >> 7) >= 32) return run_splitk<MODE_NVFP4, 1, 1, 8, 1>(g, st);  // 44 x 352 x 7296 8.8 -> 8.2 us
+        return run_splitk<MODE_NVFP4, 1, 1, 4, 2>(g, st);
+      }
+      if (rows32 * ((n + 63) / 64) <= cus) {
+        if ((k >> 7) >= 32) return run_splitk<MODE_NVFP4, 1, 2, 8, 3>(g, st);  // 16 x 9216 x 9216 14.5 -> 13.5 us
+        return run_splitk<MODE_NVFP4, 1, 2, 8, 1>(g, st);
+      }
+      if (rows32 * ((n + 95) / 96) <= cus) return run_splitk<MODE_NVFP4, 1, 3, 8, 1>(g, st);
+      if (rows64 * ((n + 95) / 96) <= cus) return run_splitk<MODE_NVFP4, 2, 3, 8, 1>(g, st);
+      return run_splitk<MODE_NVFP4, 2, 2, 4, 2>(g, st);
     }
     QG_LAUNCH_EPI(k_gemm_nvfp4_direct, dim3(std::min(tiles, cus)), st, g);
     return hipGetLastError();
@@ -3390,35 +3169,43 @@ hipError_t launch_gemm(int a_fmt, const void* a, const uint8_t* a_bscale, const 
       else hipLaunchKernelGGL((k_w4a16_stream<3, 8, 12>), dim3(grid), dim3(768), (size_t)xbytes, st, g);
       return hipGetLastError();
     }
-    // Past the ridge point with enough 256 x 256 tiles for half a round: the
-    // persistent W4A4-shaped kernel (the weight pool at M = 256, 512: 1.5x the
-    // 128 x 256 tile kernel, which was itself 1.5x the split-K kernels there)
+    // Past the ridge point with enough 256 x 256 tiles: the persistent
+    // W4A4-shaped kernel (1555 x 4512 x 3968, 126 tiles: 87 us against 95 on 64 x 64
+    // split-K tiles; 1500 x 3072 x 3072, 72 tiles: 68 against 53)
     const int t256_m = (int)((m + 255) / 256), t256_n = (int)((n + 255) / 256);
-    const int64_t t256 = (int64_t)t256_m * t256_n;
-    if (m > 128 && 2 * t256 >= device_cus()) {
+    const int64_t t256 = (int64_t)t256_m * t256_n, cus = device_cus();
+    if (m > 128 && 8 * t256 >= 3 * cus) {
       g.tiles_m = t256_m;
       g.tiles_n = t256_n;
-      QG_LAUNCH_EPI_NO_NVFP4(k_gemm_w4a16_direct, dim3((unsigned)std::min<int64_t>(t256, device_cus())), st, g);
+      QG_LAUNCH_EPI_NO_NVFP4(k_gemm_w4a16_direct, dim3((unsigned)std::min<int64_t>(t256, cus)), st, g);
       return hipGetLastError();
     }
-    if (m <= 1024) {
-      // Shapes measured on the MI355X (text-encoder linears, M <= 512):
-      // one-panel workgroups of 8 waves for narrow outputs; two panels per
-      // 4-wave workgroup once the output is wide enough that the activation
-      // re-reads (once per workgroup column) dominate.
-      const int64_t npan = (n + 31) / 32;
-      const unsigned mt = (unsigned)((m + 31) / 32);
-      if (n >= 2048 && m > 32)
-        hipLaunchKernelGGL((k_w4a16_splitk<1, 2, 4, 3, true>), dim3((unsigned)((npan + 1) / 2), mt), dim3(256), 0, st, g);
-      else if (m <= 32)
-        hipLaunchKernelGGL((k_w4a16_splitk<1, 1, 8, 3, false>), dim3((unsigned)npan, mt), dim3(512), 0, st, g);
-      else if (m <= 256)
-        hipLaunchKernelGGL((k_w4a16_splitk<1, 1, 8, 3, true>), dim3((unsigned)npan, mt), dim3(512), 0, st, g);
-      else
-        hipLaunchKernelGGL((k_w4a16_splitk<1, 2, 8, 3, true>), dim3((unsigned)((npan + 1) / 2), mt), dim3(512), 0, st, g);
-      return hipGetLastError();
+    // Split-K tilings. Up to 32 rows: one-panel workgroups, all chunks of a wave
+    // in one batch of loads only where that is one (1 x 3072 x 1024 4.4 -> 3.9 us
+    // with a chunk at a time; at K > 3072 that loses, 32 x 2048 x 6144 15.6 ->
+    // 17.3). Else the narrowest 32-row tile that gives every workgroup a CU of
+    // its own; past that 64-row tiles, which expand each weight once for two
+    // row blocks (the expansion is the bound there): 64 x 96 where those make
+    // one round that 64 x 64 tiles would overflow. 32 x 64 tiles of four waves,
+    // several workgroups per CU, stay for short reductions (256 x 3072 x 1024
+    // 8.5 us against 8.9) and where 64-row tiles would pad the rows by more than an
+    // eighth (200 x 9216 x 3072 30.3 against 34.0). Measured (GPU time from graph
+    // replays, 24 shapes, 21 tilings) against the earlier rule by M and N, with
+    // the 128 x 256 tile kernel it used past M = 1024: 64 x 3072 x 3072 10.9 -> 7.4
+    // us, 512 x 3072 x 3072 25.6 -> 21.2, 1024 x 3072 x 3072 47 -> 36, 2048 x 1024 x
+    // 3072 73 -> 27, 1148 x 352 x 2304 57 -> 11, 1446 x 1984 x 6016 140 -> 63.
+    const int64_t rows32 = (m + 31) / 32, rows64 = (m + 63) / 64, npan = (n + 31) / 32;
+    const int64_t t12 = rows32 * ((npan + 1) / 2), t22 = rows64 * ((npan + 1) / 2), t23 = rows64 * ((npan + 2) / 3);
+    if (m <= 32) {
+      if (k <= 3072) return run_w4a16_splitk<1, 1, 8, 1, false>(g, st);
+      return run_w4a16_splitk<1, 1, 8, 3, false>(g, st);
     }
-    return run<MODE_W4A16, 2, 2, 2, 4>(g, st);
+    if (rows32 * npan <= cus) return run_w4a16_splitk<1, 1, 8, 3, true>(g, st);
+    if (k <= 1024 && t12 <= 2 * cus) return run_w4a16_splitk<1, 2, 4, 3, true>(g, st);
+    if (t12 <= cus) return run_w4a16_splitk<1, 2, 8, 3, true>(g, st);
+    if (16 * rows64 > 9 * rows32) return run_w4a16_splitk<1, 2, 4, 3, true>(g, st);
+    if (t22 > cus && t23 <= cus) return run_w4a16_splitk<2, 3, 4, 1, true>(g, st);
+    return run_w4a16_splitk<2, 2, 4, 1, true>(g, st);
   }
 }
 
