@@ -1,7 +1,8 @@
-// quant_plan.hpp -- the launch plan of the two-launch dynamic quantizer of
-// dense tensors (quantize.hip): how many amax workgroups P leave their maxima,
-// into how many code regions G, and where region j begins. Host and device
-// share it, and a host-only test checks its invariants over many sizes.
+// quant_plan.hpp -- what host and device share of the quantizers' (quantize.hip)
+// addressing, checked by host-only tests over many sizes: the launch plan of
+// the two-launch dynamic quantizer (how many amax workgroups P leave their
+// maxima, into how many code regions G, and where region j begins), and the
+// rows of a column slice read in 16-byte units.
 #pragma once
 
 #include <hip/hip_runtime.h>
@@ -41,6 +42,31 @@ inline SlotsPlan slots_plan(int64_t n, int cb) {
   const int64_t need = (4 * P + 2 * cb - 1) / (2 * cb);  // unit pairs per region that hold the slots
   const int64_t G = std::min<int64_t>(std::min<int64_t>(kSlotsQuantGroups, (units + 1023) / 1024), pairs / need);
   return {P, G >= 1 ? G : 0};
+}
+
+// A tensor read as 16-byte units (8 elements): unit u of the tensor in row
+// order is unit c of row r, u = r upr + c. The row comes from a multiplication
+// by mul = ceil(2^shift / upr): exact for u < 2^31, since the excess e = mul upr -
+// 2^shift is below upr <= 2^(shift - 32), so u e < 2^shift, and mul < 2^33 keeps
+// the product in 64 bits. A column slice of a wider tensor is then read in the
+// same wave-contiguous runs as a dense one.
+struct UnitRows {
+  uint64_t mul = 0;
+  uint32_t upr = 0;   // units per row
+  int shift = 0;      // 32 + ceil(log2 upr)
+  int64_t pitch = 0;  // units between rows
+
+  __host__ __device__ uint32_t row_of(uint32_t u) const { return (uint32_t)((mul * u) >> shift); }
+};
+
+inline UnitRows unit_rows(int64_t cols, int64_t ldx) {  // cols % 8 == 0, ldx % 8 == 0, cols > 0
+  UnitRows r;
+  r.upr = (uint32_t)(cols / 8);
+  r.pitch = ldx / 8;
+  r.shift = 32;
+  while ((int64_t(1) << (r.shift - 32)) < (int64_t)r.upr) ++r.shift;
+  r.mul = ((uint64_t(1) << r.shift) + r.upr - 1) / r.upr;
+  return r;
 }
 
 }  // namespace qg

@@ -11,7 +11,7 @@
 // one launch (k_quant_small); a dense one of at most 3 Mi elements in two
 // (k_amax_slots, k_quant_dense_slots: the maxima handed over inside the code
 // buffer); any other is a short chain on the caller's stream:
-//   k_amax_dense / : max |x| as an integer max of bf16 magnitude bits (the
+//   k_amax_units / : max |x| as an integer max of bf16 magnitude bits (the
 //   k_amax_partial   bit pattern of a non-negative value orders like the
 //                    value); one partial per workgroup, parked in the code
 //                    buffer that the last kernel overwrites anyway
@@ -26,13 +26,20 @@ namespace qg {
 
 __global__ void k_fill_u32(uint32_t* p, uint32_t v) { *p = v; }
 
+// ---------------------------------------------------------------- units of 8
+// 16-byte unit u of a tensor (UnitRows in quant_plan.hpp); DENSE: ldx == cols.
+template <bool DENSE>
+__device__ inline uint4 load_unit(const uint4* __restrict__ x, int64_t u, const UnitRows& r) {
+  if (DENSE) return x[u];
+  const uint32_t row = r.row_of((uint32_t)u);
+  return x[(int64_t)row * r.pitch + ((uint32_t)u - row * r.upr)];
+}
+
 // ---------------------------------------------------------------- amax
-// Rows of `cols` bf16 elements, `ldx` apart. VEC: rows are 16-byte aligned
-// and cols % 8 == 0, so each step reads 8 elements with one 16-byte load.
-// Each workgroup writes the bf16 magnitude bits of its max to partial[id];
-// there are no atomics, so thousands of workgroups do not serialise on one
-// address. k_finalize reduces the partials.
-template <bool VEC>
+// Rows of `cols` bf16 elements, `ldx` apart, of any alignment. Each workgroup
+// writes the bf16 magnitude bits of its max to partial[id]; there are no
+// atomics, so thousands of workgroups do not serialise on one address.
+// k_finalize reduces the partials.
 __global__ void __launch_bounds__(256) k_amax_partial(const uint16_t* __restrict__ x, int64_t rows,
                                                       int64_t cols, int64_t ldx,
                                                       uint32_t* __restrict__ partial) {
@@ -40,33 +47,8 @@ __global__ void __launch_bounds__(256) k_amax_partial(const uint16_t* __restrict
   const int64_t stride = (int64_t)gridDim.x * 256;
   for (int64_t r = blockIdx.y; r < rows; r += gridDim.y) {
     const uint16_t* xr = x + r * ldx;
-    if (VEC) {
-      const int64_t units = cols >> 3;
-      const uint4* xv = reinterpret_cast<const uint4*>(xr);
-      int64_t u = (int64_t)blockIdx.x * 256 + threadIdx.x;
-      for (; u + 3 * stride < units; u += 4 * stride) {
-        const uint4 v0 = xv[u], v1 = xv[u + stride], v2 = xv[u + 2 * stride], v3 = xv[u + 3 * stride];
-        const uint32_t w[16] = {v0.x, v0.y, v0.z, v0.w, v1.x, v1.y, v1.z, v1.w,
-                          v2.x, v2.y, v2.z, v2.w, v3.x, v3.y, v3.z, v3.w};
-#pragma unroll
-        for (int i = 0; i < 16; ++i) {
-          const uint32_t t = w[i] & 0x7FFF7FFFu;
-          m = max(m, max(t & 0xFFFFu, t >> 16));
-        }
-      }
-      for (; u < units; u += stride) {
-        const uint4 v = xv[u];
-        const uint32_t w[4] = {v.x, v.y, v.z, v.w};
-#pragma unroll
-        for (int i = 0; i < 4; ++i) {
-          const uint32_t t = w[i] & 0x7FFF7FFFu;
-          m = max(m, max(t & 0xFFFFu, t >> 16));
-        }
-      }
-    } else {
-      for (int64_t c = (int64_t)blockIdx.x * 256 + threadIdx.x; c < cols; c += stride)
-        m = max(m, (uint32_t)(xr[c] & 0x7FFFu));
-    }
+    for (int64_t c = (int64_t)blockIdx.x * 256 + threadIdx.x; c < cols; c += stride)
+      m = max(m, (uint32_t)(xr[c] & 0x7FFFu));
   }
   for (int off = 32; off > 0; off >>= 1) m = max(m, (uint32_t)__shfl_xor((int)m, off));
   __shared__ uint32_t part[4];
@@ -76,15 +58,17 @@ __global__ void __launch_bounds__(256) k_amax_partial(const uint16_t* __restrict
     partial[blockIdx.y * gridDim.x + blockIdx.x] = max(max(part[0], part[1]), max(part[2], part[3]));
 }
 
-// Dense, 16-byte aligned tensors of `units` 8-element units: a grid of at most
+// 16-byte aligned rows of whole 8-element units: a grid of at most
 // kAmaxGroups workgroups strides over blocks of 1024 units, each block read
 // as four wave-contiguous runs with all four 16-byte loads of a thread issued
 // before the first max. Measured against one-shot grids (every workgroup one
-// block of 1024, 2048 or 4096 units): 3.5 us faster on a 4608 x 3072
-// activation, 1.3 us on 4608 x 9216.
+// block of 1024, 2048 or 4096 units): 3.5 us faster on a dense 4608 x 3072
+// activation, 1.3 us on 4608 x 9216. The same columns as a slice of 9216-wide
+// rows: 6.7 -> 4.4 us against a workgroup per row (kernel trace).
 constexpr int64_t kAmaxGroups = 1024;  // four workgroups per CU on 256 CUs
 
-__global__ void __launch_bounds__(256) k_amax_dense(const uint16_t* __restrict__ x, int64_t units,
+template <bool DENSE>
+__global__ void __launch_bounds__(256) k_amax_units(const uint16_t* __restrict__ x, int64_t units, UnitRows rows,
                                                     uint32_t* __restrict__ partial) {
   constexpr int U = 4;
   const uint4* xv = reinterpret_cast<const uint4*>(x);
@@ -92,7 +76,8 @@ __global__ void __launch_bounds__(256) k_amax_dense(const uint16_t* __restrict__
   for (int64_t base = (int64_t)blockIdx.x * 256 * U + threadIdx.x; base < units; base += (int64_t)gridDim.x * 256 * U) {
     uint4 v[U];
 #pragma unroll
-    for (int u = 0; u < U; ++u) v[u] = (base + u * 256 < units) ? xv[base + u * 256] : make_uint4(0u, 0u, 0u, 0u);
+    for (int u = 0; u < U; ++u)
+      v[u] = (base + u * 256 < units) ? load_unit<DENSE>(xv, base + u * 256, rows) : make_uint4(0u, 0u, 0u, 0u);
 #pragma unroll
     for (int u = 0; u < U; ++u) {
       const uint32_t w[4] = {v[u].x, v[u].y, v[u].z, v[u].w};
@@ -162,15 +147,19 @@ __device__ inline void unit_load(const uint16_t* __restrict__ p, int64_t cnt, ui
 // FP8 codes of a unit: q = E4M3(x * r) by the hardware conversion (hw_e4m3x4,
 // equal to enc_e4m3 on every finite input); one 16-byte store when vec_store
 // (whole unit, 16-byte aligned destination), else byte stores.
-__device__ inline void quant_fp8_words(const uint32_t (&w)[8], int64_t cnt, uint8_t* __restrict__ dst, float r,
-                                       bool vec_store) {
-  uint32_t c[4];
+__device__ inline void fp8_words(const uint32_t (&w)[8], uint32_t (&c)[4], float r) {
 #pragma unroll
   for (int i = 0; i < 4; ++i) {
     const float y[4] = {__fmul_rn(bf16_lo(w[2 * i]), r), __fmul_rn(bf16_hi(w[2 * i]), r),
                         __fmul_rn(bf16_lo(w[2 * i + 1]), r), __fmul_rn(bf16_hi(w[2 * i + 1]), r)};
     c[i] = hw_e4m3x4(y);
   }
+}
+
+__device__ inline void quant_fp8_words(const uint32_t (&w)[8], int64_t cnt, uint8_t* __restrict__ dst, float r,
+                                       bool vec_store) {
+  uint32_t c[4];
+  fp8_words(w, c, r);
   if (vec_store && cnt == 16) {
     *reinterpret_cast<uint4*>(dst) = make_uint4(c[0], c[1], c[2], c[3]);
   } else {
@@ -208,8 +197,8 @@ __device__ inline uint32_t quant_nvfp4_words(const uint32_t (&w)[8], uint8_t* __
 // One thread codes 16 consecutive elements of a row: q = E4M3(x * r), r = 1/s.
 // CONTIG: the tensor is one dense run of n elements (ldx == cols); a thread
 // owns elements [16 t, 16 t + 16) and the last thread may be partial.
-// Otherwise rows are handled as units of 16 (VEC requires cols % 16 == 0).
-template <bool VEC, bool CONTIG>
+// Otherwise rows are handled as units of 16. Rows of any alignment.
+template <bool CONTIG>
 __global__ void __launch_bounds__(256) k_quant_fp8(const uint16_t* __restrict__ x, int64_t rows,
                                                    int64_t cols, int64_t ldx,
                                                    uint8_t* __restrict__ q,
@@ -232,13 +221,13 @@ __global__ void __launch_bounds__(256) k_quant_fp8(const uint16_t* __restrict__ 
     cnt = min((int64_t)16, cols - u * 16);
   }
   uint32_t w[8];
-  unit_load<VEC>(x + src, cnt, w);
-  quant_fp8_words(w, cnt, q + dst, r, VEC);
+  unit_load<false>(x + src, cnt, w);
+  quant_fp8_words(w, cnt, q + dst, r, false);
 }
 
 // ---------------------------------------------------------------- NVFP4
-// One thread per 16-element block.
-template <bool VEC, bool CONTIG>
+// One thread per 16-element block; rows of any alignment.
+template <bool CONTIG>
 __global__ void __launch_bounds__(256) k_quant_nvfp4(const uint16_t* __restrict__ x, int64_t rows,
                                                      int64_t cols, int64_t ldx,
                                                      uint8_t* __restrict__ q,
@@ -256,7 +245,7 @@ __global__ void __launch_bounds__(256) k_quant_nvfp4(const uint16_t* __restrict_
     src = row * ldx + b * 16;
   }
   uint32_t w[8];
-  unit_load<VEC>(x + src, 16, w);
+  unit_load<false>(x + src, 16, w);
   bscale[t] = (uint8_t)quant_nvfp4_words(w, q + t * 8, *tscale);
 }
 
@@ -388,55 +377,53 @@ __device__ inline void code_units8_nv_pair(const uint4 (&raw)[2], const int64_t 
   }
 }
 
-// Dense tensors (ldx == cols, 16-byte aligned rows): each wavefront codes a
-// chunk of 512 H consecutive elements. Lane l reads elements
-// [512 h + 8l, 512 h + 8l + 8) of the chunk for h < H with one 16-byte load
-// each, all issued before the first is used, so every load and store
-// instruction of the wave covers one contiguous run of memory and H loads
-// per lane are in flight. Elements are coded with the hardware conversions
-// (hw_e4m3x4 / hw_e2m1x8). NVFP4: n % 16 == 0, so lanes (2j, 2j+1) hold one
-// whole 16-element block (or both lie past the end); the block max is shared
-// with one lane swap, and each lane of the pair derives the scale of one of
-// the two blocks the pair holds in two consecutive steps.
-template <int FMT, int H>
-__global__ void __launch_bounds__(256) k_quant_dense(const uint16_t* __restrict__ x, int64_t n,
-                                                     uint8_t* __restrict__ q,
-                                                     uint8_t* __restrict__ bscale,
+// 16-byte aligned rows of whole 8-element units (dense FP8 tensors may end in a
+// shorter one): each lane codes H blocks of 16 consecutive elements, 64 blocks
+// apart (two adjacent 16-byte loads each, all issued before the first is used),
+// and writes FP8 codes with one 16-byte store, NVFP4 with an 8-byte store and
+// its scale byte. HBM-bound. H: one where the scale is the caller's, two in the
+// dynamic chain, where every wave waits for the scale the kernel before just
+// wrote (4608 x 3072 FP8, static: H = 1 7.4 us, H = 2 7.8; chain 15.9 and 14.0).
+// Against lanes of 8 elements (8-byte stores, a block's two divisions shared
+// over a lane pair), four loads apart: static FP8 4608 x 3072 8.4 -> 7.4 us,
+// 512 x 3072 2.7 -> 2.4, NVFP4 8.1 -> 7.3; chain 14.3 -> 14.0, 14.6 -> 14.2.
+// PLAIN: whole blocks and 16-byte aligned codes (NVFP4 always); behind run-time
+// branches in one kernel the FP8 case lost half of that (7.4 -> 8.2 us).
+template <int FMT, int H, bool DENSE, bool PLAIN>
+__global__ void __launch_bounds__(256) k_quant_units(const uint16_t* __restrict__ x, int64_t n, UnitRows rows,
+                                                     uint8_t* __restrict__ q, uint8_t* __restrict__ bscale,
                                                      const float* __restrict__ tscale) {
-  const int lane = threadIdx.x & 63;
-  const int64_t chunk = ((int64_t)blockIdx.x * 256 + threadIdx.x) >> 6;
-  uint4 raw[H];
+  const int64_t b0 = (((int64_t)blockIdx.x * 256 + threadIdx.x) >> 6) * (64 * H) + (threadIdx.x & 63);
+  const uint4* xv = reinterpret_cast<const uint4*>(x);
+  uint32_t w[H][8];
 #pragma unroll
   for (int h = 0; h < H; ++h) {
-    const int64_t e0 = chunk * (512 * H) + h * 512 + lane * 8;
-    raw[h] = (e0 + 8 <= n) ? *reinterpret_cast<const uint4*>(x + e0) : make_uint4(0u, 0u, 0u, 0u);
+    const int64_t e = 16 * (b0 + 64 * h);
+    const uint4 lo = (e + (PLAIN ? 16 : 8) <= n) ? load_unit<DENSE>(xv, e >> 3, rows) : make_uint4(0u, 0u, 0u, 0u);
+    const uint4 hi = (e + 16 <= n) ? load_unit<DENSE>(xv, (e >> 3) + 1, rows) : make_uint4(0u, 0u, 0u, 0u);
+    w[h][0] = lo.x; w[h][1] = lo.y; w[h][2] = lo.z; w[h][3] = lo.w;
+    w[h][4] = hi.x; w[h][5] = hi.y; w[h][6] = hi.z; w[h][7] = hi.w;
   }
   const float s = *tscale;
   const float r = (FMT == 1 && s > 0.0f) ? __fdiv_rn(1.0f, s) : 0.0f;
-  const float d_t = __fmul_rn(6.0f, s);
-  if constexpr (FMT == 2) {
-    static_assert(H % 2 == 0, "NVFP4 steps go in pairs");
 #pragma unroll
-    for (int h = 0; h < H; h += 2) {
-      const int64_t e0 = chunk * (512 * H) + h * 512 + lane * 8;
-      const uint4 rw[2] = {raw[h], raw[h + 1]};
-      const int64_t u[2] = {e0 >> 3, (e0 + 512) >> 3};
-      const bool in[2] = {e0 + 8 <= n, e0 + 520 <= n};
-      code_units8_nv_pair(rw, u, in, q, bscale, s, d_t, lane);
+  for (int h = 0; h < H; ++h) {
+    const int64_t b = b0 + 64 * h, left = n - 16 * b;
+    if (left <= 0) continue;
+    if (FMT == 2) {
+      bscale[b] = (uint8_t)quant_nvfp4_words(w[h], q + 8 * b, s);
+      continue;
     }
-  } else {
-#pragma unroll
-    for (int h = 0; h < H; ++h) {
-      const int64_t e0 = chunk * (512 * H) + h * 512 + lane * 8;
-      const bool full = (e0 + 8 <= n);
-      code_unit8_fp8(raw[h], e0 >> 3, full, q, r);
-      if (!full && e0 < n) {  // FP8 tail unit of fewer than 8 elements
-        float y[8];
-#pragma unroll
-        for (int j = 0; j < 8; ++j) y[j] = (e0 + j < n) ? __fmul_rn(u2f((uint32_t)x[e0 + j] << 16), r) : 0.0f;
-        const uint32_t lo = hw_e4m3x4(y), hi = hw_e4m3x4(y + 4);
-        for (int j = 0; j < 8 && e0 + j < n; ++j) q[e0 + j] = (uint8_t)(((j < 4 ? lo : hi) >> (8 * (j & 3))) & 0xFFu);
-      }
+    if (PLAIN) {
+      quant_fp8_words(w[h], 16, q + 16 * b, r, true);
+    } else if (left >= 16) {
+      uint32_t c[4];
+      fp8_words(w[h], c, r);
+      reinterpret_cast<uint2*>(q + 16 * b)[0] = make_uint2(c[0], c[1]);
+      reinterpret_cast<uint2*>(q + 16 * b)[1] = make_uint2(c[2], c[3]);
+    } else {  // the last block; a dense tensor's may hold part of a unit
+      if (DENSE) unit_load<false>(x + 16 * b, left, w[h]);
+      quant_fp8_words(w[h], left, q + 16 * b, r, false);
     }
   }
 }
@@ -456,15 +443,16 @@ __global__ void __launch_bounds__(256) k_quant_dense(const uint16_t* __restrict_
 // that every region's codes hold the 4 P bytes of slots.
 // (the plan: slot_region_lo, slots_plan and their limits in quant_plan.hpp)
 
-template <int U>
-__global__ void __launch_bounds__(256) k_amax_slots(const uint16_t* __restrict__ x, int64_t units,
+template <int U, bool DENSE>
+__global__ void __launch_bounds__(256) k_amax_slots(const uint16_t* __restrict__ x, int64_t units, UnitRows rows,
                                                     uint8_t* __restrict__ q, int cb, int gq) {
   const uint4* xv = reinterpret_cast<const uint4*>(x);
   uint32_t m = 0;
   for (int64_t base = (int64_t)blockIdx.x * 256 * U + threadIdx.x; base < units; base += (int64_t)gridDim.x * 256 * U) {
     uint4 v[U];
 #pragma unroll
-    for (int u = 0; u < U; ++u) v[u] = (base + u * 256 < units) ? xv[base + u * 256] : make_uint4(0u, 0u, 0u, 0u);
+    for (int u = 0; u < U; ++u)
+      v[u] = (base + u * 256 < units) ? load_unit<DENSE>(xv, base + u * 256, rows) : make_uint4(0u, 0u, 0u, 0u);
 #pragma unroll
     for (int u = 0; u < U; ++u) {
       const uint32_t w[4] = {v[u].x, v[u].y, v[u].z, v[u].w};
@@ -491,8 +479,8 @@ __global__ void __launch_bounds__(256) k_amax_slots(const uint16_t* __restrict__
 
 // Each wave codes runs of 64 consecutive units (one 16-byte load per lane,
 // four per lane in flight); rounds of 1024 units until the region ends.
-template <int FMT>
-__global__ void __launch_bounds__(256) k_quant_dense_slots(const uint16_t* __restrict__ x, int64_t units,
+template <int FMT, bool DENSE>
+__global__ void __launch_bounds__(256) k_quant_dense_slots(const uint16_t* __restrict__ x, int64_t units, UnitRows rows,
                                                            uint8_t* __restrict__ q, uint8_t* __restrict__ bscale,
                                                            float* __restrict__ tscale, int P) {
   constexpr int H = 4;
@@ -506,7 +494,7 @@ __global__ void __launch_bounds__(256) k_quant_dense_slots(const uint16_t* __res
 #pragma unroll
   for (int h = 0; h < H; ++h) {
     const int64_t u = lo + 256 * wv + 64 * h + lane;
-    raw[h] = (u < hi) ? xv[u] : make_uint4(0u, 0u, 0u, 0u);
+    raw[h] = (u < hi) ? load_unit<DENSE>(xv, u, rows) : make_uint4(0u, 0u, 0u, 0u);
   }
   // the tensor max from this region's slots, all read before the barrier
   const uint32_t* slots = reinterpret_cast<const uint32_t*>(q + lo * CB);
@@ -543,7 +531,7 @@ __global__ void __launch_bounds__(256) k_quant_dense_slots(const uint16_t* __res
 #pragma unroll
     for (int h = 0; h < H; ++h) {
       const int64_t u = base + 256 * wv + 64 * h + lane;
-      raw[h] = (u < hi) ? xv[u] : make_uint4(0u, 0u, 0u, 0u);
+      raw[h] = (u < hi) ? load_unit<DENSE>(xv, u, rows) : make_uint4(0u, 0u, 0u, 0u);
     }
   }
 }
@@ -555,41 +543,14 @@ __global__ void __launch_bounds__(256) k_quant_dense_slots(const uint16_t* __res
 // (emax 2 for E2M1, 8 for E4M3), E8M0 code = that + 127 clamped to [0, 254],
 // 0 for an all-zero block; elements = RNE_sat(x * 2^(127 - code)), the
 // multiply exact (a power of two, inside the normal range for bf16 inputs).
-// One thread codes 8 consecutive elements of a row; rows hold whole blocks
-// (cols % 32 == 0), so the 4 threads of a block are lanes 4j .. 4j + 3 of one
-// wave and share its max with two lane swaps. VEC: 16-byte aligned rows.
-template <bool FP4, bool VEC>
-__global__ void __launch_bounds__(256) k_quant_mx(const uint16_t* __restrict__ x, int64_t rows, int64_t cols,
-                                                  int64_t ldx, uint8_t* __restrict__ q,
-                                                  uint8_t* __restrict__ scales) {
-  const int64_t upr = cols >> 3;  // 8-element units per row
-  const int64_t u = (int64_t)blockIdx.x * 256 + threadIdx.x;
-  const bool live = u < rows * upr;
-  const int64_t row = live ? u / upr : 0, c8 = live ? u - row * upr : 0;
-  float v[8];
-  if (live) {
-    const uint16_t* p = x + row * ldx + 8 * c8;
-    if (VEC) {
-      const uint4 w = *reinterpret_cast<const uint4*>(p);
-      const uint32_t ww[4] = {w.x, w.y, w.z, w.w};
-#pragma unroll
-      for (int j = 0; j < 4; ++j) {
-        v[2 * j] = bf16_lo(ww[j]);
-        v[2 * j + 1] = bf16_hi(ww[j]);
-      }
-    } else {
-#pragma unroll
-      for (int j = 0; j < 8; ++j) v[j] = u2f((uint32_t)p[j] << 16);
-    }
-  } else {
-#pragma unroll
-    for (int j = 0; j < 8; ++j) v[j] = 0.0f;
-  }
-  uint32_t am = 0;
-#pragma unroll
-  for (int j = 0; j < 8; ++j) am = max(am, f2u(v[j]) & 0x7FFFFFFFu);
-  am = max(am, (uint32_t)__shfl_xor((int)am, 1));
-  am = max(am, (uint32_t)__shfl_xor((int)am, 2));
+// Rows hold whole blocks (cols % 32 == 0), so the four 8-element units of a
+// block are units 4 j .. 4 j + 3 of the tensor and lanes 4 j .. 4 j + 3 of one
+// wave, which share its max with two lane swaps.
+
+// E8M0 code of a block from the fp32 bits of its largest magnitude and the
+// factor its elements are multiplied by.
+template <bool FP4>
+__device__ inline uint32_t mx_block(uint32_t am, float& r) {
   // floor(log2(max)) from the fp32 bits (normal or denormal), then the code.
   // A block holding inf or NaN gets the E8M0 NaN code 255 (its element codes
   // are then unspecified: r = 0 makes them signed zeros).
@@ -602,7 +563,87 @@ __global__ void __launch_bounds__(256) k_quant_mx(const uint16_t* __restrict__ x
     e = min(max(fl - (FP4 ? 2 : 8) + 127, 0), 254);
   }
   // 2^(127 - e); finite bf16 inputs give e <= 252, so this is a normal number
-  const float r = (e == 255) ? 0.0f : u2f((uint32_t)(254 - e) << 23);
+  r = (e == 255) ? 0.0f : u2f((uint32_t)(254 - e) << 23);
+  return (uint32_t)e;
+}
+
+// 16-byte aligned rows. Each lane codes H half blocks of 16 elements, 64 apart
+// (two adjacent 16-byte loads each, all issued before the first is used); a lane
+// pair shares a block's max. Codes and scales are contiguous in unit order, so
+// every store instruction of a wave covers one run. HBM-bound; against one unit
+// of 8 per thread with a 64-bit division: MXFP4 4608 x 3072 8.5 -> 7.0 us, MXFP8
+// 2800 x 3072 6.8 -> 5.7, 4608 x 9216 26.5 -> 23.9 (two half blocks per lane were
+// 3-10% slower). PLAIN: codes aligned to a half block's (MXFP8 16 bytes, MXFP4 8;
+// MXFP4 codes are always 4-byte aligned).
+template <bool FP4, int H, bool DENSE, bool PLAIN>
+__global__ void __launch_bounds__(256) k_quant_mx_units(const uint16_t* __restrict__ x, int64_t halves, UnitRows rows,
+                                                        uint8_t* __restrict__ q, uint8_t* __restrict__ scales) {
+  const int64_t b0 = (((int64_t)blockIdx.x * 256 + threadIdx.x) >> 6) * (64 * H) + (threadIdx.x & 63);
+  const uint4* xv = reinterpret_cast<const uint4*>(x);
+  uint32_t w[H][8];
+#pragma unroll
+  for (int h = 0; h < H; ++h) {
+    uint4 lo = make_uint4(0u, 0u, 0u, 0u), hi = lo;
+    if (b0 + 64 * h < halves) {
+      lo = load_unit<DENSE>(xv, 2 * (b0 + 64 * h), rows);
+      hi = load_unit<DENSE>(xv, 2 * (b0 + 64 * h) + 1, rows);
+    }
+    w[h][0] = lo.x; w[h][1] = lo.y; w[h][2] = lo.z; w[h][3] = lo.w;
+    w[h][4] = hi.x; w[h][5] = hi.y; w[h][6] = hi.z; w[h][7] = hi.w;
+  }
+#pragma unroll
+  for (int h = 0; h < H; ++h) {
+    const int64_t b = b0 + 64 * h;
+    uint32_t am = 0;  // bf16 magnitude bits
+#pragma unroll
+    for (int j = 0; j < 8; ++j) {
+      const uint32_t t = w[h][j] & 0x7FFF7FFFu;
+      am = max(am, max(t & 0xFFFFu, t >> 16));
+    }
+    am = max(am, (uint32_t)__shfl_xor((int)am, 1));
+    float r;
+    const uint32_t e = mx_block<FP4>(am << 16, r);
+    if (b >= halves) continue;
+    if (FP4) {
+      float y[16];
+#pragma unroll
+      for (int j = 0; j < 8; ++j) {
+        y[2 * j] = __fmul_rn(bf16_lo(w[h][j]), r);
+        y[2 * j + 1] = __fmul_rn(bf16_hi(w[h][j]), r);
+      }
+      const uint32_t c0 = hw_e2m1x8(y), c1 = hw_e2m1x8(y + 8);
+      if (PLAIN) {
+        reinterpret_cast<uint2*>(q)[b] = make_uint2(c0, c1);
+      } else {
+        reinterpret_cast<uint32_t*>(q)[2 * b] = c0;
+        reinterpret_cast<uint32_t*>(q)[2 * b + 1] = c1;
+      }
+    } else {
+      quant_fp8_words(w[h], 16, q + 16 * b, r, PLAIN);
+    }
+    if ((b & 1) == 0) scales[b >> 1] = (uint8_t)e;
+  }
+}
+
+// Rows of any alignment: one unit per thread.
+template <bool FP4>
+__global__ void __launch_bounds__(256) k_quant_mx(const uint16_t* __restrict__ x, int64_t rows, int64_t cols,
+                                                  int64_t ldx, uint8_t* __restrict__ q,
+                                                  uint8_t* __restrict__ scales) {
+  const int64_t upr = cols >> 3;  // 8-element units per row
+  const int64_t u = (int64_t)blockIdx.x * 256 + threadIdx.x;
+  const bool live = u < rows * upr;
+  const int64_t row = live ? u / upr : 0, c8 = live ? u - row * upr : 0;
+  float v[8];
+#pragma unroll
+  for (int j = 0; j < 8; ++j) v[j] = live ? u2f((uint32_t)x[row * ldx + 8 * c8 + j] << 16) : 0.0f;
+  uint32_t am = 0;
+#pragma unroll
+  for (int j = 0; j < 8; ++j) am = max(am, f2u(v[j]) & 0x7FFFFFFFu);
+  am = max(am, (uint32_t)__shfl_xor((int)am, 1));
+  am = max(am, (uint32_t)__shfl_xor((int)am, 2));
+  float r;
+  const uint32_t e = mx_block<FP4>(am, r);
   float y[8];
 #pragma unroll
   for (int j = 0; j < 8; ++j) y[j] = __fmul_rn(v[j], r);
@@ -719,66 +760,96 @@ __global__ void __launch_bounds__(256) k_dequant_mx(const uint8_t* __restrict__ 
 // ---------------------------------------------------------------- launchers
 static inline unsigned grid_for(int64_t threads) { return (unsigned)((threads + 255) / 256); }
 
+// Whether the unit kernels take rows of this tensor: 16-byte aligned units,
+// whole ones in every row, and (a slice) unit numbers below 2^31.
+static inline bool unit_tensor(const uint16_t* x, int64_t rows, int64_t cols, int64_t ldx) {
+  if (reinterpret_cast<uintptr_t>(x) % 16 != 0) return false;
+  return ldx == cols || (ldx % 8 == 0 && cols % 8 == 0 && rows <= (int64_t(1) << 31) / (cols / 8));
+}
+
+template <int H, bool DENSE>
+static void launch_units(int fmt, const uint16_t* x, int64_t n, const UnitRows& ur, uint8_t* codes, uint8_t* bscale,
+                         const float* tscale, hipStream_t st) {
+  const dim3 g((unsigned)((n + 4096 * H - 1) / (4096 * H)));  // 4 waves x 64 H blocks of 16 per workgroup
+  const bool plain = reinterpret_cast<uintptr_t>(codes) % 16 == 0 && n % 16 == 0;
+  if (fmt == 2)
+    hipLaunchKernelGGL((k_quant_units<2, H, DENSE, true>), g, dim3(256), 0, st, x, n, ur, codes, bscale, tscale);
+  else if (plain)
+    hipLaunchKernelGGL((k_quant_units<1, H, DENSE, true>), g, dim3(256), 0, st, x, n, ur, codes, bscale, tscale);
+  else
+    hipLaunchKernelGGL((k_quant_units<1, H, DENSE, false>), g, dim3(256), 0, st, x, n, ur, codes, bscale, tscale);
+}
+
 // The element kernels alone, reading a finished decode scale from `tscale`:
-// the last kernel of the dynamic chain, and the whole of a quantization with
-// a static (calibrated) scale.
-hipError_t launch_quantize_static(int fmt, const uint16_t* x, int64_t rows, int64_t cols, int64_t ldx,
-                                  uint8_t* codes, uint8_t* bscale, const float* tscale, hipStream_t st) {
+// the last kernel of the dynamic chain (chained), and the whole of a
+// quantization with a static (calibrated) scale.
+static hipError_t launch_elements(int fmt, const uint16_t* x, int64_t rows, int64_t cols, int64_t ldx, uint8_t* codes,
+                                  uint8_t* bscale, const float* tscale, bool chained, hipStream_t st) {
   if (rows == 0 || cols == 0) return hipSuccess;
   const bool contig = (ldx == cols);
-  const bool aligned = (reinterpret_cast<uintptr_t>(x) % 16 == 0);
   const int64_t n = rows * cols;
-  const bool qal = (reinterpret_cast<uintptr_t>(codes) % 8 == 0);
-  if (contig && aligned && qal) {
-    const unsigned g = (unsigned)((n + 8191) / 8192);  // 4 waves x 2048 elements per workgroup
-    if (fmt == 1) hipLaunchKernelGGL((k_quant_dense<1, 4>), dim3(g), dim3(256), 0, st, x, n, codes, bscale, tscale);
-    else hipLaunchKernelGGL((k_quant_dense<2, 4>), dim3(g), dim3(256), 0, st, x, n, codes, bscale, tscale);
+  if (unit_tensor(x, rows, cols, ldx) && reinterpret_cast<uintptr_t>(codes) % 8 == 0) {
+    const UnitRows ur = contig ? UnitRows() : unit_rows(cols, ldx);
+    if (contig && chained) launch_units<2, true>(fmt, x, n, ur, codes, bscale, tscale, st);
+    else if (contig) launch_units<1, true>(fmt, x, n, ur, codes, bscale, tscale, st);
+    else if (chained) launch_units<2, false>(fmt, x, n, ur, codes, bscale, tscale, st);
+    else launch_units<1, false>(fmt, x, n, ur, codes, bscale, tscale, st);
   } else if (fmt == 1) {
-    const bool qal16 = (reinterpret_cast<uintptr_t>(codes) % 16 == 0);
-    if (contig) {
-      const bool vec = aligned && qal16;
-      const unsigned g = grid_for((rows * cols + 15) / 16);
-      if (vec) hipLaunchKernelGGL((k_quant_fp8<true, true>), dim3(g), dim3(256), 0, st, x, rows, cols, ldx, codes, tscale);
-      else hipLaunchKernelGGL((k_quant_fp8<false, true>), dim3(g), dim3(256), 0, st, x, rows, cols, ldx, codes, tscale);
-    } else {
-      const bool vec = aligned && qal16 && (ldx % 8 == 0) && (cols % 16 == 0);
-      const unsigned g = grid_for(rows * ((cols + 15) / 16));
-      if (vec) hipLaunchKernelGGL((k_quant_fp8<true, false>), dim3(g), dim3(256), 0, st, x, rows, cols, ldx, codes, tscale);
-      else hipLaunchKernelGGL((k_quant_fp8<false, false>), dim3(g), dim3(256), 0, st, x, rows, cols, ldx, codes, tscale);
-    }
+    const unsigned g = grid_for(contig ? (n + 15) / 16 : rows * ((cols + 15) / 16));
+    if (contig) hipLaunchKernelGGL((k_quant_fp8<true>), dim3(g), dim3(256), 0, st, x, rows, cols, ldx, codes, tscale);
+    else hipLaunchKernelGGL((k_quant_fp8<false>), dim3(g), dim3(256), 0, st, x, rows, cols, ldx, codes, tscale);
   } else {
     const unsigned g = grid_for(rows * (cols / 16));
-    const bool vec = aligned && (contig || ldx % 8 == 0);
-    if (contig) {
-      if (vec) hipLaunchKernelGGL((k_quant_nvfp4<true, true>), dim3(g), dim3(256), 0, st, x, rows, cols, ldx, codes, bscale, tscale);
-      else hipLaunchKernelGGL((k_quant_nvfp4<false, true>), dim3(g), dim3(256), 0, st, x, rows, cols, ldx, codes, bscale, tscale);
-    } else {
-      if (vec) hipLaunchKernelGGL((k_quant_nvfp4<true, false>), dim3(g), dim3(256), 0, st, x, rows, cols, ldx, codes, bscale, tscale);
-      else hipLaunchKernelGGL((k_quant_nvfp4<false, false>), dim3(g), dim3(256), 0, st, x, rows, cols, ldx, codes, bscale, tscale);
-    }
+    if (contig) hipLaunchKernelGGL((k_quant_nvfp4<true>), dim3(g), dim3(256), 0, st, x, rows, cols, ldx, codes, bscale, tscale);
+    else hipLaunchKernelGGL((k_quant_nvfp4<false>), dim3(g), dim3(256), 0, st, x, rows, cols, ldx, codes, bscale, tscale);
   }
   return hipGetLastError();
 }
 
+hipError_t launch_quantize_static(int fmt, const uint16_t* x, int64_t rows, int64_t cols, int64_t ldx,
+                                  uint8_t* codes, uint8_t* bscale, const float* tscale, hipStream_t st) {
+  return launch_elements(fmt, x, rows, cols, ldx, codes, bscale, tscale, false, st);
+}
+
 // MX formats: block scales only, one kernel.
-static hipError_t launch_quantize_mx(int fmt, const uint16_t* x, int64_t rows, int64_t cols, int64_t ldx,
+template <bool FP4>
+static hipError_t launch_quantize_mx(const uint16_t* x, int64_t rows, int64_t cols, int64_t ldx,
                                      uint8_t* codes, uint8_t* scales, hipStream_t st) {
   if (rows == 0 || cols == 0) return hipSuccess;
-  const unsigned g = grid_for(rows * (cols / 8));
-  const bool vec = (reinterpret_cast<uintptr_t>(x) % 16 == 0) && (ldx % 8 == 0);
-  if (fmt == 3) {
-    if (vec) hipLaunchKernelGGL((k_quant_mx<true, true>), dim3(g), dim3(256), 0, st, x, rows, cols, ldx, codes, scales);
-    else hipLaunchKernelGGL((k_quant_mx<true, false>), dim3(g), dim3(256), 0, st, x, rows, cols, ldx, codes, scales);
+  const int64_t units = rows * (cols / 8);
+  if (!unit_tensor(x, rows, cols, ldx)) {
+    hipLaunchKernelGGL((k_quant_mx<FP4>), dim3(grid_for(units)), dim3(256), 0, st, x, rows, cols, ldx, codes, scales);
+    return hipGetLastError();
+  }
+  constexpr int H = 1;
+  const bool plain = reinterpret_cast<uintptr_t>(codes) % (FP4 ? 8 : 16) == 0;
+  const int64_t halves = units / 2;
+  const dim3 g((unsigned)((halves + 256 * H - 1) / (256 * H)));
+  if (ldx == cols) {
+    const UnitRows ur;
+    if (plain) hipLaunchKernelGGL((k_quant_mx_units<FP4, H, true, true>), g, dim3(256), 0, st, x, halves, ur, codes, scales);
+    else hipLaunchKernelGGL((k_quant_mx_units<FP4, H, true, false>), g, dim3(256), 0, st, x, halves, ur, codes, scales);
   } else {
-    if (vec) hipLaunchKernelGGL((k_quant_mx<false, true>), dim3(g), dim3(256), 0, st, x, rows, cols, ldx, codes, scales);
-    else hipLaunchKernelGGL((k_quant_mx<false, false>), dim3(g), dim3(256), 0, st, x, rows, cols, ldx, codes, scales);
+    const UnitRows ur = unit_rows(cols, ldx);
+    if (plain) hipLaunchKernelGGL((k_quant_mx_units<FP4, H, false, true>), g, dim3(256), 0, st, x, halves, ur, codes, scales);
+    else hipLaunchKernelGGL((k_quant_mx_units<FP4, H, false, false>), g, dim3(256), 0, st, x, halves, ur, codes, scales);
   }
   return hipGetLastError();
+}
+
+template <int FMT, bool DENSE>
+static void launch_slots(const uint16_t* x, int64_t units, const UnitRows& ur, uint8_t* codes, uint8_t* bscale,
+                         float* tscale, const SlotsPlan& plan, hipStream_t st) {
+  hipLaunchKernelGGL((k_amax_slots<kSlotsAmaxLoads, DENSE>), dim3((unsigned)plan.P), dim3(256), 0, st, x, units, ur,
+                     codes, FMT == 1 ? 8 : 4, (int)plan.G);
+  hipLaunchKernelGGL((k_quant_dense_slots<FMT, DENSE>), dim3((unsigned)plan.G), dim3(256), 0, st, x, units, ur, codes,
+                     bscale, tscale, (int)plan.P);
 }
 
 hipError_t launch_quantize(int fmt, const uint16_t* x, int64_t rows, int64_t cols, int64_t ldx,
                            uint8_t* codes, uint8_t* bscale, float* tscale, hipStream_t st) {
-  if (fmt == 3 || fmt == 4) return launch_quantize_mx(fmt, x, rows, cols, ldx, codes, bscale, st);
+  if (fmt == 3) return launch_quantize_mx<true>(x, rows, cols, ldx, codes, bscale, st);
+  if (fmt == 4) return launch_quantize_mx<false>(x, rows, cols, ldx, codes, bscale, st);
   if (rows == 0 || cols == 0) {
     hipLaunchKernelGGL(k_fill_u32, dim3(1), dim3(1), 0, st, reinterpret_cast<uint32_t*>(tscale), 0u);
     return hipGetLastError();
@@ -807,56 +878,49 @@ hipError_t launch_quantize(int fmt, const uint16_t* x, int64_t rows, int64_t col
     return hipGetLastError();
   }
   const int64_t n = rows * cols;
-  if (contig && aligned && reinterpret_cast<uintptr_t>(codes) % 8 == 0) {
-    // dense: two launches, the maxima handed over in every code region
-    const int64_t units = n / 8;
-    const int cb = (fmt == 1) ? 8 : 4;
-    const SlotsPlan plan = slots_plan(n, cb);
-    const int64_t P = plan.P, G = plan.G;
-    if (G >= 1) {
-      hipLaunchKernelGGL(k_amax_slots<kSlotsAmaxLoads>, dim3((unsigned)P), dim3(256), 0, st, x, units, codes, cb, (int)G);
-      if (fmt == 1)
-        hipLaunchKernelGGL(k_quant_dense_slots<1>, dim3((unsigned)G), dim3(256), 0, st, x, units, codes, bscale, tscale, (int)P);
-      else
-        hipLaunchKernelGGL(k_quant_dense_slots<2>, dim3((unsigned)G), dim3(256), 0, st, x, units, codes, bscale, tscale, (int)P);
+  const bool unit = unit_tensor(x, rows, cols, ldx);
+  const UnitRows ur = (unit && !contig) ? unit_rows(cols, ldx) : UnitRows();
+  if (unit && reinterpret_cast<uintptr_t>(codes) % 8 == 0) {
+    // two launches, the maxima handed over in every code region
+    const SlotsPlan plan = slots_plan(n, fmt == 1 ? 8 : 4);
+    if (plan.G >= 1) {
+      if (contig) {
+        if (fmt == 1) launch_slots<1, true>(x, n / 8, ur, codes, bscale, tscale, plan, st);
+        else launch_slots<2, true>(x, n / 8, ur, codes, bscale, tscale, plan, st);
+      } else {
+        if (fmt == 1) launch_slots<1, false>(x, n / 8, ur, codes, bscale, tscale, plan, st);
+        else launch_slots<2, false>(x, n / 8, ur, codes, bscale, tscale, plan, st);
+      }
       return hipGetLastError();
     }
   }
   // amax: per-workgroup partial maxima are parked in the code buffer, which
   // the quantize kernel overwrites afterwards (stream order separates them).
+  // More than kSmallUnits units: the codes hold kAmaxGroups partials.
   {
-    const int64_t r_eff = contig ? 1 : rows;
-    const int64_t c_eff = contig ? rows * cols : cols;
-    const bool vec = aligned && (c_eff % 8 == 0) && (contig || ldx % 8 == 0);
-    const int64_t per_row = vec ? c_eff / 8 : c_eff;
-    const int64_t code_bytes = (fmt == 1) ? rows * cols : rows * cols / 2;
     const uintptr_t base = (reinterpret_cast<uintptr_t>(codes) + 3) & ~uintptr_t(3);
-    const int64_t cap = (code_bytes - (int64_t)(base - reinterpret_cast<uintptr_t>(codes))) / 4;
-    int64_t gx, gy;
     uint32_t* partial = reinterpret_cast<uint32_t*>(base);
-    const int64_t dense_groups = std::min<int64_t>((c_eff / 8 + 1023) / 1024, kAmaxGroups);
-    if (contig && vec && dense_groups <= cap) {
-      gx = dense_groups;
-      gy = 1;
-      hipLaunchKernelGGL(k_amax_dense, dim3((unsigned)gx), dim3(256), 0, st, x, c_eff / 8, partial);
+    int64_t gx, gy = 1;
+    if (unit && n % 8 == 0) {
+      gx = std::min<int64_t>((n / 8 + 1023) / 1024, kAmaxGroups);
+      if (contig) hipLaunchKernelGGL(k_amax_units<true>, dim3((unsigned)gx), dim3(256), 0, st, x, n / 8, ur, partial);
+      else hipLaunchKernelGGL(k_amax_units<false>, dim3((unsigned)gx), dim3(256), 0, st, x, n / 8, ur, partial);
     } else {
+      const int64_t r_eff = contig ? 1 : rows, c_eff = contig ? n : cols;
       gy = std::min<int64_t>(r_eff, 1024);
-      gx = std::min<int64_t>(std::max<int64_t>(1, (per_row + 1023) / 1024), std::max<int64_t>(1, 1024 / gy));
-      if (gx * gy > cap) {  // tiny tensor: one workgroup, its max goes straight to the scale slot
+      gx = std::min<int64_t>(std::max<int64_t>(1, (c_eff + 1023) / 1024), std::max<int64_t>(1, 1024 / gy));
+      const int64_t cap = ((fmt == 1 ? n : n / 2) - (int64_t)(base - reinterpret_cast<uintptr_t>(codes))) / 4;
+      if (gx * gy > cap) {  // short rows in many units: one workgroup, its max goes straight to the scale slot
         gx = gy = 1;
         partial = reinterpret_cast<uint32_t*>(tscale);
       }
-      if (vec)
-        hipLaunchKernelGGL(k_amax_partial<true>, dim3((unsigned)gx, (unsigned)gy), dim3(256), 0, st, x, r_eff, c_eff,
-                           contig ? c_eff : ldx, partial);
-      else
-        hipLaunchKernelGGL(k_amax_partial<false>, dim3((unsigned)gx, (unsigned)gy), dim3(256), 0, st, x, r_eff, c_eff,
-                           contig ? c_eff : ldx, partial);
+      hipLaunchKernelGGL(k_amax_partial, dim3((unsigned)gx, (unsigned)gy), dim3(256), 0, st, x, r_eff, c_eff,
+                         contig ? c_eff : ldx, partial);
     }
     hipLaunchKernelGGL(k_finalize, dim3(1), dim3(256), 0, st, partial, (int)(gx * gy), tscale,
                        fmt == 1 ? 448.0f : 2688.0f);
   }
-  return launch_quantize_static(fmt, x, rows, cols, ldx, codes, bscale, tscale, st);
+  return launch_elements(fmt, x, rows, cols, ldx, codes, bscale, tscale, true, st);
 }
 
 hipError_t launch_dequant(int fmt, const uint8_t* codes, const uint8_t* bscale, const float* tscale,
