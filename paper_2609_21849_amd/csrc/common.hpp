@@ -38,6 +38,12 @@ __host__ __device__ inline uint32_t f32_to_bf16(float f) {
   return ((u & 0x7FFFFFFFu) > 0x7F800000u) ? 0x7FC0u : r;
 }
 
+// Two fp32 values (not NaN where the bits matter) to a pair of bf16 (low half
+// = a), round to nearest even (one v_cvt_pk_bf16_f32).
+__device__ __attribute__((always_inline)) inline uint32_t pk_bf16(float a, float b) {
+  return __builtin_bit_cast(uint32_t, __builtin_convertvector((v2f){a, b}, v2bf));
+}
+
 // E4M3 code of fp32 y: nearest of the 127 finite magnitudes, ties to the
 // even code, |y| >= 448 saturates to 448 (0x7E), NaN -> 0x7F, sign kept.
 //   normal range [2^-6, 448): round the 23-bit mantissa to 3 bits (RNE on

@@ -81,14 +81,6 @@ __device__ __attribute__((always_inline)) inline float out_rscale(const GemmArgs
   return (s > 0.0f) ? __fdiv_rn(1.0f, s) : 0.0f;
 }
 
-// Two fp32 values to a pair of bf16 (low half = a), round to nearest even
-// (one v_cvt_pk_bf16_f32).
-__device__ __attribute__((always_inline)) inline uint32_t pk_bf16(float a, float b) {
-  typedef float v2f_t __attribute__((ext_vector_type(2)));
-  typedef __bf16 v2bf_t __attribute__((ext_vector_type(2)));
-  return __builtin_bit_cast(uint32_t, __builtin_convertvector((v2f_t){a, b}, v2bf_t));
-}
-
 // Four consecutive outputs y[m][n .. n+3] (n % 4 == 0) in the output format:
 // bf16 (RNE), fp32, or E4M3 codes of fl(y * r) (round to nearest even,
 // saturating: the element step of the static quantizer, on the fp32 value).

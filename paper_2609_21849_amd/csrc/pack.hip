@@ -29,153 +29,136 @@
 // Chunks of one panel follow each other along k, so a panel is one
 // contiguous stream. The header keeps format, n, k and the tensor scale
 // (1.0 for the MX formats, which have none).
+#include <algorithm>
+
 #include "common.hpp"
 #include "kernels.hpp"
 
 namespace qg {
 
-__global__ void k_pack_header(uint8_t* packed, int fmt, int64_t n, int64_t k, const float* tscale) {
-  uint32_t* h = reinterpret_cast<uint32_t*>(packed);
-  h[0] = kPackMagic;
-  h[1] = kPackVersion;
-  h[2] = (uint32_t)fmt;
-  h[3] = 0u;
-  reinterpret_cast<int64_t*>(packed)[2] = n;
-  reinterpret_cast<int64_t*>(packed)[3] = k;
-  reinterpret_cast<float*>(packed + kPackScaleOffset)[0] = tscale ? *tscale : 1.0f;
+// One launch packs (or unpacks) codes, block scales and header. Memory-bound:
+// 2 x the weight's bytes. A workgroup's 256 threads are 8 neighbouring pieces of
+// each of the panel's 32 rows, so a wave reads whole 128-byte runs of 8 rows and
+// writes 128-byte runs of the packed images (8 rows of one piece), and the panel
+// and column come from the grid, with no division. Against a thread per packed
+// piece (a wave reading 16 bytes of each of 64 places, two 64-bit divisions) in
+// three launches, NVFP4 9216 x 3072: 11.5 us of kernels -> 7.6, unpack
+// 12.1 -> 7.8 us.
+
+// Byte offset inside a panel's packed codes of the 16-byte piece at byte o of
+// its row r (see the layout above).
+template <int FMT>
+__device__ inline int64_t packed_piece(int64_t o, int r) {
+  const int h16 = (int)(o >> 4) & 1, h32 = (int)(o >> 5) & 1, h64 = (int)(o >> 6) & 1;
+  if (FMT == 1) return (o >> 7) * 4096 + h64 * 2048 + h16 * 1024 + (32 * h32 + r) * 16;
+  if (FMT == 4) return (o >> 7) * 4096 + h64 * 2048 + h32 * 1024 + (32 * h16 + r) * 16;
+  if (FMT == 2) return (o >> 6) * 2048 + h16 * 1024 + (32 * h32 + r) * 16;
+  return (o >> 5) * 1024 + (32 * h16 + r) * 16;
 }
 
-__global__ void k_unpack_header(const uint8_t* packed, float* tscale) {
-  if (tscale) *tscale = reinterpret_cast<const float*>(packed + kPackScaleOffset)[0];
-}
+constexpr int kPackSegs = 2;  // 128-byte column segments per workgroup, loaded together
 
-// Canonical [n, row_bytes] byte offset of the 16-byte piece that packed
-// piece `p` holds, or -1 for a padding row (see the layout above).
-__device__ inline int64_t canon_piece(int fmt, int64_t p, int64_t n, int64_t k) {
-  if (fmt == 3) {
-    const int64_t steps = k / 64;
-    const int64_t sc = p >> 6, l = p & 63;
-    const int64_t panel = sc / steps, t = sc - panel * steps;
-    const int64_t row = panel * 32 + (l & 31);
-    if (row >= n) return -1;
-    return row * (k / 2) + t * 32 + 16 * (l >> 5);
+template <int FMT, bool PACK>
+__global__ void __launch_bounds__(256) k_pack(uint8_t* canon, uint8_t* bscale, float* tscale, int64_t n, int64_t k,
+                                              int64_t panels, int64_t code_blocks, uint8_t* packed) {
+  constexpr bool MX = FMT == 3 || FMT == 4;
+  if (blockIdx.x == 0 && blockIdx.y == 0 && threadIdx.x == 0) {
+    float* scale = reinterpret_cast<float*>(packed + kPackScaleOffset);
+    if (PACK) {
+      uint32_t* h = reinterpret_cast<uint32_t*>(packed);
+      h[0] = kPackMagic;
+      h[1] = kPackVersion;
+      h[2] = (uint32_t)FMT;
+      h[3] = 0u;
+      reinterpret_cast<int64_t*>(packed)[2] = n;
+      reinterpret_cast<int64_t*>(packed)[3] = k;
+      *scale = tscale ? *tscale : 1.0f;
+    } else if (tscale) {
+      *tscale = *scale;
+    }
   }
-  const int64_t kc_n = k / 128;
-  const int per = (fmt == 1 || fmt == 4) ? 256 : 128;  // pieces per chunk
-  const int64_t chunk = p / per, s = p - chunk * per;
-  const int64_t panel = chunk / kc_n, kc = chunk - panel * kc_n;
-  const int64_t h = s >> 6, l = s & 63;
-  const int64_t row = panel * 32 + (l & 31);
-  if (row >= n) return -1;
-  if (fmt == 1) return row * k + kc * 128 + 64 * (h >> 1) + 32 * (l >> 5) + 16 * (h & 1);
-  if (fmt == 4) return row * k + kc * 128 + 64 * (h >> 1) + 32 * (h & 1) + 16 * (l >> 5);
-  return row * (k / 2) + kc * 64 + 32 * (l >> 5) + 16 * h;
-}
-
-// Canonical [n, k/16] offset of the 8-byte scale run that packed run `p`
-// holds (run = one row of one chunk), or -1 for a padding row.
-__device__ inline int64_t canon_scale_run(int64_t p, int64_t n, int64_t k) {
-  const int64_t kc_n = k / 128;
-  const int64_t chunk = p >> 5, r = p & 31;
-  const int64_t panel = chunk / kc_n, kc = chunk - panel * kc_n;
-  const int64_t row = panel * 32 + r;
-  if (row >= n) return -1;
-  return row * (k / 16) + kc * 8;
-}
-
-template <bool PACK>
-__global__ void __launch_bounds__(256) k_pack_codes(int fmt, uint8_t* canon, uint8_t* packed_codes,
-                                                    int64_t npieces, int64_t n, int64_t k) {
-  const int64_t p = (int64_t)blockIdx.x * 256 + threadIdx.x;
-  if (p >= npieces) return;
-  const int64_t c = canon_piece(fmt, p, n, k);
-  if (PACK)
-    reinterpret_cast<uint4*>(packed_codes)[p] =
-        (c < 0) ? make_uint4(0u, 0u, 0u, 0u) : *reinterpret_cast<const uint4*>(canon + c);
-  else if (c >= 0)
-    *reinterpret_cast<uint4*>(canon + c) = reinterpret_cast<const uint4*>(packed_codes)[p];
-}
-
-template <bool PACK>
-__global__ void __launch_bounds__(256) k_pack_scales(uint8_t* canon, uint8_t* packed_scales,
-                                                     int64_t nruns, int64_t n, int64_t k) {
-  const int64_t p = (int64_t)blockIdx.x * 256 + threadIdx.x;
-  if (p >= nruns) return;
-  const int64_t c = canon_scale_run(p, n, k);
-  if (PACK)
-    reinterpret_cast<uint2*>(packed_scales)[p] =
-        (c < 0) ? make_uint2(0u, 0u) : *reinterpret_cast<const uint2*>(canon + c);
-  else if (c >= 0)
-    *reinterpret_cast<uint2*>(canon + c) = reinterpret_cast<const uint2*>(packed_scales)[p];
-}
-
-// MXFP4 scale runs: run p = (panel, 256-wide chunk c, lane l); byte s of
-// the run is the E8M0 scale of block 8c + 2s + g of row panel * 32 + r.
-template <bool PACK>
-__global__ void __launch_bounds__(256) k_pack_mx_scales(uint8_t* canon, uint8_t* packed_scales,
-                                                        int64_t nruns, int64_t n, int64_t k) {
-  const int64_t p = (int64_t)blockIdx.x * 256 + threadIdx.x;
-  if (p >= nruns) return;
-  const int64_t cn = k / 256;
-  const int64_t pc = p >> 6, l = p & 63;
-  const int64_t panel = pc / cn, c = pc - panel * cn;
-  const int64_t row = panel * 32 + (l & 31), g = l >> 5;
-  uint8_t* run = packed_scales + 4 * p;
-  if (PACK) {
-    uint32_t w = 0;
-    if (row < n)
-      for (int s = 0; s < 4; ++s) w |= (uint32_t)canon[row * (k / 32) + 8 * c + 2 * s + g] << (8 * s);
-    *reinterpret_cast<uint32_t*>(run) = w;
-  } else if (row < n) {
-    const uint32_t w = *reinterpret_cast<const uint32_t*>(run);
-    for (int s = 0; s < 4; ++s) canon[row * (k / 32) + 8 * c + 2 * s + g] = (uint8_t)(w >> (8 * s));
+  const int64_t rb = (FMT == 1 || FMT == 4) ? k : k / 2;  // code bytes of a row, a multiple of 64
+  uint8_t* codes = packed + kPackHeader;
+  const int r = threadIdx.x >> 3, j = threadIdx.x & 7;
+  for (int64_t panel = blockIdx.y; panel < panels; panel += gridDim.y) {
+    const int64_t row = panel * 32 + r;
+    const bool live = row < n;
+    if ((int64_t)blockIdx.x < code_blocks) {
+      uint8_t* c = canon + row * rb;
+      uint8_t* p = codes + panel * 32 * rb;
+      uint4 v[kPackSegs];
+#pragma unroll
+      for (int s = 0; s < kPackSegs; ++s) {
+        const int64_t o = ((int64_t)blockIdx.x * kPackSegs + s) * 128 + 16 * j;
+        v[s] = make_uint4(0u, 0u, 0u, 0u);
+        if (o < rb && (live || !PACK))
+          v[s] = *reinterpret_cast<const uint4*>(PACK ? c + o : p + packed_piece<FMT>(o, r));
+      }
+#pragma unroll
+      for (int s = 0; s < kPackSegs; ++s) {
+        const int64_t o = ((int64_t)blockIdx.x * kPackSegs + s) * 128 + 16 * j;
+        if (o < rb && (live || PACK)) *reinterpret_cast<uint4*>(PACK ? p + packed_piece<FMT>(o, r) : c + o) = v[s];
+      }
+    } else if (FMT == 2) {  // 8-byte scale run of row r in 128-wide chunk kc
+      const int64_t kc = ((int64_t)blockIdx.x - code_blocks) * 8 + j, kcn = k / 128;
+      if (kc >= kcn) continue;
+      uint2* c = reinterpret_cast<uint2*>(bscale + row * (k / 16)) + kc;
+      uint2* p = reinterpret_cast<uint2*>(codes + panels * 32 * rb) + (panel * kcn + kc) * 32 + r;
+      if (PACK) *p = live ? *c : make_uint2(0u, 0u);
+      else if (live) *c = *p;
+    } else if (MX) {  // the 8 scale bytes of row r in 256-wide chunk kc: blocks 2 s + g to byte s of lane 32 g + r
+      const int64_t kc = ((int64_t)blockIdx.x - code_blocks) * 8 + j, kcn = k / 256;
+      if (kc >= kcn) continue;
+      uint8_t* c = bscale + row * (k / 32) + 8 * kc;
+      uint32_t* p = reinterpret_cast<uint32_t*>(codes + panels * 32 * rb) + (panel * kcn + kc) * 64 + r;
+      if (PACK) {
+        uint32_t w[2] = {0u, 0u};
+        if (live)
+          for (int s = 0; s < 4; ++s) {
+            w[0] |= (uint32_t)c[2 * s] << (8 * s);
+            w[1] |= (uint32_t)c[2 * s + 1] << (8 * s);
+          }
+        p[0] = w[0];
+        p[32] = w[1];
+      } else if (live) {
+        const uint32_t w[2] = {p[0], p[32]};
+        for (int s = 0; s < 4; ++s) {
+          c[2 * s] = (uint8_t)(w[0] >> (8 * s));
+          c[2 * s + 1] = (uint8_t)(w[1] >> (8 * s));
+        }
+      }
+    }
   }
 }
 
-static inline unsigned blocks_for(int64_t t) { return (unsigned)((t + 255) / 256); }
+template <bool PACK>
+static hipError_t launch(int fmt, uint8_t* codes, uint8_t* bscale, float* tscale, int64_t n, int64_t k,
+                         uint8_t* packed, hipStream_t st) {
+  const bool empty = packed_codes_bytes(fmt, n, k) == 0;  // the header alone
+  const int64_t panels = empty ? 0 : padded_rows(n) / 32;
+  const int64_t rb = (fmt == 1 || fmt == 4) ? k : k / 2;
+  const int64_t code_blocks = empty ? 0 : (rb + 128 * kPackSegs - 1) / (128 * kPackSegs);
+  const int64_t chunks = (fmt == 2) ? k / 128 : (fmt == 1 || empty) ? 0 : k / 256;  // 8 a workgroup
+  const dim3 grid((unsigned)std::max<int64_t>(1, code_blocks + (chunks + 7) / 8),
+                  (unsigned)std::max<int64_t>(1, std::min<int64_t>(panels, 65535)));
+  switch (fmt) {
+    case 1: hipLaunchKernelGGL((k_pack<1, PACK>), grid, dim3(256), 0, st, codes, bscale, tscale, n, k, panels, code_blocks, packed); break;
+    case 2: hipLaunchKernelGGL((k_pack<2, PACK>), grid, dim3(256), 0, st, codes, bscale, tscale, n, k, panels, code_blocks, packed); break;
+    case 3: hipLaunchKernelGGL((k_pack<3, PACK>), grid, dim3(256), 0, st, codes, bscale, tscale, n, k, panels, code_blocks, packed); break;
+    default: hipLaunchKernelGGL((k_pack<4, PACK>), grid, dim3(256), 0, st, codes, bscale, tscale, n, k, panels, code_blocks, packed); break;
+  }
+  return hipGetLastError();
+}
 
 hipError_t launch_pack(int fmt, const uint8_t* codes, const uint8_t* bscale, const float* tscale,
                        int64_t n, int64_t k, uint8_t* packed, hipStream_t st) {
-  hipLaunchKernelGGL(k_pack_header, dim3(1), dim3(1), 0, st, packed, fmt, n, k, tscale);
-  const int64_t cb = packed_codes_bytes(fmt, n, k);
-  if (cb == 0) return hipGetLastError();
-  uint8_t* pc = packed + kPackHeader;
-  const int64_t npieces = cb / 16;
-  hipLaunchKernelGGL(k_pack_codes<true>, dim3(blocks_for(npieces)), dim3(256), 0, st, fmt,
-                     const_cast<uint8_t*>(codes), pc, npieces, n, k);
-  if (fmt == 3 || fmt == 4) {
-    const int64_t nruns = padded_rows(n) * k / 128;
-    hipLaunchKernelGGL(k_pack_mx_scales<true>, dim3(blocks_for(nruns)), dim3(256), 0, st,
-                       const_cast<uint8_t*>(bscale), pc + cb, nruns, n, k);
-  }
-  if (fmt == 2) {
-    const int64_t nruns = padded_rows(n) * k / 128;
-    hipLaunchKernelGGL(k_pack_scales<true>, dim3(blocks_for(nruns)), dim3(256), 0, st,
-                       const_cast<uint8_t*>(bscale), pc + cb, nruns, n, k);
-  }
-  return hipGetLastError();
+  return launch<true>(fmt, const_cast<uint8_t*>(codes), const_cast<uint8_t*>(bscale), const_cast<float*>(tscale), n, k,
+                      packed, st);
 }
 
 hipError_t launch_unpack(int fmt, const uint8_t* packed, int64_t n, int64_t k, uint8_t* codes,
                          uint8_t* bscale, float* tscale, hipStream_t st) {
-  hipLaunchKernelGGL(k_unpack_header, dim3(1), dim3(1), 0, st, packed, tscale);
-  const int64_t cb = packed_codes_bytes(fmt, n, k);
-  if (cb == 0) return hipGetLastError();
-  uint8_t* pc = const_cast<uint8_t*>(packed) + kPackHeader;
-  const int64_t npieces = cb / 16;
-  hipLaunchKernelGGL(k_pack_codes<false>, dim3(blocks_for(npieces)), dim3(256), 0, st, fmt, codes,
-                     pc, npieces, n, k);
-  if (fmt == 3 || fmt == 4) {
-    const int64_t nruns = padded_rows(n) * k / 128;
-    hipLaunchKernelGGL(k_pack_mx_scales<false>, dim3(blocks_for(nruns)), dim3(256), 0, st, bscale,
-                       pc + cb, nruns, n, k);
-  }
-  if (fmt == 2) {
-    const int64_t nruns = padded_rows(n) * k / 128;
-    hipLaunchKernelGGL(k_pack_scales<false>, dim3(blocks_for(nruns)), dim3(256), 0, st, bscale,
-                       pc + cb, nruns, n, k);
-  }
-  return hipGetLastError();
+  return launch<false>(fmt, codes, bscale, tscale, n, k, const_cast<uint8_t*>(packed), st);
 }
 
 }  // namespace qg
