@@ -44,6 +44,7 @@
 
 #include "common.hpp"
 #include "kernels.hpp"
+#include "tile_plan.hpp"
 
 namespace qg {
 
@@ -217,9 +218,7 @@ __device__ inline v4i dequant8_bf16(uint32_t w, float sc) {
 // a contiguous band of tiles, walked in groups of GROUP_M tile rows so that
 // concurrently running tiles share activation rows and weight panels.
 __device__ inline void tile_coords(int id, int tiles_m, int tiles_n, int& bm, int& bn) {
-  const int total = tiles_m * tiles_n;
-  int t = id;
-  if (total % 8 == 0) t = (id & 7) * (total >> 3) + (id >> 3);
+  const int t = xcd_tile(id, tiles_m * tiles_n);
   constexpr int GROUP_M = 4;
   const int per_group = GROUP_M * tiles_n;
   const int grp = t / per_group;
@@ -501,7 +500,7 @@ __global__ void __launch_bounds__(64 * NW) k_gemm_splitk(GemmArgs g) {
   const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int r = lane & 31, gq = lane >> 5;
   const int tiles = g.tiles_m * g.tiles_n;
-  const int t = (tiles % 8 == 0) ? (int)(blockIdx.x & 7) * (tiles >> 3) + (int)(blockIdx.x >> 3) : (int)blockIdx.x;
+  const int t = xcd_tile((int)blockIdx.x, tiles);
   const int bn = t / g.tiles_m, bm = t - bn * g.tiles_m;
   const int m0 = bm * BM, n0 = bn * BN;
   const int kcn = g.k >> 7;
@@ -1057,19 +1056,22 @@ __device__ __attribute__((always_inline)) inline void store_tiles_epi(const Gemm
 
 // The epilogue instance of an output.
 inline int epilogue_of(const GemmArgs& g) { return out_staged(g) ? g.out_mode : EPI_DIRECT; }
-#define QG_LAUNCH_EPI_NO_NVFP4(KERNEL, grid, st, g)                                                    \
-  do {                                                                                                 \
-    switch (epilogue_of(g)) {                                                                          \
-      case OUT_BF16: hipLaunchKernelGGL(KERNEL<OUT_BF16>, grid, dim3(256), 0, st, g); break;           \
-      case OUT_F32: hipLaunchKernelGGL(KERNEL<OUT_F32>, grid, dim3(256), 0, st, g); break;             \
-      case OUT_FP8: hipLaunchKernelGGL(KERNEL<OUT_FP8>, grid, dim3(256), 0, st, g); break;             \
-      default: hipLaunchKernelGGL(KERNEL<EPI_DIRECT>, grid, dim3(256), 0, st, g);                      \
-    }                                                                                                  \
+// (trailing arguments: the kernel's template arguments after the epilogue)
+#define QG_LAUNCH_EPI_NO_NVFP4(KERNEL, grid, st, g, ...)                                                          \
+  do {                                                                                                            \
+    switch (epilogue_of(g)) {                                                                                     \
+      case OUT_BF16: hipLaunchKernelGGL((KERNEL<OUT_BF16 __VA_OPT__(, ) __VA_ARGS__>), grid, dim3(256), 0, st, g); break; \
+      case OUT_F32: hipLaunchKernelGGL((KERNEL<OUT_F32 __VA_OPT__(, ) __VA_ARGS__>), grid, dim3(256), 0, st, g); break;   \
+      case OUT_FP8: hipLaunchKernelGGL((KERNEL<OUT_FP8 __VA_OPT__(, ) __VA_ARGS__>), grid, dim3(256), 0, st, g); break;   \
+      default: hipLaunchKernelGGL((KERNEL<EPI_DIRECT __VA_OPT__(, ) __VA_ARGS__>), grid, dim3(256), 0, st, g);            \
+    }                                                                                                             \
   } while (0)
-#define QG_LAUNCH_EPI(KERNEL, grid, st, g)                                                             \
-  do {                                                                                                 \
-    if (epilogue_of(g) == OUT_NVFP4) hipLaunchKernelGGL(KERNEL<OUT_NVFP4>, grid, dim3(256), 0, st, g); \
-    else QG_LAUNCH_EPI_NO_NVFP4(KERNEL, grid, st, g);                                                  \
+#define QG_LAUNCH_EPI(KERNEL, grid, st, g, ...)                                                                   \
+  do {                                                                                                            \
+    if (epilogue_of(g) == OUT_NVFP4)                                                                              \
+      hipLaunchKernelGGL((KERNEL<OUT_NVFP4 __VA_OPT__(, ) __VA_ARGS__>), grid, dim3(256), 0, st, g);              \
+    else                                                                                                          \
+      QG_LAUNCH_EPI_NO_NVFP4(KERNEL, grid, st, g __VA_OPT__(, ) __VA_ARGS__);                                     \
   } while (0)
 
 // Activation staging shared by the 256 x 256 FP8 kernels: 256 rows x one
@@ -1086,8 +1088,10 @@ inline int epilogue_of(const GemmArgs& g) { return out_staged(g) ? g.out_mode : 
 // from register half h of both lane halves, so there piece c belongs to
 // step s = c / 4, register half h = (c / 2) % 2 and lane half g = c % 2; the
 // slot XOR is the same function of (s, g, h), so read_a_frag serves both.
-struct AStage256 {
-  static constexpr int RA = 8;  // pieces per thread per chunk
+// RA: row panels of the tile = pieces per thread and chunk (8: 256 rows).
+template <int RA_>
+struct AStage {
+  static constexpr int RA = RA_;
   uint32_t oa[RA], la[RA];
   template <bool MX8 = false>
   __device__ __attribute__((always_inline)) inline void init(const GemmArgs& g, int m0, int tid) {
@@ -1102,6 +1106,8 @@ struct AStage256 {
     }
   }
 };
+
+using AStage256 = AStage<8>;
 
 // Operand fragment of activation panel `panel`, step s (0/1) of a staged chunk.
 __device__ __attribute__((always_inline)) inline v8i read_a_frag(const uint8_t* st, int panel, int s, int lane) {
@@ -1588,12 +1594,14 @@ __global__ void __launch_bounds__(256) k_gemm_fp8_t288(GemmArgs g) {
 //                 [half 0: steps 0, 1][half 1: steps 0, 1], one 16-bit read per
 //                 lane and panel.
 // K must be a multiple of 256 (whole chunk pairs, no odd first chunk); no
-// tensor scales.
-template <int EPI>
+// tensor scales. TM (4, 3, 2): tiles of 64 TM rows (plan_tile_rows).
+template <int EPI, int TM>
 __global__ void __launch_bounds__(256) k_gemm_mxfp8_direct(GemmArgs g) {
-  constexpr int A_CODES = 8 * 4096;
+  constexpr int A_CODES = 2 * TM * 4096;
   constexpr int A_STAGE = A_CODES + 256 * 4;
-  constexpr int RA = AStage256::RA;
+  constexpr int RA = AStage<2 * TM>::RA;
+  constexpr int PG = (RA + TM - 2) / (TM - 1);  // pieces staged per MFMA group of step 1
+  constexpr int VB = (16 + 4 * TM - 1) / (4 * TM);  // weight loads per MFMA of step 0
   constexpr uint32_t OOB = 0x80000000u;
   constexpr int OUT_STAGE = 32 * (64 * 4 + 16);
   __shared__ __attribute__((aligned(16))) uint8_t smem[2 * A_STAGE];
@@ -1615,16 +1623,16 @@ __global__ void __launch_bounds__(256) k_gemm_mxfp8_direct(GemmArgs g) {
   const __amdgpu_buffer_rsrc_t rs_bs = __builtin_amdgcn_make_buffer_rsrc(
       const_cast<uint8_t*>(g.w_scales), 0, (int)((int64_t)npanels_w * (kcn >> 1) * 256), 0x00020000);
 
-  AStage256 A;
+  AStage<RA> A;
   uint32_t ob[4], osb[4], osa;
   v4i ga[RA];
   uint32_t gs;         // staged activation scales of the thread's row (4 blocks of a chunk)
   v8i fb[2][2][4];     // [chunk parity][step][weight panel]
   uint32_t bsc[4];     // weight scales of the current chunk pair [panel]: byte 2 (kc % 2) + s
   uint32_t bsn[4];     // ... of the next pair
-  uint32_t asc[4];     // activation scales of the current chunk [panel]: byte s (low half)
+  uint32_t asc[TM];    // activation scales of the current chunk [panel]: byte s (low half)
   v8i fa[2];
-  v16f acc[4][4];
+  v16f acc[TM][4];
 
   // Chunk offsets are uniform: they travel in the loads' scalar offset,
   // clamped to the last chunk (prefetches past the end re-read it in bounds;
@@ -1648,8 +1656,8 @@ __global__ void __launch_bounds__(256) k_gemm_mxfp8_direct(GemmArgs g) {
   };
   auto read_asc = [&](const uint8_t* st) __attribute__((always_inline)) {
 #pragma unroll
-    for (int i = 0; i < 4; ++i)
-      asc[i] = *reinterpret_cast<const uint16_t*>(st + A_CODES + ((wm * 4 + i) * 32 + r) * 4 + 2 * gq);
+    for (int i = 0; i < TM; ++i)
+      asc[i] = *reinterpret_cast<const uint16_t*>(st + A_CODES + ((wm * TM + i) * 32 + r) * 4 + 2 * gq);
   };
   auto load_b = [&](auto Pc, int kc) __attribute__((always_inline)) {
     constexpr int P = decltype(Pc)::value;
@@ -1668,61 +1676,61 @@ __global__ void __launch_bounds__(256) k_gemm_mxfp8_direct(GemmArgs g) {
 #pragma unroll
     for (int j = 0; j < 4; ++j) bsn[j] = __builtin_amdgcn_raw_buffer_load_b32(rs_bs, osb[j], (kcl(kc) >> 1) * 256, 0);
   };
-  // MFMA group f = (step f / 4, activation panel f % 4); chunk parity P
+  // MFMA group f = (step f / TM, activation panel f % TM); chunk parity P
   auto mgroup = [&](auto Pc, auto Fc) __attribute__((always_inline)) {
     constexpr int P = decltype(Pc)::value, f = decltype(Fc)::value;
 #pragma unroll
     for (int j = 0; j < 4; ++j)
-      acc[f & 3][j] = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(fb[P][f >> 2][j], fa[f & 1], acc[f & 3][j], 0, 0,
-                                                                       2 * P + (f >> 2), (int)bsc[j], f >> 2,
-                                                                       (int)asc[f & 3]);
+      acc[f % TM][j] = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(fb[P][f / TM][j], fa[f & 1], acc[f % TM][j], 0, 0,
+                                                                        2 * P + f / TM, (int)bsc[j], f / TM,
+                                                                        (int)asc[f % TM]);
   };
   auto chunk = [&](auto Pc, int kc) __attribute__((always_inline)) {
     constexpr int P = decltype(Pc)::value;
     const uint8_t* cur = smem + P * A_STAGE;
     uint8_t* nxt = smem + (P ^ 1) * A_STAGE;
     // step 0: weight loads of chunk kc + 1 (and, in the first chunk of a
-    // pair, the scale dwords of the next pair), activation fragments 1..4
+    // pair, the scale dwords of the next pair), activation fragments 1..TM
     load_b(std::integral_constant<int, P ^ 1>(), kc + 1);
     if (P == 0) load_bs(kc + 2);
     [&]<int... F>(std::integer_sequence<int, F...>) {
-      ((fa[(F + 1) & 1] = read_a_frag(cur, wm * 4 + ((F + 1) & 3), (F + 1) >> 2, lane),
+      ((fa[(F + 1) & 1] = read_a_frag(cur, wm * TM + (F + 1) % TM, (F + 1) / TM, lane),
         mgroup(Pc, std::integral_constant<int, F>())), ...);
-    }(std::make_integer_sequence<int, 4>());
+    }(std::make_integer_sequence<int, TM>());
 #pragma unroll
-    for (int f = 0; f < 4; ++f) {
+    for (int f = 0; f < TM; ++f) {
       __builtin_amdgcn_sched_group_barrier(0x100, 2, 0);  // DS read: next fragment
 #pragma unroll
       for (int t = 0; t < 4; ++t) {
         __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);  // MFMA
-        __builtin_amdgcn_sched_group_barrier(0x020, 1, 0);  // VMEM read (weights)
+        __builtin_amdgcn_sched_group_barrier(0x020, VB, 0);  // VMEM read (weights)
       }
     }
     __builtin_amdgcn_sched_barrier(0);
-    // step 1, groups 4..6: stage activations of chunk kc + 1, load kc + 2
+    // step 1 but its last group: stage activations of chunk kc + 1, load kc + 2
     const int a_so = kcl(kc + 2);
     [&]<int... F>(std::integer_sequence<int, F...>) {
-      ((fa[(F + 5) & 1] = read_a_frag(cur, wm * 4 + ((F + 5) & 3), (F + 5) >> 2, lane),
+      ((fa[(F + TM + 1) & 1] = read_a_frag(cur, wm * TM + F + 1, 1, lane),
         [&] {
 #pragma unroll
-          for (int it = 3 * F; it < 3 * F + 3 && it < RA; ++it) *reinterpret_cast<v4i*>(nxt + A.la[it]) = ga[it];
-          if (F == 2) write_a_scales(nxt);
+          for (int it = PG * F; it < PG * F + PG && it < RA; ++it) *reinterpret_cast<v4i*>(nxt + A.la[it]) = ga[it];
+          if (F == TM - 2) write_a_scales(nxt);
         }(),
-        mgroup(Pc, std::integral_constant<int, F + 4>()),
+        mgroup(Pc, std::integral_constant<int, F + TM>()),
         [&] {
 #pragma unroll
-          for (int it = 3 * F; it < 3 * F + 3 && it < RA; ++it)
+          for (int it = PG * F; it < PG * F + PG && it < RA; ++it)
             ga[it] = __builtin_amdgcn_raw_buffer_load_b128(rs_a, A.oa[it], a_so * 128, 0);
-          if (F == 2) gs = __builtin_amdgcn_raw_buffer_load_b32(rs_as, osa, a_so * 4, 0);
+          if (F == TM - 2) gs = __builtin_amdgcn_raw_buffer_load_b32(rs_as, osa, a_so * 4, 0);
         }()), ...);
-    }(std::make_integer_sequence<int, 3>());
+    }(std::make_integer_sequence<int, TM - 1>());
 #pragma unroll
-    for (int f = 4; f < 7; ++f) {
+    for (int f = 0; f < TM - 1; ++f) {
       __builtin_amdgcn_sched_group_barrier(0x100, 2, 0);  // DS read: next fragment
 #pragma unroll
       for (int t = 0; t < 4; ++t) {
         __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);  // MFMA
-        if (t < 3 && 3 * (f - 4) + t < RA) {
+        if (t < PG && PG * f + t < RA) {
           __builtin_amdgcn_sched_group_barrier(0x200, 1, 0);  // DS write
           __builtin_amdgcn_sched_group_barrier(0x020, 1, 0);  // VMEM read (activations)
         }
@@ -1731,9 +1739,9 @@ __global__ void __launch_bounds__(256) k_gemm_mxfp8_direct(GemmArgs g) {
     __builtin_amdgcn_sched_barrier(0);
     __syncthreads();
     __builtin_amdgcn_sched_barrier(0);
-    // group 7 covers the reads of the next chunk's first fragment and scales
-    fa[0] = read_a_frag(nxt, wm * 4, 0, lane);
-    mgroup(Pc, std::integral_constant<int, 7>());
+    // the last group covers the reads of the next chunk's first fragment and scales
+    fa[0] = read_a_frag(nxt, wm * TM, 0, lane);
+    mgroup(Pc, std::integral_constant<int, 2 * TM - 1>());
     read_asc(nxt);
     if (P == 1) {
 #pragma unroll
@@ -1749,8 +1757,8 @@ __global__ void __launch_bounds__(256) k_gemm_mxfp8_direct(GemmArgs g) {
     gq = lane >> 5;
     int bm, bn;
     tile_coords(tile, g.tiles_m, g.tiles_n, bm, bn);
-    const int m0 = bm * 256, n0 = bn * 256;
-    A.init<true>(g, m0, tid);
+    const int m0 = bm * (64 * TM), n0 = bn * 256;
+    A.template init<true>(g, m0, tid);
     {
       const uint32_t row = (uint32_t)(m0 + tid);
       osa = (row < (uint32_t)g.m) ? row * ks : OOB;
@@ -1763,7 +1771,7 @@ __global__ void __launch_bounds__(256) k_gemm_mxfp8_direct(GemmArgs g) {
       osb[j] = in ? panel * (uint32_t)((kcn >> 1) * 256) + 4u * lane : OOB;
     }
 #pragma unroll
-    for (int i = 0; i < 4; ++i)
+    for (int i = 0; i < TM; ++i)
 #pragma unroll
       for (int j = 0; j < 4; ++j)
 #pragma unroll
@@ -1775,7 +1783,7 @@ __global__ void __launch_bounds__(256) k_gemm_mxfp8_direct(GemmArgs g) {
     __syncthreads();
     load_a(1);
     load_b(std::integral_constant<int, 0>(), 0);
-    fa[0] = read_a_frag(smem, wm * 4, 0, lane);
+    fa[0] = read_a_frag(smem, wm * TM, 0, lane);
     read_asc(smem);
 #pragma unroll
     for (int j = 0; j < 4; ++j) bsc[j] = bsn[j];
@@ -1783,7 +1791,7 @@ __global__ void __launch_bounds__(256) k_gemm_mxfp8_direct(GemmArgs g) {
       chunk(std::integral_constant<int, 0>(), kc);
       chunk(std::integral_constant<int, 1>(), kc + 1);
     }
-    store_tiles_epi<EPI, 4, 4>(g, acc, sout + wave * OUT_STAGE, m0 + wm * 128, n0 + wn * 128, lane, 1.0f);
+    store_tiles_epi<EPI, TM, 4>(g, acc, sout + wave * OUT_STAGE, m0 + wm * (32 * TM), n0 + wn * 128, lane, 1.0f);
   }
 }
 
@@ -1805,10 +1813,11 @@ __global__ void __launch_bounds__(256) k_gemm_mxfp8_direct(GemmArgs g) {
 // issued at steps 4 and 5); step 6 reads the next chunk's first activation
 // code half and scales, a whole step before step 7 expands them (read one
 // MFMA before their use, their latency stalled the wave). Persistent grid and
-// staged epilogue as in k_gemm_fp8_direct.
-template <int EPI>
+// staged epilogue as in k_gemm_fp8_direct. TM (4, 3, 2): tiles of 64 TM rows,
+// waves of 32 TM x 128 (plan_tile_rows).
+template <int EPI, int TM>
 __global__ void __launch_bounds__(256) k_gemm_nvfp4_direct(GemmArgs g) {
-  constexpr int A_CODES = 8 * 2048;              // 256 rows x 64 B of codes
+  constexpr int A_CODES = 2 * TM * 2048;         // 64 TM rows x 64 B of codes
   constexpr int A_STAGE = A_CODES + 256 * 16;    // + 256 rows x 8 fp16 scales
   constexpr int OUT_STAGE = 32 * (64 * 4 + 16);
   constexpr uint32_t OOB = 0x80000000u;
@@ -1835,16 +1844,16 @@ __global__ void __launch_bounds__(256) k_gemm_nvfp4_direct(GemmArgs g) {
   const __amdgpu_buffer_rsrc_t rs_bs = __builtin_amdgcn_make_buffer_rsrc(
       const_cast<uint8_t*>(g.w_scales), 0, (int)((int64_t)npanels_w * kcn * 256), 0x00020000);
 
-  uint32_t oa[4], la[4], osa, ob[4], osb[4];
-  v4i ga[4];        // staged activation codes of a chunk
+  uint32_t oa[TM], la[TM], osa, ob[4], osb[4];
+  v4i ga[TM];       // staged activation codes of a chunk
   v2i gs;           // staged activation scales (one row per thread)
   v4i bc[2][4][2];  // weight codes [chunk parity][panel][half]
   uint32_t bs[2][4];  // weight E4M3 scales [chunk parity][panel]
   uint2 bf[4];      // weight fp16 scales of the current chunk
-  v4i ac[2][4];     // activation codes [half][panel] of the current chunk
-  uint2 af[4];      // activation fp16 scales of the current chunk
-  v8h fa[2][4], fb[2][4];  // expanded fragments, two steps
-  v16f acc[4][4];
+  v4i ac[2][TM];    // activation codes [half][panel] of the current chunk
+  uint2 af[TM];     // activation fp16 scales of the current chunk
+  v8h fa[2][TM], fb[2][4];  // expanded fragments, two steps
+  v16f acc[TM][4];
 
   // Chunk offsets are uniform: they travel in the loads' scalar offset,
   // clamped to the last chunk (prefetches past the end re-read it in bounds;
@@ -1853,12 +1862,12 @@ __global__ void __launch_bounds__(256) k_gemm_nvfp4_direct(GemmArgs g) {
   auto kcl = [&](int kc) __attribute__((always_inline)) { return kc < kcn ? kc : kcn - 1; };
   auto load_a = [&](int kc) __attribute__((always_inline)) {
 #pragma unroll
-    for (int it = 0; it < 4; ++it) ga[it] = __builtin_amdgcn_raw_buffer_load_b128(rs_a, oa[it], kcl(kc) * 64, 0);
+    for (int it = 0; it < TM; ++it) ga[it] = __builtin_amdgcn_raw_buffer_load_b128(rs_a, oa[it], kcl(kc) * 64, 0);
     gs = __builtin_amdgcn_raw_buffer_load_b64(rs_as, osa, kcl(kc) * 8, 0);
   };
   auto write_a_codes = [&](uint8_t* st, int from, int to) __attribute__((always_inline)) {
 #pragma unroll
-    for (int it = 0; it < 4; ++it)
+    for (int it = 0; it < TM; ++it)
       if (it >= from && it < to) *reinterpret_cast<v4i*>(st + la[it]) = ga[it];
   };
   auto write_a_scales = [&](uint8_t* st) __attribute__((always_inline)) {
@@ -1877,12 +1886,12 @@ __global__ void __launch_bounds__(256) k_gemm_nvfp4_direct(GemmArgs g) {
   };
   auto read_a_half = [&](const uint8_t* st, int h) __attribute__((always_inline)) {
 #pragma unroll
-    for (int i = 0; i < 4; ++i)
-      ac[h][i] = *reinterpret_cast<const v4i*>(st + (wm * 4 + i) * 2048 + h * 1024 + ((lane ^ (4 * h + 10 * gq)) * 16));
+    for (int i = 0; i < TM; ++i)
+      ac[h][i] = *reinterpret_cast<const v4i*>(st + (wm * TM + i) * 2048 + h * 1024 + ((lane ^ (4 * h + 10 * gq)) * 16));
   };
   auto read_a_scales = [&](const uint8_t* st) __attribute__((always_inline)) {
 #pragma unroll
-    for (int i = 0; i < 4; ++i) af[i] = *reinterpret_cast<const uint2*>(st + A_CODES + ((wm * 4 + i) * 32 + r) * 16 + 8 * gq);
+    for (int i = 0; i < TM; ++i) af[i] = *reinterpret_cast<const uint2*>(st + A_CODES + ((wm * TM + i) * 32 + r) * 16 + 8 * gq);
   };
   auto convert_b_scales = [&](auto Pc) __attribute__((always_inline)) {
     constexpr int P = decltype(Pc)::value;
@@ -1893,7 +1902,7 @@ __global__ void __launch_bounds__(256) k_gemm_nvfp4_direct(GemmArgs g) {
   auto expand = [&](auto Pc, int s, int D) __attribute__((always_inline)) {
     constexpr int P = decltype(Pc)::value;
 #pragma unroll
-    for (int i = 0; i < 4; ++i) {
+    for (int i = 0; i < TM; ++i) {
       const v4i c = ac[s >> 2][i];
       const uint32_t w = (uint32_t)((s & 3) == 0 ? c.x : (s & 3) == 1 ? c.y : (s & 3) == 2 ? c.z : c.w);
       fa[D][i] = dequant8_f16(w, scale_f16(af[i], s >> 1));
@@ -1907,24 +1916,25 @@ __global__ void __launch_bounds__(256) k_gemm_nvfp4_direct(GemmArgs g) {
   };
   auto mfmas = [&](int D) __attribute__((always_inline)) {
 #pragma unroll
-    for (int i = 0; i < 4; ++i)
+    for (int i = 0; i < TM; ++i)
 #pragma unroll
       for (int j = 0; j < 4; ++j)
         acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_f16(fb[D][j], fa[D][i], acc[i][j], 0, 0, 0);
   };
-  // 16 MFMAs, each followed by its share of the expansion (64 VALU + scale
-  // work); LDS reads in the groups whose bit is set in rmask
+  // 4 TM MFMAs, each followed by its share of the expansion (8 (TM + 4) VALU +
+  // scale work) and of the loads; LDS reads in the groups whose bit is set in rmask
   auto interleave = [&](int nvmem, unsigned rmask, int nds_w) __attribute__((always_inline)) {
 #pragma unroll
-    for (int t = 0; t < 16; ++t) {
+    for (int t = 0; t < 4 * TM; ++t) {
       __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);  // MFMA
-      __builtin_amdgcn_sched_group_barrier(0x002, 5, 0);  // VALU
-      if (t < nvmem) __builtin_amdgcn_sched_group_barrier(0x020, 1, 0);
+      __builtin_amdgcn_sched_group_barrier(0x002, TM == 4 ? 5 : TM == 3 ? 6 : 7, 0);  // VALU
+      if (t < nvmem) __builtin_amdgcn_sched_group_barrier(0x020, TM == 2 ? 2 : 1, 0);
       if ((rmask >> t) & 1) __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);
       if (t < nds_w) __builtin_amdgcn_sched_group_barrier(0x200, 1, 0);
     }
   };
 
+  constexpr unsigned RM = (1u << TM) - 1;  // TM LDS reads, one per group
   auto chunk = [&](auto Pc, int kc) __attribute__((always_inline)) {
     constexpr int P = decltype(Pc)::value;
     const uint8_t* cur = smem + P * A_STAGE;
@@ -1938,18 +1948,18 @@ __global__ void __launch_bounds__(256) k_gemm_nvfp4_direct(GemmArgs g) {
       if (s == 2) read_a_half(cur, 1);
       mfmas(s & 1);
       expand(Pc, s + 1, (s + 1) & 1);
-      interleave(s == 0 ? 12 : 0, s == 2 ? 0xFu : 0u, 0);
+      interleave(s == 0 ? 12 : 0, s == 2 ? RM : 0u, 0);
       __builtin_amdgcn_sched_barrier(0);
     }
     // steps 4, 5: stage the activations of chunk kc + 1, then load kc + 2
 #pragma unroll
     for (int s = 4; s < 6; ++s) {
-      if (s == 4) write_a_codes(nxt, 0, 2);
-      else { write_a_codes(nxt, 2, 4); write_a_scales(nxt); }
+      if (s == 4) write_a_codes(nxt, 0, TM / 2);
+      else { write_a_codes(nxt, TM / 2, TM); write_a_scales(nxt); }
       if (s == 5) load_a(kc + 2);
       mfmas(s & 1);
       expand(Pc, s + 1, (s + 1) & 1);
-      interleave(s == 5 ? 5 : 0, 0u, s == 4 ? 2 : 3);
+      interleave(s == 5 ? TM + 1 : 0, 0u, s == 4 ? TM / 2 : TM - TM / 2 + 1);
       __builtin_amdgcn_sched_barrier(0);
     }
     // the barrier that publishes chunk kc + 1 (its last writes were issued at
@@ -1964,7 +1974,7 @@ __global__ void __launch_bounds__(256) k_gemm_nvfp4_direct(GemmArgs g) {
     mfmas(0);
     expand(Pc, 7, 1);
     read_a_scales(nxt);
-    interleave(0, 0x0F0Fu, 0);
+    interleave(0, RM | (RM << (2 * TM)), 0);
     __builtin_amdgcn_sched_barrier(0);
     // step 7: the next chunk's step-0 expansion
     convert_b_scales(Q);
@@ -1981,9 +1991,9 @@ __global__ void __launch_bounds__(256) k_gemm_nvfp4_direct(GemmArgs g) {
     gq = lane >> 5;
     int bm, bn;
     tile_coords(tile, g.tiles_m, g.tiles_n, bm, bn);
-    const int m0 = bm * 256, n0 = bn * 256;
+    const int m0 = bm * (64 * TM), n0 = bn * 256;
 #pragma unroll
-    for (int it = 0; it < 4; ++it) {
+    for (int it = 0; it < TM; ++it) {
       const int q = it * 256 + tid;
       const int p = q >> 7, rr = (q >> 2) & 31, c = q & 3;
       const uint32_t row = (uint32_t)(m0 + 32 * p + rr);
@@ -2004,7 +2014,7 @@ __global__ void __launch_bounds__(256) k_gemm_nvfp4_direct(GemmArgs g) {
       osb[j] = in ? panel * (uint32_t)(kcn * 256) + 8u * r + 4u * gq : OOB;
     }
 #pragma unroll
-    for (int i = 0; i < 4; ++i)
+    for (int i = 0; i < TM; ++i)
 #pragma unroll
       for (int j = 0; j < 4; ++j)
 #pragma unroll
@@ -2015,7 +2025,7 @@ __global__ void __launch_bounds__(256) k_gemm_nvfp4_direct(GemmArgs g) {
     if (kcn & 1) {
       load_a(0);
       load_b(std::integral_constant<int, 0>(), 0);
-      write_a_codes(smem, 0, 4);
+      write_a_codes(smem, 0, TM);
       write_a_scales(smem);
       __syncthreads();
       read_a_half(smem, 0);
@@ -2033,7 +2043,7 @@ __global__ void __launch_bounds__(256) k_gemm_nvfp4_direct(GemmArgs g) {
     if (kc < kcn) {
       load_a(kc);
       load_b(std::integral_constant<int, 0>(), kc);
-      write_a_codes(smem, 0, 4);
+      write_a_codes(smem, 0, TM);
       write_a_scales(smem);
       __syncthreads();
       load_a(kc + 1);
@@ -2046,7 +2056,7 @@ __global__ void __launch_bounds__(256) k_gemm_nvfp4_direct(GemmArgs g) {
         chunk(std::integral_constant<int, 1>(), kc + 1);
       }
     }
-    store_tiles_epi<EPI, 4, 4>(g, acc, sout + wave * OUT_STAGE, m0 + wm * 128, n0 + wn * 128, lane, scale);
+    store_tiles_epi<EPI, TM, 4>(g, acc, sout + wave * OUT_STAGE, m0 + wm * (32 * TM), n0 + wn * 128, lane, scale);
   }
 }
 
@@ -2074,10 +2084,11 @@ __global__ void __launch_bounds__(256) k_gemm_nvfp4_direct(GemmArgs g) {
 //                 dword; the MFMA's byte select picks step s's scale. A group
 //                 of 4 fp4 MFMAs lasts about one LDS read latency, so the
 //                 fragments are read two groups ahead.
-// K must be a multiple of 256 (checked by the caller).
-template <int EPI>
+// K must be a multiple of 256 (checked by the caller). TM (4, 3, 2): tiles of
+// 64 TM rows, waves of 32 TM x 128 (plan_tile_rows).
+template <int EPI, int TM>
 __global__ void __launch_bounds__(256) k_gemm_mxfp4_direct(GemmArgs g) {
-  constexpr int A_CODES = 8 * 4096;              // 8 panels x 4 steps x 1 KiB
+  constexpr int A_CODES = 2 * TM * 4096;         // 2 TM panels x 4 steps x 1 KiB
   constexpr int A_STAGE = A_CODES + 256 * 8;     // + 8 scale bytes per row
   constexpr int OUT_STAGE = 32 * (64 * 4 + 16);
   constexpr uint32_t OOB = 0x80000000u;
@@ -2102,14 +2113,14 @@ __global__ void __launch_bounds__(256) k_gemm_mxfp4_direct(GemmArgs g) {
   const __amdgpu_buffer_rsrc_t rs_bs = __builtin_amdgcn_make_buffer_rsrc(
       const_cast<uint8_t*>(g.w_scales), 0, (int)((int64_t)npanels_w * kcn * 256), 0x00020000);
 
-  uint32_t oa[8], la[8], osa, ob[4], osb[4];
-  v4i ga[8];           // staged activation codes of a chunk
+  uint32_t oa[2 * TM], la[2 * TM], osa, ob[4], osb[4];
+  v4i ga[2 * TM];         // staged activation codes of a chunk
   uint2 gs;            // staged activation scales of the thread's row
   v4i fb[4][4];        // weight codes, ring over steps: [step % 4][panel]
   uint32_t bsc[2][4];  // weight scales [chunk parity][panel]: byte s = step s
-  uint32_t asc[2][4];  // activation scales [chunk parity][panel]: byte s = step s
+  uint32_t asc[2][TM];  // activation scales [chunk parity][panel]: byte s = step s
   v4i fa[4];           // activation fragments, ring over MFMA groups (read two groups ahead)
-  v16f acc[4][4];
+  v16f acc[TM][4];
 
   // Chunk and step offsets are uniform: they travel in the loads' scalar
   // offset, clamped to the last chunk / step (prefetches past the end re-read
@@ -2118,7 +2129,7 @@ __global__ void __launch_bounds__(256) k_gemm_mxfp4_direct(GemmArgs g) {
   auto kcl = [&](int kc) __attribute__((always_inline)) { return kc < kcn ? kc : kcn - 1; };
   auto load_a = [&](int kc) __attribute__((always_inline)) {
 #pragma unroll
-    for (int it = 0; it < 8; ++it) ga[it] = __builtin_amdgcn_raw_buffer_load_b128(rs_a, oa[it], kcl(kc) * 128, 0);
+    for (int it = 0; it < 2 * TM; ++it) ga[it] = __builtin_amdgcn_raw_buffer_load_b128(rs_a, oa[it], kcl(kc) * 128, 0);
     const v2i t = __builtin_amdgcn_raw_buffer_load_b64(rs_as, osa, kcl(kc) * 8, 0);
     gs = make_uint2((uint32_t)t.x, (uint32_t)t.y);
   };
@@ -2141,31 +2152,32 @@ __global__ void __launch_bounds__(256) k_gemm_mxfp4_direct(GemmArgs g) {
     for (int j = 0; j < 4; ++j) bsc[P][j] = __builtin_amdgcn_raw_buffer_load_b32(rs_bs, osb[j], kcl(kc) * 256, 0);
   };
   auto read_fa = [&](const uint8_t* st, int s, int i) __attribute__((always_inline)) {
-    return *reinterpret_cast<const v4i*>(st + (wm * 4 + i) * 4096 + s * 1024 + ((lane ^ (2 * s + 9 * gq)) * 16));
+    return *reinterpret_cast<const v4i*>(st + (wm * TM + i) * 4096 + s * 1024 + ((lane ^ (2 * s + 9 * gq)) * 16));
   };
   auto read_asc = [&](auto Pc, const uint8_t* st) __attribute__((always_inline)) {
     constexpr int P = decltype(Pc)::value;
 #pragma unroll
-    for (int i = 0; i < 4; ++i)
-      asc[P][i] = *reinterpret_cast<const uint32_t*>(st + A_CODES + ((wm * 4 + i) * 32 + r) * 8 + 4 * gq);
+    for (int i = 0; i < TM; ++i)
+      asc[P][i] = *reinterpret_cast<const uint32_t*>(st + A_CODES + ((wm * TM + i) * 32 + r) * 8 + 4 * gq);
   };
-  // MFMA group f = (step f / 4, activation panel f % 4) on fragment fa[f % 4]
+  // MFMA group f = (step f / TM, activation panel f % TM) on fragment fa[f % 4]
   auto mgroup = [&](auto Pc, auto Fc) __attribute__((always_inline)) {
     constexpr int P = decltype(Pc)::value, f = decltype(Fc)::value;
     const v4i xa = fa[f & 3];
     const v8i xv = (v8i){xa.x, xa.y, xa.z, xa.w, 0, 0, 0, 0};
 #pragma unroll
     for (int j = 0; j < 4; ++j) {
-      const v4i wa = fb[f >> 2][j];
+      const v4i wa = fb[f / TM][j];
       const v8i wv = (v8i){wa.x, wa.y, wa.z, wa.w, 0, 0, 0, 0};
-      acc[f & 3][j] = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(wv, xv, acc[f & 3][j], 4, 4, f >> 2, (int)bsc[P][j],
-                                                                       f >> 2, (int)asc[P][f & 3]);
+      acc[f % TM][j] = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(wv, xv, acc[f % TM][j], 4, 4, f / TM, (int)bsc[P][j],
+                                                                        f / TM, (int)asc[P][f % TM]);
     }
   };
-  // one region: groups 4s .. 4s + NG - 1, each a fragment read for the next
-  // group and 4 MFMAs; NV global loads and NW LDS writes spread over the slots
+  // one region of NG groups, each a fragment read for a later group and 4
+  // MFMAs; NV global loads (VS a slot) and NW LDS writes spread over the slots
   auto pattern = [&](auto NGc, auto NVc, auto NWc) __attribute__((always_inline)) {
     constexpr int NG = decltype(NGc)::value, NV = decltype(NVc)::value, NW = decltype(NWc)::value;
+    constexpr int VS = (NV + 4 * NG - 1) / (4 * NG);
 #pragma unroll
     for (int f = 0; f < NG; ++f) {
       __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);  // DS read
@@ -2173,47 +2185,53 @@ __global__ void __launch_bounds__(256) k_gemm_mxfp4_direct(GemmArgs g) {
       for (int t = 0; t < 4; ++t) {
         __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);  // MFMA
         if (4 * f + t < NW) __builtin_amdgcn_sched_group_barrier(0x200, 1, 0);  // DS write
-        if (4 * f + t < NV) __builtin_amdgcn_sched_group_barrier(0x020, 1, 0);  // VMEM
+        if (VS * (4 * f + t) < NV) __builtin_amdgcn_sched_group_barrier(0x020, VS, 0);  // VMEM
       }
     }
     __builtin_amdgcn_sched_barrier(0);
   };
   // fragment reads run two groups ahead of their MFMAs: group f reads the
-  // fragment of group f + 2 (for f = 14, 15: groups 0, 1 of the next chunk,
+  // fragment of group f + 2 (the last two: groups 0, 1 of the next chunk,
   // after the barrier that publishes it)
   auto chunk = [&](auto Pc, int kc) __attribute__((always_inline)) {
     constexpr int P = decltype(Pc)::value;
     using I = std::integral_constant<int, 0>;
+    using G = std::integral_constant<int, TM>;
     const uint8_t* cur = smem + P * A_STAGE;
     uint8_t* nxt = smem + (P ^ 1) * A_STAGE;
     const int t0 = 4 * kc;
+    auto group = [&](auto Fc) __attribute__((always_inline)) {
+      constexpr int F = decltype(Fc)::value;
+      fa[(F + 2) & 3] = read_fa(cur, (F + 2) / TM, (F + 2) % TM);
+      mgroup(Pc, Fc);
+    };
     // step 0: refill slot 3 (step 3 of this chunk)
     load_b(std::integral_constant<int, 3>(), t0 + 3);
     [&]<int... F>(std::integer_sequence<int, F...>) {
-      ((fa[(F + 2) & 3] = read_fa(cur, (F + 2) >> 2, (F + 2) & 3), mgroup(Pc, std::integral_constant<int, F>())), ...);
-    }(std::make_integer_sequence<int, 4>());
-    pattern(std::integral_constant<int, 4>(), std::integral_constant<int, 4>(), I());
+      (group(std::integral_constant<int, F>()), ...);
+    }(std::make_integer_sequence<int, TM>());
+    pattern(G(), std::integral_constant<int, 4>(), I());
     // step 1: slot 0 <- step 0 of the next chunk; next chunk's weight scales
     load_b(std::integral_constant<int, 0>(), t0 + 4);
     load_bs(std::integral_constant<int, P ^ 1>(), kc + 1);
     [&]<int... F>(std::integer_sequence<int, F...>) {
-      ((fa[(F + 6) & 3] = read_fa(cur, (F + 6) >> 2, (F + 6) & 3), mgroup(Pc, std::integral_constant<int, F + 4>())), ...);
-    }(std::make_integer_sequence<int, 4>());
-    pattern(std::integral_constant<int, 4>(), std::integral_constant<int, 8>(), I());
+      (group(std::integral_constant<int, F + TM>()), ...);
+    }(std::make_integer_sequence<int, TM>());
+    pattern(G(), std::integral_constant<int, 8>(), I());
     // step 2: slot 1 refill; stage the activations of chunk kc + 1 (written
     // between the fragment reads in program order), then load those of kc + 2
     const int a_so = kcl(kc + 2) * 128;
     load_b(std::integral_constant<int, 1>(), t0 + 5);
     [&]<int... F>(std::integer_sequence<int, F...>) {
-      ((fa[(F + 10) & 3] = read_fa(cur, (F + 10) >> 2, (F + 10) & 3),
+      ((fa[(F + 2 * TM + 2) & 3] = read_fa(cur, (F + 2 * TM + 2) / TM, (F + 2 * TM + 2) % TM),
         *reinterpret_cast<v4i*>(nxt + la[2 * F]) = ga[2 * F],
         *reinterpret_cast<v4i*>(nxt + la[2 * F + 1]) = ga[2 * F + 1],
-        mgroup(Pc, std::integral_constant<int, F + 8>()),
+        mgroup(Pc, std::integral_constant<int, F + 2 * TM>()),
         ga[2 * F] = __builtin_amdgcn_raw_buffer_load_b128(rs_a, oa[2 * F], a_so, 0),
         ga[2 * F + 1] = __builtin_amdgcn_raw_buffer_load_b128(rs_a, oa[2 * F + 1], a_so, 0)), ...);
-    }(std::make_integer_sequence<int, 4>());
-    pattern(std::integral_constant<int, 4>(), std::integral_constant<int, 12>(), std::integral_constant<int, 8>());
-    // step 3, first half: slot 2 refill, the row scales of chunk kc + 1
+    }(std::make_integer_sequence<int, TM>());
+    pattern(G(), std::integral_constant<int, 4 + 2 * TM>(), std::integral_constant<int, 2 * TM>());
+    // step 3 but its last two groups: slot 2 refill, the row scales of chunk kc + 1
     load_b(std::integral_constant<int, 2>(), t0 + 6);
     write_a_scales(nxt);
     {
@@ -2221,17 +2239,17 @@ __global__ void __launch_bounds__(256) k_gemm_mxfp4_direct(GemmArgs g) {
       gs = make_uint2((uint32_t)t.x, (uint32_t)t.y);
     }
     [&]<int... F>(std::integer_sequence<int, F...>) {
-      ((fa[(F + 14) & 3] = read_fa(cur, 3, (F + 2) & 3), mgroup(Pc, std::integral_constant<int, F + 12>())), ...);
-    }(std::make_integer_sequence<int, 2>());
-    pattern(std::integral_constant<int, 2>(), std::integral_constant<int, 5>(), std::integral_constant<int, 1>());
+      (group(std::integral_constant<int, F + 3 * TM>()), ...);
+    }(std::make_integer_sequence<int, TM - 2>());
+    if constexpr (TM > 2) pattern(std::integral_constant<int, TM - 2>(), std::integral_constant<int, 5>(), std::integral_constant<int, 1>());
     __syncthreads();
     __builtin_amdgcn_sched_barrier(0);
-    // step 3, second half: the next chunk's first two fragments and its scales
+    // step 3, last two groups: the next chunk's first two fragments and its scales
     fa[0] = read_fa(nxt, 0, 0);
-    mgroup(Pc, std::integral_constant<int, 14>());
+    mgroup(Pc, std::integral_constant<int, 4 * TM - 2>());
     fa[1] = read_fa(nxt, 0, 1);
     read_asc(std::integral_constant<int, P ^ 1>(), nxt);
-    mgroup(Pc, std::integral_constant<int, 15>());
+    mgroup(Pc, std::integral_constant<int, 4 * TM - 1>());
     __builtin_amdgcn_sched_barrier(0);
   };
 
@@ -2242,9 +2260,9 @@ __global__ void __launch_bounds__(256) k_gemm_mxfp4_direct(GemmArgs g) {
     gq = lane >> 5;
     int bm, bn;
     tile_coords(tile, g.tiles_m, g.tiles_n, bm, bn);
-    const int m0 = bm * 256, n0 = bn * 256;
+    const int m0 = bm * (64 * TM), n0 = bn * 256;
 #pragma unroll
-    for (int it = 0; it < 8; ++it) {
+    for (int it = 0; it < 2 * TM; ++it) {
       const int q = it * 256 + tid;
       const int p = q >> 8, rr = (q >> 3) & 31, c = q & 7;
       const uint32_t row = (uint32_t)(m0 + 32 * p + rr);
@@ -2263,7 +2281,7 @@ __global__ void __launch_bounds__(256) k_gemm_mxfp4_direct(GemmArgs g) {
       osb[j] = in ? panel * (uint32_t)(kcn * 256) + 4u * lane : OOB;
     }
 #pragma unroll
-    for (int i = 0; i < 4; ++i)
+    for (int i = 0; i < TM; ++i)
 #pragma unroll
       for (int j = 0; j < 4; ++j)
 #pragma unroll
@@ -2278,20 +2296,20 @@ __global__ void __launch_bounds__(256) k_gemm_mxfp4_direct(GemmArgs g) {
       load_b(std::integral_constant<int, 3>(), 3);
       load_bs(std::integral_constant<int, 0>(), 0);
 #pragma unroll
-      for (int it = 0; it < 8; ++it) *reinterpret_cast<v4i*>(smem + la[it]) = ga[it];
+      for (int it = 0; it < 2 * TM; ++it) *reinterpret_cast<v4i*>(smem + la[it]) = ga[it];
       write_a_scales(smem);
       __syncthreads();
       read_asc(std::integral_constant<int, 0>(), smem);
       [&]<int... F>(std::integer_sequence<int, F...>) {
-        ((fa[F & 3] = read_fa(smem, F >> 2, F & 3), mgroup(std::integral_constant<int, 0>(), std::integral_constant<int, F>())), ...);
-      }(std::make_integer_sequence<int, 16>());
+        ((fa[F & 3] = read_fa(smem, F / TM, F % TM), mgroup(std::integral_constant<int, 0>(), std::integral_constant<int, F>())), ...);
+      }(std::make_integer_sequence<int, 4 * TM>());
       __syncthreads();
       kc = 1;
     }
     if (kc < kcn) {
       load_a(kc);
 #pragma unroll
-      for (int it = 0; it < 8; ++it) *reinterpret_cast<v4i*>(smem + la[it]) = ga[it];
+      for (int it = 0; it < 2 * TM; ++it) *reinterpret_cast<v4i*>(smem + la[it]) = ga[it];
       write_a_scales(smem);
       __syncthreads();
       load_a(kc + 1);
@@ -2308,7 +2326,7 @@ __global__ void __launch_bounds__(256) k_gemm_mxfp4_direct(GemmArgs g) {
       }
     }
     // no tensor scales in MX: the block scales are applied inside the MFMAs
-    store_tiles_epi<EPI, 4, 4>(g, acc, sout + wave * OUT_STAGE, m0 + wm * 128, n0 + wn * 128, lane, 1.0f);
+    store_tiles_epi<EPI, TM, 4>(g, acc, sout + wave * OUT_STAGE, m0 + wm * (32 * TM), n0 + wn * 128, lane, 1.0f);
   }
 }
 
@@ -2992,6 +3010,36 @@ static int device_cus() {
   return n;
 }
 
+template <int MODE, int TM>
+static void launch_large_tm(GemmArgs g, int64_t cus, hipStream_t st) {
+  g.tiles_m = (g.m + 64 * TM - 1) / (64 * TM);
+  g.tiles_n = (g.n + 255) / 256;
+  const dim3 grid((unsigned)std::min<int64_t>((int64_t)g.tiles_m * g.tiles_n, cus));
+  if constexpr (MODE == MODE_MXFP4) QG_LAUNCH_EPI(k_gemm_mxfp4_direct, grid, st, g, TM);
+  else if constexpr (MODE == MODE_MXFP8) QG_LAUNCH_EPI(k_gemm_mxfp8_direct, grid, st, g, TM);
+  else QG_LAUNCH_EPI(k_gemm_nvfp4_direct, grid, st, g, TM);
+}
+
+// Persistent grids of 256-column tiles, their height by plan_tile_rows; every
+// output is the same sum in the same order whatever that is. Measured (back to
+// back calls, 256-row tiles -> chosen): MXFP8 500 x 9216 x 3072 30.4 -> 25.0 us (128
+// rows), 2304 x 9216 x 3072 68.0 -> 60.6 (192), 2300 x 3072 x 9216 81.8 -> 70.7 (128);
+// MXFP4 21.6 -> 15.1, 47.3 -> 40.2, 51.9 -> 42.6; NVFP4 3000 x 3072 x 3072 59.7 -> 50.6
+// (192), 2304 x 9216 x 3072 129 -> 106 (192). 256 rows stay at 4608 x 3072 and 4608 x
+// 9216 (K = 3072), where 192 take MXFP8 38 -> 57 and 108 -> 122 us, NVFP4 70 -> 100 and
+// 208 -> 216. Cutting the rows into a 256-row head of whole rounds and a shorter
+// tail in a second launch gained 1-2% or lost.
+template <int MODE>
+static hipError_t launch_large(const GemmArgs& g, int64_t cus, hipStream_t st) {
+  constexpr RoundCost cost = MODE == MODE_NVFP4 ? RoundCost{83, 56} : MODE == MODE_MXFP8 ? RoundCost{92, 70} : RoundCost{86, 62};
+  switch (plan_tile_rows(g.m, (g.n + 255) / 256, cus, cost)) {
+    case 4: launch_large_tm<MODE, 4>(g, cus, st); break;
+    case 3: launch_large_tm<MODE, 3>(g, cus, st); break;
+    default: launch_large_tm<MODE, 2>(g, cus, st);
+  }
+  return hipGetLastError();
+}
+
 // MXFP4 / MXFP8. Up to two rounds of 64 x 96 tiles on the CUs the split-K
 // kernel, above that 256 x 256 tiles: those walk K serially (about 25-40 us at
 // K = 3072 however few there are), while a split-K tile's waves share K and
@@ -3012,13 +3060,7 @@ static hipError_t launch_mx(GemmArgs g, hipStream_t st) {
   const int64_t t6496 = rows64 * ((g.n + 95) / 96);
   if (t6496 > cus && rows64 * ((g.n + 127) / 128) <= cus) return run_splitk<MODE, 2, 4, 8, 1>(g, st);
   if (t6496 <= 2 * cus) return run_splitk<MODE, 2, 3, 4, 2>(g, st);
-  // persistent grids of 256 x 256 tiles, four waves of 128 x 128 each
-  g.tiles_m = (g.m + 255) / 256;
-  g.tiles_n = (g.n + 255) / 256;
-  const dim3 grid((unsigned)std::min<int64_t>((int64_t)g.tiles_m * g.tiles_n, cus));
-  if (MODE == MODE_MXFP4) QG_LAUNCH_EPI(k_gemm_mxfp4_direct, grid, st, g);
-  else QG_LAUNCH_EPI(k_gemm_mxfp8_direct, grid, st, g);
-  return hipGetLastError();
+  return launch_large<MODE>(g, cus, st);
 }
 
 hipError_t launch_gemm(int a_fmt, const void* a, const uint8_t* a_bscale, const float* a_tscale,
@@ -3107,9 +3149,11 @@ hipError_t launch_gemm(int a_fmt, const void* a, const uint8_t* a_bscale, const 
     g.tiles_m = (g.m + 255) / 256;
     g.tiles_n = (g.n + 255) / 256;
     const int tiles = g.tiles_m * g.tiles_n;
-    // Below half a round of 256 x 256 tiles the split-K kernel is faster
-    // (measured up to M = 2300 at N = K = 3072: 0.9x the time there, 0.3x at
-    // M = 512; 68.8 against 75.4 us at 1555 x 4512 x 3968, 126 tiles). The
+    // Below half a round of 256 x 256 tiles and 11/16 of a round of 128 x 256
+    // ones the split-K kernel is faster (back to back, split-K against 128-row
+    // tiles: 500 x 9216 x 3072, 144 tiles, 35.7 / 37.2 us; 1280 x 4096 x 4096, 160, 46.9 /
+    // 48.3; 640 x 9216 x 3072, 180, 42.6 / 38.4; 1900 x 3072 x 1024, 180, 21.3 / 16.8; 1024 x
+    // 6144 x 3072, 192, 44.3 / 40.1; 2300 x 3072 x 9216, 216, 164 / 113). The
     // narrowest tile that gives every workgroup a CU of its own; past that 64 x
     // 64 tiles of four waves, two workgroups per CU, so that one's reduction
     // runs beside the other's loop. Measured (GPU time from graph replays,
@@ -3118,7 +3162,8 @@ hipError_t launch_gemm(int a_fmt, const void* a, const uint8_t* a_bscale, const 
     // 3072 x 3072 8.0 -> 5.8, 300 x 1024 x 3072 8.1 -> 6.9, 151 x 3520 x 5504 21.6 ->
     // 14.8, 2048 x 1024 x 3072 25.0 -> 20.3, 1555 x 4512 x 3968 80 -> 69; 512 x 3072 x
     // 3072 (64 x 96, one round) as before.
-    if (m <= 128 || 2 * tiles < cus) {
+    const int64_t tiles128 = (m + 127) / 128 * g.tiles_n;
+    if (m <= 128 || (2 * tiles < cus && 16 * tiles128 < 11 * cus)) {
       const int64_t rows32 = (m + 31) / 32, rows64 = (m + 63) / 64;
       if (rows32 * ((n + 31) / 32) <= cus) {
         if ((k >> 7) >= 32) return run_splitk<MODE_NVFP4, 1, 1, 8, 1>(g, st);  // 44 x 352 x 7296 8.8 -> 8.2 us
@@ -3132,8 +3177,7 @@ hipError_t launch_gemm(int a_fmt, const void* a, const uint8_t* a_bscale, const 
       if (rows64 * ((n + 95) / 96) <= cus) return run_splitk<MODE_NVFP4, 2, 3, 8, 1>(g, st);
       return run_splitk<MODE_NVFP4, 2, 2, 4, 2>(g, st);
     }
-    QG_LAUNCH_EPI(k_gemm_nvfp4_direct, dim3(std::min(tiles, cus)), st, g);
-    return hipGetLastError();
+    return launch_large<MODE_NVFP4>(g, cus, st);
   } else {
     const int64_t npan_all = (n + 31) / 32;
     const int64_t xbytes = (m + 1) * (k * 2 + 16);

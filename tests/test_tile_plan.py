@@ -1,0 +1,23 @@
+"""Host-only check of the GEMMs' tile order and tile height (csrc/tile_plan.hpp)
+over many sizes. No GPU."""
+import os
+import shutil
+import subprocess
+
+import pytest
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+
+
+def test_tile_order_and_height(tmp_path):
+    hipcc = shutil.which("hipcc") or "/opt/rocm/bin/hipcc"
+    if not os.path.exists(hipcc):
+        pytest.skip("hipcc not available")
+    exe = str(tmp_path / "tile_plan_check")
+    subprocess.run([hipcc, "-x", "hip", "--offload-host-only", "-O2", "-std=c++20",
+                    "-I" + os.path.join(ROOT, "paper_2609_21849_amd", "csrc"),
+                    os.path.join(ROOT, "tests", "native", "tile_plan_check.cpp"), "-o", exe],
+                   check=True, capture_output=True)
+    r = subprocess.run([exe], capture_output=True, text=True, timeout=300)
+    assert r.returncode == 0 and "violations 0" in r.stdout, r.stdout[-2000:]
+    assert int(r.stdout.split("checked ")[1].split()[0]) > 1000000
