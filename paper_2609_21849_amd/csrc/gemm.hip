@@ -1107,8 +1107,6 @@ struct AStage {
   }
 };
 
-using AStage256 = AStage<8>;
-
 // Operand fragment of activation panel `panel`, step s (0/1) of a staged chunk.
 __device__ __attribute__((always_inline)) inline v8i read_a_frag(const uint8_t* st, int panel, int s, int lane) {
   const int x = 4 * s + 2 * (lane >> 5);
@@ -1132,11 +1130,14 @@ __device__ __attribute__((always_inline)) inline v8i read_a_frag(const uint8_t* 
 // tiles blockIdx.x, + gridDim.x, ...), so a workgroup's next tile starts
 // loading while the stores of its previous tile drain. Prefetches that would
 // run past the last chunk of a tile are turned into out-of-range loads,
-// which return zeros without touching memory.
-template <int EPI>
+// which return zeros without touching memory. TM (4, 3, 2): tiles of 64 TM rows,
+// waves of 32 TM x 128 (plan_tile_rows).
+template <int EPI, int TM>
 __global__ void __launch_bounds__(256) k_gemm_fp8_direct(GemmArgs g) {
-  constexpr int A_STAGE = 8 * 4096;
-  constexpr int RA = AStage256::RA;
+  constexpr int A_STAGE = 2 * TM * 4096;
+  constexpr int RA = AStage<2 * TM>::RA;
+  constexpr int PG = (RA + TM - 2) / (TM - 1);      // pieces staged per MFMA group of step 1
+  constexpr int VB = (16 + 4 * TM - 1) / (4 * TM);  // weight loads per MFMA of step 0
   constexpr uint32_t OOB = 0x80000000u;
   constexpr int OUT_STAGE = 32 * (64 * 4 + 16);  // per wave: 32 rows of 128 bf16 + pad
   __shared__ __attribute__((aligned(16))) uint8_t smem[2 * A_STAGE];
@@ -1153,12 +1154,12 @@ __global__ void __launch_bounds__(256) k_gemm_fp8_direct(GemmArgs g) {
   const __amdgpu_buffer_rsrc_t rs_b = __builtin_amdgcn_make_buffer_rsrc(
       const_cast<uint8_t*>(g.w_codes), 0, (int)((int64_t)npanels_w * kcn * 4096), 0x00020000);
 
-  AStage256 A;
+  AStage<RA> A;
   uint32_t ob[4];
   v4i ga[RA];
   v8i fb[2][2][4];  // [chunk parity][step][weight panel]
   v8i fa[2];
-  v16f acc[4][4];
+  v16f acc[TM][4];
 
   // The chunk's byte offset is uniform, so it travels in the loads' scalar
   // offset and costs no per-lane arithmetic. Prefetches past the last chunk
@@ -1187,57 +1188,57 @@ __global__ void __launch_bounds__(256) k_gemm_fp8_direct(GemmArgs g) {
         fb[P][s][j] = (v8i){lo.x, lo.y, lo.z, lo.w, hi.x, hi.y, hi.z, hi.w};
       }
   };
-  // MFMA group f = (step f / 4, activation panel f % 4) on fragment fa[f % 2]
+  // MFMA group f = (step f / TM, activation panel f % TM) on fragment fa[f % 2]
   auto mgroup = [&](auto Pc, int f) __attribute__((always_inline)) {
     constexpr int P = decltype(Pc)::value;
 #pragma unroll
     for (int j = 0; j < 4; ++j)
-      acc[f & 3][j] = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(fb[P][f >> 2][j], fa[f & 1], acc[f & 3][j], 0, 0, 0, 0, 0, 0);
+      acc[f % TM][j] = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(fb[P][f / TM][j], fa[f & 1], acc[f % TM][j], 0, 0, 0, 0, 0, 0);
   };
   auto chunk = [&](auto Pc, int kc) __attribute__((always_inline)) {
     constexpr int P = decltype(Pc)::value;
     const uint8_t* cur = smem + P * A_STAGE;
     uint8_t* nxt = smem + (P ^ 1) * A_STAGE;
-    // step 0: weight loads of chunk kc + 1, activation fragments 1..4
+    // step 0: weight loads of chunk kc + 1, activation fragments 1..TM
     load_b(std::integral_constant<int, P ^ 1>(), kc + 1);
 #pragma unroll
-    for (int f = 0; f < 4; ++f) {
-      fa[(f + 1) & 1] = read_a_frag(cur, wm * 4 + ((f + 1) & 3), (f + 1) >> 2, lane);
+    for (int f = 0; f < TM; ++f) {
+      fa[(f + 1) & 1] = read_a_frag(cur, wm * TM + (f + 1) % TM, (f + 1) / TM, lane);
       mgroup(Pc, f);
     }
 #pragma unroll
-    for (int f = 0; f < 4; ++f) {
+    for (int f = 0; f < TM; ++f) {
       __builtin_amdgcn_sched_group_barrier(0x100, 2, 0);  // DS read: next fragment
 #pragma unroll
       for (int t = 0; t < 4; ++t) {
         __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);  // MFMA
-        __builtin_amdgcn_sched_group_barrier(0x020, 1, 0);  // VMEM read (weights)
+        __builtin_amdgcn_sched_group_barrier(0x020, VB, 0);  // VMEM read (weights)
       }
     }
     __builtin_amdgcn_sched_barrier(0);
-    // step 1, groups 4..6: stage activations of chunk kc + 1, load kc + 2.
+    // step 1 but its last group: stage activations of chunk kc + 1, load kc + 2.
     // The LDS writes sit between the fragment reads in program order (the
     // compiler cannot tell the two stages apart, so it keeps LDS accesses in
     // that order); each activation load follows the write of its register.
     const int a_so = kcl(kc + 2) * 128;
 #pragma unroll
-    for (int f = 4; f < 7; ++f) {
-      fa[(f + 1) & 1] = read_a_frag(cur, wm * 4 + ((f + 1) & 3), (f + 1) >> 2, lane);
+    for (int f = TM; f < 2 * TM - 1; ++f) {
+      fa[(f + 1) & 1] = read_a_frag(cur, wm * TM + (f + 1) % TM, (f + 1) / TM, lane);
 #pragma unroll
-      for (int it = 3 * (f - 4); it < 3 * (f - 3) && it < RA; ++it)
+      for (int it = PG * (f - TM); it < PG * (f - TM + 1) && it < RA; ++it)
         *reinterpret_cast<v4i*>(nxt + A.la[it]) = ga[it];
       mgroup(Pc, f);
 #pragma unroll
-      for (int it = 3 * (f - 4); it < 3 * (f - 3) && it < RA; ++it)
+      for (int it = PG * (f - TM); it < PG * (f - TM + 1) && it < RA; ++it)
         ga[it] = __builtin_amdgcn_raw_buffer_load_b128(rs_a, A.oa[it], a_so, 0);
     }
 #pragma unroll
-    for (int f = 4; f < 7; ++f) {
+    for (int f = 0; f < TM - 1; ++f) {
       __builtin_amdgcn_sched_group_barrier(0x100, 2, 0);  // DS read: next fragment
 #pragma unroll
       for (int t = 0; t < 4; ++t) {
         __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);  // MFMA
-        if (t < 3 && 3 * (f - 4) + t < RA) {
+        if (t < PG && PG * f + t < RA) {
           __builtin_amdgcn_sched_group_barrier(0x200, 1, 0);  // DS write
           __builtin_amdgcn_sched_group_barrier(0x020, 1, 0);  // VMEM read (activations)
         }
@@ -1246,9 +1247,9 @@ __global__ void __launch_bounds__(256) k_gemm_fp8_direct(GemmArgs g) {
     __builtin_amdgcn_sched_barrier(0);
     __syncthreads();
     __builtin_amdgcn_sched_barrier(0);
-    // group 7 covers the read of the next chunk's first fragment
-    fa[0] = read_a_frag(nxt, wm * 4, 0, lane);
-    mgroup(Pc, 7);
+    // the last group covers the read of the next chunk's first fragment
+    fa[0] = read_a_frag(nxt, wm * TM, 0, lane);
+    mgroup(Pc, 2 * TM - 1);
     __builtin_amdgcn_sched_group_barrier(0x100, 2, 0);
     __builtin_amdgcn_sched_group_barrier(0x008, 4, 0);
     __builtin_amdgcn_sched_barrier(0);
@@ -1259,7 +1260,7 @@ __global__ void __launch_bounds__(256) k_gemm_fp8_direct(GemmArgs g) {
     lane = tid & 63;
     int bm, bn;
     tile_coords(tile, g.tiles_m, g.tiles_n, bm, bn);
-    const int m0 = bm * 256, n0 = bn * 256;
+    const int m0 = bm * (64 * TM), n0 = bn * 256;
     A.init(g, m0, tid);
 #pragma unroll
     for (int j = 0; j < 4; ++j) {
@@ -1267,7 +1268,7 @@ __global__ void __launch_bounds__(256) k_gemm_fp8_direct(GemmArgs g) {
       ob[j] = (panel < (uint32_t)npanels_w) ? panel * (uint32_t)(kcn * 4096) + 16u * lane : OOB;
     }
 #pragma unroll
-    for (int i = 0; i < 4; ++i)
+    for (int i = 0; i < TM; ++i)
 #pragma unroll
       for (int j = 0; j < 4; ++j)
 #pragma unroll
@@ -1283,8 +1284,8 @@ __global__ void __launch_bounds__(256) k_gemm_fp8_direct(GemmArgs g) {
       load_b(std::integral_constant<int, 0>(), 0);
       __syncthreads();
 #pragma unroll
-      for (int f = 0; f < 8; ++f) {
-        fa[f & 1] = read_a_frag(smem, wm * 4 + (f & 3), f >> 2, lane);
+      for (int f = 0; f < 2 * TM; ++f) {
+        fa[f & 1] = read_a_frag(smem, wm * TM + f % TM, f / TM, lane);
         mgroup(std::integral_constant<int, 0>(), f);
       }
       __syncthreads();
@@ -1298,7 +1299,7 @@ __global__ void __launch_bounds__(256) k_gemm_fp8_direct(GemmArgs g) {
       // issues them in, so that the loop head's waits count the same loads
       load_b(std::integral_constant<int, 0>(), kc);
       load_a(kc + 1);
-      fa[0] = read_a_frag(smem, wm * 4, 0, lane);
+      fa[0] = read_a_frag(smem, wm * TM, 0, lane);
       for (; kc < kcn; kc += 2) {
         chunk(std::integral_constant<int, 0>(), kc);
         chunk(std::integral_constant<int, 1>(), kc + 1);
@@ -1307,7 +1308,7 @@ __global__ void __launch_bounds__(256) k_gemm_fp8_direct(GemmArgs g) {
     // Every operand write of this tile happened before its last barrier; the
     // next tile's first write to stage 0 can only race with the discarded
     // fragment read after that barrier.
-    store_tiles_epi<EPI, 4, 4>(g, acc, sout + wave * OUT_STAGE, m0 + wm * 128, n0 + wn * 128, lane, scale);
+    store_tiles_epi<EPI, TM, 4>(g, acc, sout + wave * OUT_STAGE, m0 + wm * (32 * TM), n0 + wn * 128, lane, scale);
   }
 }
 
@@ -1585,7 +1586,7 @@ __global__ void __launch_bounds__(256) k_gemm_fp8_t288(GemmArgs g) {
 // takes a row's 32-element scale block h from register half h of both lane
 // halves (elements 32 h + 16 g of the step in lane half g), and the scale of
 // block h from lane half h, so weights and activations are laid out that way
-// (MXFP8 packing, AStage256<MX8>):
+// (MXFP8 packing, AStage::init<MX8>):
 //   weights     : the FP8 packed images, plus one dword per panel, 256-wide
 //                 group and lane holding the lane's scales of its four steps
 //                 (the MXFP4 scale layout); chunk kc uses bytes 2 (kc % 2) + s;
@@ -3010,6 +3011,13 @@ static int device_cus() {
   return n;
 }
 
+// Measured (K = 3072 and 9216, whole and partial rounds).
+template <int MODE>
+constexpr RoundCost kRoundCost = MODE == MODE_FP8     ? RoundCost{80, 62}
+                                 : MODE == MODE_NVFP4 ? RoundCost{83, 56}
+                                 : MODE == MODE_MXFP8 ? RoundCost{92, 70}
+                                                      : RoundCost{86, 62};
+
 template <int MODE, int TM>
 static void launch_large_tm(GemmArgs g, int64_t cus, hipStream_t st) {
   g.tiles_m = (g.m + 64 * TM - 1) / (64 * TM);
@@ -3017,6 +3025,7 @@ static void launch_large_tm(GemmArgs g, int64_t cus, hipStream_t st) {
   const dim3 grid((unsigned)std::min<int64_t>((int64_t)g.tiles_m * g.tiles_n, cus));
   if constexpr (MODE == MODE_MXFP4) QG_LAUNCH_EPI(k_gemm_mxfp4_direct, grid, st, g, TM);
   else if constexpr (MODE == MODE_MXFP8) QG_LAUNCH_EPI(k_gemm_mxfp8_direct, grid, st, g, TM);
+  else if constexpr (MODE == MODE_FP8) QG_LAUNCH_EPI(k_gemm_fp8_direct, grid, st, g, TM);
   else QG_LAUNCH_EPI(k_gemm_nvfp4_direct, grid, st, g, TM);
 }
 
@@ -3024,15 +3033,15 @@ static void launch_large_tm(GemmArgs g, int64_t cus, hipStream_t st) {
 // output is the same sum in the same order whatever that is. Measured (back to
 // back calls, 256-row tiles -> chosen): MXFP8 500 x 9216 x 3072 30.4 -> 25.0 us (128
 // rows), 2304 x 9216 x 3072 68.0 -> 60.6 (192), 2300 x 3072 x 9216 81.8 -> 70.7 (128);
-// MXFP4 21.6 -> 15.1, 47.3 -> 40.2, 51.9 -> 42.6; NVFP4 3000 x 3072 x 3072 59.7 -> 50.6
+// MXFP4 21.6 -> 15.1, 47.3 -> 40.2, 51.9 -> 42.6; FP8 3000 x 3072 x 3072 30.8 -> 28.8
+// (192), 2300 x 3072 x 9216 71.6 -> 57.6 (128); NVFP4 3000 x 3072 x 3072 59.7 -> 50.6
 // (192), 2304 x 9216 x 3072 129 -> 106 (192). 256 rows stay at 4608 x 3072 and 4608 x
 // 9216 (K = 3072), where 192 take MXFP8 38 -> 57 and 108 -> 122 us, NVFP4 70 -> 100 and
 // 208 -> 216. Cutting the rows into a 256-row head of whole rounds and a shorter
 // tail in a second launch gained 1-2% or lost.
 template <int MODE>
 static hipError_t launch_large(const GemmArgs& g, int64_t cus, hipStream_t st) {
-  constexpr RoundCost cost = MODE == MODE_NVFP4 ? RoundCost{83, 56} : MODE == MODE_MXFP8 ? RoundCost{92, 70} : RoundCost{86, 62};
-  switch (plan_tile_rows(g.m, (g.n + 255) / 256, cus, cost)) {
+  switch (plan_tile_rows(g.m, (g.n + 255) / 256, cus, kRoundCost<MODE>).tm) {
     case 4: launch_large_tm<MODE, 4>(g, cus, st); break;
     case 3: launch_large_tm<MODE, 3>(g, cus, st); break;
     default: launch_large_tm<MODE, 2>(g, cus, st);
@@ -3040,16 +3049,16 @@ static hipError_t launch_large(const GemmArgs& g, int64_t cus, hipStream_t st) {
   return hipGetLastError();
 }
 
-// MXFP4 / MXFP8. Up to two rounds of 64 x 96 tiles on the CUs the split-K
-// kernel, above that 256 x 256 tiles: those walk K serially (about 25-40 us at
-// K = 3072 however few there are), while a split-K tile's waves share K and
-// the operands' L2 traffic is all that bounds it. Inside the split-K range the
-// narrowest tile that still gives every workgroup a CU of its own. Measured
-// (GPU time from graph replays, 256 x 256 -> split-K; best of 16 tilings within
-// 8% everywhere): MXFP4 1 x 3072 x 1024 12.7 -> 2.8 us, 256 x 3072 x 3072 25.0 ->
-// 6.8, 500 x 3072 x 3072 38 -> 10.8, 1024 x 3072 x 3072 (two rounds) 26.5 -> 19.5;
-// MXFP8 14.3 -> 3.1, 32.0 -> 10.3, 37.5 -> 15.0, 33.2 -> 27.9; three rounds (1500 x
-// 3072 x 3072) lose for MXFP8 (42.0 against 37.5).
+// MXFP4 / MXFP8. Up to a round of 64 x 96 tiles on the CUs the split-K kernel,
+// above that the large tiles: those walk K serially, while a split-K tile's waves
+// share K and the operands' L2 traffic is all that bounds it. Inside the split-K
+// range the narrowest tile that still gives every workgroup a CU of its own.
+// Measured (GPU time from graph replays, 256 x 256 -> split-K; best of 16 tilings
+// within 8% everywhere): MXFP4 1 x 3072 x 1024 12.7 -> 2.8 us, 256 x 3072 x 3072 25.0 ->
+// 6.8, 500 x 3072 x 3072 38 -> 10.8; MXFP8 14.3 -> 3.1, 32.0 -> 10.3, 37.5 -> 15.0.
+// Two rounds of split-K tiles against 128-row large ones, calls back to back: 1024 x
+// 3072 x 3072 MXFP4 18.8 / 14.2 us, MXFP8 26.8 / 24.0; 256 x 9216 x 3072 18.3 / 13.7, 26.8 /
+// 24.1; 700 x 4096 x 9216 41.1 / 37.9, 64.8 / 67.2.
 template <int MODE>
 static hipError_t launch_mx(GemmArgs g, hipStream_t st) {
   const int64_t cus = device_cus();
@@ -3059,7 +3068,9 @@ static hipError_t launch_mx(GemmArgs g, hipStream_t st) {
   if (rows32 * ((g.n + 95) / 96) <= cus) return run_splitk<MODE, 1, 3, 8, 1>(g, st);
   const int64_t t6496 = rows64 * ((g.n + 95) / 96);
   if (t6496 > cus && rows64 * ((g.n + 127) / 128) <= cus) return run_splitk<MODE, 2, 4, 8, 1>(g, st);
-  if (t6496 <= 2 * cus) return run_splitk<MODE, 2, 3, 4, 2>(g, st);
+  // (two rounds of them: only where K is short, or long in MXFP8)
+  if (t6496 <= cus || (t6496 <= 2 * cus && (g.k < 2048 || (MODE == MODE_MXFP8 && g.k > 6144))))
+    return run_splitk<MODE, 2, 3, 4, 2>(g, st);
   return launch_large<MODE>(g, cus, st);
 }
 
@@ -3126,25 +3137,29 @@ hipError_t launch_gemm(int a_fmt, const void* a, const uint8_t* a_bscale, const 
     // 3072 x 9216 34.2 -> 29.4 (at 889 x 1584 x 1152 it loses, 8.8 -> 9.2)
     if (k >= 2048 && (int64_t)((m + 63) / 64) * ((n + 95) / 96) <= cus)
       return run_splitk<MODE_FP8, 2, 3, 4, 2>(g, st);
-    // Too few 256 x 256 tiles to fill the chip: the 64 x 128 kernel's eight
-    // times as many workgroups win. Measured crossover (encoder and
-    // transformer widths, M = 128 .. 3072): below 3/8 of a tile per CU.
-    if (m <= 128 || 8 * tiles < 3 * cus) return run_fp8<1, 2>(g, st);
-    // 288 x 192 tiles where their rounds of tiles cover less area than the
-    // 256 x 256 tiles' rounds (the time of both kernels follows the round
-    // count); not for NVFP4 outputs, whose 16-blocks the 256 x 256 epilogue forms
+    // Too few large tiles to fill the chip: the 64 x 128 kernel's many more
+    // workgroups win. Measured crossover: 3/8 of a 128 x 256 tile per CU (1024 x
+    // 3072 x 3072, 96 tiles, 20.7 us against 20.4; 700 x 4096 x 9216, 96, 49.2 against
+    // 50.6; 1500 x 3072 x 3072, 144, 28.4 against 21.2); below K = 1024 3/8 of a 256 x
+    // 256 tile.
+    if (m <= 128 || (k < 1024 ? 8 * tiles < 3 * cus : 8 * ((m + 127) / 128 * g.tiles_n) <= 3 * (int64_t)cus))
+      return run_fp8<1, 2>(g, st);
+    // 288 x 192 tiles where their rounds take less than those of the 256-column
+    // tiles (a full round 92 % of one of 256 x 256: 4608 x 3072 x 3072 36.7 us against
+    // 37.7, 2800 x 9216 x 3072 71.1 against 76.1; but 2304 x 9216 x 3072 64.1 against
+    // 59.6 on 192-row tiles, 4200 x 4608 x 3072 59.0 against 54.9); not for NVFP4
+    // outputs, whose 16-blocks the 256-column epilogue forms
     const int t288_m = (int)((m + 287) / 288), t288_n = (int)((n + 191) / 192);
     const int64_t t288 = (int64_t)t288_m * t288_n;
     if (out_mode != OUT_NVFP4 &&
-        ((t288 + cus - 1) / cus) * (288 * 192) < (int64_t)((tiles + cus - 1) / cus) * (256 * 256)) {
+        92 * rounds_cost(t288, cus) < plan_tile_rows(m, g.tiles_n, cus, kRoundCost<MODE_FP8>).cost) {
       g.tiles_m = t288_m;
       g.tiles_n = t288_n;
       const dim3 grid((unsigned)std::min<int64_t>(t288, cus));
       QG_LAUNCH_EPI_NO_NVFP4(k_gemm_fp8_t288, grid, st, g);
       return hipGetLastError();
     }
-    QG_LAUNCH_EPI(k_gemm_fp8_direct, dim3(std::min(tiles, cus)), st, g);
-    return hipGetLastError();
+    return launch_large<MODE_FP8>(g, cus, st);
   } else if (a_fmt == 2) {
     g.tiles_m = (g.m + 255) / 256;
     g.tiles_n = (g.n + 255) / 256;

@@ -24,22 +24,28 @@ struct RoundCost {
   int rows192, rows128;
 };
 
+// Time of `tiles` equal tiles, one a CU at a time, in percent of a full round
+// times the CUs. A tile walks K serially, so a round that is partly empty costs
+// nearly what a full one does (72 % of it and up: fewer busy CUs run at a higher
+// clock and share less bandwidth).
+inline int64_t rounds_cost(int64_t tiles, int64_t cus) {
+  const int64_t rest = tiles % cus;
+  return 100 * (tiles / cus) * cus + (rest > 0 ? 72 * cus + 28 * rest : 0);
+}
+
 // Height of the tiles of a persistent large-tile GEMM, 64 tm rows (tm = 4, 3, 2),
-// for m rows and tiles_n tile columns: the one whose rounds of tiles take least.
-// A tile walks K serially, so a round that is partly empty costs nearly what a
-// full one does (72 % of it and up: fewer busy CUs run at a higher clock and share
-// less bandwidth), and shorter tiles are cheaper where they don't start another.
-inline int plan_tile_rows(int64_t m, int64_t tiles_n, int64_t cus, RoundCost cost) {
-  int best = 4;
-  int64_t best_cost = -1;
+// for m rows and tiles_n tile columns: the one whose rounds of tiles take least
+// (shorter tiles are cheaper where they don't start another round).
+struct TileRows {
+  int tm;
+  int64_t cost;  // rounds_cost x percent of a 256-row round
+};
+inline TileRows plan_tile_rows(int64_t m, int64_t tiles_n, int64_t cus, RoundCost cost) {
+  TileRows best = {0, 0};
   for (int tm = 4; tm >= 2; --tm) {
-    const int64_t tiles = (m + 64 * tm - 1) / (64 * tm) * tiles_n, rest = tiles % cus;
-    const int64_t rounds = 100 * (tiles / cus) * cus + (rest > 0 ? 72 * cus + 28 * rest : 0);
-    const int64_t c = rounds * (tm == 4 ? 100 : tm == 3 ? cost.rows192 : cost.rows128);
-    if (best_cost < 0 || c < best_cost) {
-      best_cost = c;
-      best = tm;
-    }
+    const int64_t c = rounds_cost((m + 64 * tm - 1) / (64 * tm) * tiles_n, cus) *
+                      (tm == 4 ? 100 : tm == 3 ? cost.rows192 : cost.rows128);
+    if (best.tm == 0 || c < best.cost) best = {tm, c};
   }
   return best;
 }

@@ -19,13 +19,13 @@ int main() {
       if (id >= 8 && t != qg::xcd_tile(id - 8, total) + 1) { ++bad; printf("total %d id %d not contiguous\n", total, id); }
     }
   }
-  const qg::RoundCost costs[] = {{83, 56}, {92, 70}, {86, 62}};
+  const qg::RoundCost costs[] = {{83, 56}, {92, 70}, {86, 62}, {80, 62}};
   for (int64_t cus : {256, 304, 64})
     for (const qg::RoundCost& c : costs)
       for (int64_t m = 1; m <= 6000; m += 7)
         for (int64_t tn = 1; tn <= 48; ++tn) {
           ++checked;
-          const int tm = qg::plan_tile_rows(m, tn, cus, c);
+          const int tm = qg::plan_tile_rows(m, tn, cus, c).tm;
           if (tm < 2 || tm > 4) { ++bad; printf("m %lld tn %lld tm %d\n", (long long)m, (long long)tn, tm); continue; }
           const auto time = [&](int h) {  // the stated model, in rounds of 256-row tiles
             const int64_t tiles = (m + 64 * h - 1) / (64 * h) * tn;

@@ -14,19 +14,21 @@ from test_gpu_tile_epilogues import FMTS, test_ragged_tiles_every_output as ever
 
 pytestmark = pytest.mark.gpu
 
-# on 256 CUs: 2420 x 5136 takes 256-row tiles, 1230 x 8208 192, 1900 x 4112 128
+# on 256 CUs: 2420 x 5136 takes 256-row tiles (FP8 288 x 192, 256 rows at 1777 x
+# 7008 instead), 1230 x 8208 192, 1900 x 4112 128
 SHAPES = [(2420, 5136), (1230, 8208), (1900, 4112)]
 
 
-@pytest.mark.parametrize("kind,k", [("nvfp4", 256), ("mxfp4", 512), ("mxfp8", 256)])
+@pytest.mark.parametrize("kind,k", [("nvfp4", 256), ("mxfp4", 512), ("mxfp8", 256), ("fp8", 1024)])
 @pytest.mark.parametrize("m,n", SHAPES)
 def test_every_output(kind, m, n, k):
     every_output(kind, m, n, k)
 
 
 @pytest.mark.parametrize("kind,k", [("nvfp4", 128), ("nvfp4", 384), ("nvfp4", 640), ("mxfp4", 256), ("mxfp4", 768),
-                                    ("mxfp4", 1024), ("mxfp8", 512), ("mxfp8", 768)])
-@pytest.mark.parametrize("m,n", SHAPES)
+                                    ("mxfp4", 1024), ("mxfp8", 512), ("mxfp8", 768),
+                                    ("fp8", 1024), ("fp8", 1152)])
+@pytest.mark.parametrize("m,n", SHAPES + [(1777, 7008)])
 def test_values_at_tile_edges(kind, m, n, k):
     log("tile heights %s m=%d n=%d k=%d" % (kind, m, n, k))
     x = synth.normal_bf16(m, k, 1.0, 52, 0)
