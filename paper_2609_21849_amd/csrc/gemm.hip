@@ -48,7 +48,7 @@
 
 namespace qg {
 
-enum { MODE_FP8 = 1, MODE_NVFP4 = 2, MODE_MXFP4 = 3, MODE_MXFP8 = 4 };  // format ids
+enum { MODE_W4A16 = 0, MODE_FP8 = 1, MODE_NVFP4 = 2, MODE_MXFP4 = 3, MODE_MXFP8 = 4 };  // format ids
 
 typedef float v16f __attribute__((ext_vector_type(16)));
 
@@ -2355,14 +2355,15 @@ __global__ void __launch_bounds__(256) k_gemm_mxfp4_direct(GemmArgs g) {
 // fragments. The bf16 output staging of the epilogue reuses activation
 // stage 1, which no wave reads after the last chunk's barrier (a tile's
 // chunks run in pairs, stage 0 then 1), and the next tile writes it only
-// after its first barrier.
-template <int EPI>
+// after its first barrier. TM (4, 3, 2): tiles of 64 TM rows, TM staging
+// quarters (plan_tile_rows).
+template <int EPI, int TM>
 __global__ void __launch_bounds__(256) k_gemm_w4a16_direct(GemmArgs g) {
-  constexpr int A_STAGE = 8 * 8192;              // 256 rows x 128 bf16
+  constexpr int A_STAGE = 2 * TM * 8192;         // 64 TM rows x 128 bf16
   constexpr int OUT_STAGE = 32 * (64 * 4 + 16);
   constexpr uint32_t OOB = 0x80000000u;
-  static_assert(4 * OUT_STAGE <= A_STAGE, "the output staging fits in one activation stage");
-  __shared__ __attribute__((aligned(16))) uint8_t smem[2 * A_STAGE];
+  // the output staging takes activation stage 1 and, for 128-row tiles, 2 KiB more
+  __shared__ __attribute__((aligned(16))) uint8_t smem[A_STAGE + (4 * OUT_STAGE > A_STAGE ? 4 * OUT_STAGE : A_STAGE)];
 
   int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -2380,7 +2381,7 @@ __global__ void __launch_bounds__(256) k_gemm_w4a16_direct(GemmArgs g) {
   const __amdgpu_buffer_rsrc_t rs_bs = __builtin_amdgcn_make_buffer_rsrc(
       const_cast<uint8_t*>(g.w_scales), 0, (int)((int64_t)npanels_w * kcn * 256), 0x00020000);
   // staging: thread tid copies piece c = tid % 16 of rows 16 i + tid / 16,
-  // i = 0 .. 15; its LDS slots depend only on i % 2 (and i / 2 through the
+  // i = 0 .. 4 TM - 1; its LDS slots depend only on i % 2 (and i / 2 through the
   // panel, a constant offset)
   const int cpc = tid & 15, s_c = cpc & 7, g_c = cpc >> 3, rlo = tid >> 4;
   uint32_t la_pair[2];
@@ -2388,16 +2389,16 @@ __global__ void __launch_bounds__(256) k_gemm_w4a16_direct(GemmArgs g) {
   for (int h = 0; h < 2; ++h)
     la_pair[h] = (uint32_t)(s_c * 1024 + ((((16 * h + rlo) + 32 * g_c) ^ (s_c + 8 * g_c)) * 16));
 
-  uint32_t oa[16], ob[4], osb[4];
+  uint32_t oa[4 * TM], ob[4], osb[4];
   v4i ga[8];            // two staging quarters (register sets 0 and 1)
   v4i bc[2][4][2];      // weight codes [chunk parity][panel][half]
   uint32_t bs[2][4];    // weight E4M3 scales [chunk parity][panel]
   float sw[4][4];       // weight block scales of the current chunk, fp32 [panel][block]
-  v8bf fa[2][4], fb[2][4];
-  v16f acc[4][4];
+  v8bf fa[2][TM], fb[2][4];
+  v16f acc[TM][4];
 
   auto kcl = [&](int kc) __attribute__((always_inline)) { return kc < kcn ? kc : kcn - 1; };
-  // quarter q of the thread's 16 pieces (rows 16 i + tid / 16, i = 4 q ..
+  // quarter q (of TM) of the thread's 4 TM pieces (rows 16 i + tid / 16, i = 4 q ..
   // 4 q + 3) through register set q % 2
   auto load_a = [&](int kc, int q) __attribute__((always_inline)) {
 #pragma unroll
@@ -2423,9 +2424,9 @@ __global__ void __launch_bounds__(256) k_gemm_w4a16_direct(GemmArgs g) {
   };
   auto read_a = [&](const uint8_t* st, int s, int D) __attribute__((always_inline)) {
 #pragma unroll
-    for (int i = 0; i < 4; ++i)
+    for (int i = 0; i < TM; ++i)
       fa[D][i] = __builtin_bit_cast(v8bf, *reinterpret_cast<const v4i*>(
-          st + (wm * 4 + i) * 8192 + s * 1024 + ((lane ^ (s + 8 * gq)) * 16)));
+          st + (wm * TM + i) * 8192 + s * 1024 + ((lane ^ (s + 8 * gq)) * 16)));
   };
   // the lane's four E4M3 block scales of each panel, exactly (never negative or NaN)
   auto convert_b_scales = [&](auto Pc) __attribute__((always_inline)) {
@@ -2448,18 +2449,18 @@ __global__ void __launch_bounds__(256) k_gemm_w4a16_direct(GemmArgs g) {
   };
   auto mfmas = [&](int D) __attribute__((always_inline)) {
 #pragma unroll
-    for (int i = 0; i < 4; ++i)
+    for (int i = 0; i < TM; ++i)
 #pragma unroll
       for (int j = 0; j < 4; ++j)
         acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fb[D][j], fa[D][i], acc[i][j], 0, 0, 0);
   };
-  // 16 MFMAs, each followed by its share of the next step's expansion (64 VALU)
+  // 4 TM MFMAs, each followed by its share of the next step's expansion (64 VALU)
   auto interleave = [&](int nvmem, int nds_r, int nds_w) __attribute__((always_inline)) {
 #pragma unroll
-    for (int t = 0; t < 16; ++t) {
+    for (int t = 0; t < 4 * TM; ++t) {
       __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);  // MFMA
-      __builtin_amdgcn_sched_group_barrier(0x002, 6, 0);  // VALU
-      if (t < nvmem) __builtin_amdgcn_sched_group_barrier(0x020, 1, 0);
+      __builtin_amdgcn_sched_group_barrier(0x002, TM == 4 ? 6 : TM == 3 ? 7 : 9, 0);  // VALU
+      if (t < nvmem) __builtin_amdgcn_sched_group_barrier(0x020, TM == 4 ? 1 : 2, 0);
       if (t < nds_r) __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);
       if (t < nds_w) __builtin_amdgcn_sched_group_barrier(0x200, 1, 0);
     }
@@ -2479,14 +2480,17 @@ __global__ void __launch_bounds__(256) k_gemm_w4a16_direct(GemmArgs g) {
       // four stores and four loads per step keep the compiler on the
       // MFMA / expansion interleave
       if (s == 0) { load_b(Q, kc + 1); load_a(kc + 1, 0); load_a(kc + 1, 1); }
-      if (s == 2) { write_a(nxt, 0); load_a(kc + 1, 2); }
-      if (s == 3) { write_a(nxt, 1); load_a(kc + 1, 3); }
-      if (s == 5) write_a(nxt, 2);
-      if (s == 6) write_a(nxt, 3);
+      if (s == 2) write_a(nxt, 0);
+      if (s == 2 && TM > 2) load_a(kc + 1, 2);
+      if (s == 3) write_a(nxt, 1);
+      if (s == 3 && TM > 3) load_a(kc + 1, 3);
+      if (s == 5 && TM > 2) write_a(nxt, 2);
+      if (s == 6 && TM > 3) write_a(nxt, 3);
       read_a(cur, s + 1, (s + 1) & 1);
       mfmas(s & 1);
       expand(Pc, s + 1, (s + 1) & 1);
-      interleave(s == 0 ? 20 : (s == 2 || s == 3) ? 4 : 0, 4, (s == 2 || s == 3 || s >= 5) ? 4 : 0);
+      constexpr int AL = TM > 2 ? 4 : 0, AW = TM > 3 ? 4 : 0;  // of quarters 2 and 3
+      interleave(s == 0 ? 20 : s == 2 ? AL : s == 3 ? AW : 0, TM, (s == 2 || s == 3) ? 4 : s == 5 ? AL : s == 6 ? AW : 0);
       __builtin_amdgcn_sched_barrier(0);
     }
     __syncthreads();
@@ -2496,7 +2500,7 @@ __global__ void __launch_bounds__(256) k_gemm_w4a16_direct(GemmArgs g) {
     convert_b_scales(Q);
     mfmas(1);
     expand(Q, 0, 0);
-    interleave(0, 4, 0);
+    interleave(0, TM, 0);
     __builtin_amdgcn_sched_barrier(0);
   };
 
@@ -2507,9 +2511,9 @@ __global__ void __launch_bounds__(256) k_gemm_w4a16_direct(GemmArgs g) {
     gq = lane >> 5;
     int bm, bn;
     tile_coords(tile, g.tiles_m, g.tiles_n, bm, bn);
-    const int m0 = bm * 256, n0 = bn * 256;
+    const int m0 = bm * (64 * TM), n0 = bn * 256;
 #pragma unroll
-    for (int i = 0; i < 16; ++i) {
+    for (int i = 0; i < 4 * TM; ++i) {
       const uint32_t row = (uint32_t)(m0 + 16 * i + rlo);
       oa[i] = (row < (uint32_t)g.m) ? row * lda2 + 16u * cpc : OOB;
     }
@@ -2521,7 +2525,7 @@ __global__ void __launch_bounds__(256) k_gemm_w4a16_direct(GemmArgs g) {
       osb[j] = in ? panel * (uint32_t)(kcn * 256) + 8u * r + 4u * gq : OOB;
     }
 #pragma unroll
-    for (int i = 0; i < 4; ++i)
+    for (int i = 0; i < TM; ++i)
 #pragma unroll
       for (int j = 0; j < 4; ++j)
 #pragma unroll
@@ -2532,7 +2536,7 @@ __global__ void __launch_bounds__(256) k_gemm_w4a16_direct(GemmArgs g) {
     if (kcn & 1) {
       load_b(std::integral_constant<int, 0>(), 0);
 #pragma unroll
-      for (int q = 0; q < 4; ++q) {
+      for (int q = 0; q < TM; ++q) {
         load_a(0, q);
         write_a(smem, q);
       }
@@ -2550,7 +2554,7 @@ __global__ void __launch_bounds__(256) k_gemm_w4a16_direct(GemmArgs g) {
     if (kc < kcn) {
       load_b(std::integral_constant<int, 0>(), kc);
 #pragma unroll
-      for (int q = 0; q < 4; ++q) {
+      for (int q = 0; q < TM; ++q) {
         load_a(kc, q);
         write_a(smem, q);
       }
@@ -2563,7 +2567,7 @@ __global__ void __launch_bounds__(256) k_gemm_w4a16_direct(GemmArgs g) {
         chunk(std::integral_constant<int, 1>(), kc + 1);
       }
     }
-    store_tiles_epi<EPI, 4, 4>(g, acc, smem + A_STAGE + wave * OUT_STAGE, m0 + wm * 128, n0 + wn * 128, lane, scale);
+    store_tiles_epi<EPI, TM, 4>(g, acc, smem + A_STAGE + wave * OUT_STAGE, m0 + wm * (32 * TM), n0 + wn * 128, lane, scale);
   }
 }
 
@@ -3016,6 +3020,7 @@ template <int MODE>
 constexpr RoundCost kRoundCost = MODE == MODE_FP8     ? RoundCost{80, 62}
                                  : MODE == MODE_NVFP4 ? RoundCost{83, 56}
                                  : MODE == MODE_MXFP8 ? RoundCost{92, 70}
+                                 : MODE == MODE_W4A16 ? RoundCost{86, 71}
                                                       : RoundCost{86, 62};
 
 template <int MODE, int TM>
@@ -3026,6 +3031,7 @@ static void launch_large_tm(GemmArgs g, int64_t cus, hipStream_t st) {
   if constexpr (MODE == MODE_MXFP4) QG_LAUNCH_EPI(k_gemm_mxfp4_direct, grid, st, g, TM);
   else if constexpr (MODE == MODE_MXFP8) QG_LAUNCH_EPI(k_gemm_mxfp8_direct, grid, st, g, TM);
   else if constexpr (MODE == MODE_FP8) QG_LAUNCH_EPI(k_gemm_fp8_direct, grid, st, g, TM);
+  else if constexpr (MODE == MODE_W4A16) QG_LAUNCH_EPI_NO_NVFP4(k_gemm_w4a16_direct, grid, st, g, TM);
   else QG_LAUNCH_EPI(k_gemm_nvfp4_direct, grid, st, g, TM);
 }
 
@@ -3220,17 +3226,15 @@ hipError_t launch_gemm(int a_fmt, const void* a, const uint8_t* a_bscale, const 
       else hipLaunchKernelGGL((k_w4a16_stream<3, 8, 12>), dim3(grid), dim3(768), (size_t)xbytes, st, g);
       return hipGetLastError();
     }
-    // Past the ridge point with enough 256 x 256 tiles: the persistent
-    // W4A4-shaped kernel (1555 x 4512 x 3968, 126 tiles: 87 us against 95 on 64 x 64
-    // split-K tiles; 1500 x 3072 x 3072, 72 tiles: 68 against 53)
-    const int t256_m = (int)((m + 255) / 256), t256_n = (int)((n + 255) / 256);
-    const int64_t t256 = (int64_t)t256_m * t256_n, cus = device_cus();
-    if (m > 128 && 8 * t256 >= 3 * cus) {
-      g.tiles_m = t256_m;
-      g.tiles_n = t256_n;
-      QG_LAUNCH_EPI_NO_NVFP4(k_gemm_w4a16_direct, dim3((unsigned)std::min<int64_t>(t256, cus)), st, g);
-      return hipGetLastError();
-    }
+    // Past the ridge point with enough large tiles: the persistent W4A4-shaped
+    // kernel. From 21/32 of a round of 128 x 256 tiles (split-K against 128-row
+    // tiles, back to back: 500 x 9216 x 3072, 144 tiles, 50.5 / 53.6 us; 1280 x 4096 x 4096,
+    // 160, 66.1 / 69.2; 3500 x 1536 x 3072, 168, 57.6 / 53.0), or 3/8 of one of 256 x 256.
+    // Heights (256 rows -> chosen): 1024 x 6144 x 3072 68.4 -> 54.0 us (128), 2304 x 9216 x
+    // 3072 146.7 -> 128.8 (192), 1900 x 3072 x 1024 28.3 -> 21.3 (128).
+    const int64_t t256_n = (n + 255) / 256, cus = device_cus();
+    if (m > 128 && (8 * ((m + 255) / 256 * t256_n) >= 3 * cus || 32 * ((m + 127) / 128 * t256_n) >= 21 * cus))
+      return launch_large<MODE_W4A16>(g, cus, st);
     // Split-K tilings. Up to 32 rows: one-panel workgroups, all chunks of a wave
     // in one batch of loads only where that is one (1 x 3072 x 1024 4.4 -> 3.9 us
     // with a chunk at a time; at K > 3072 that loses, 32 x 2048 x 6144 15.6 ->

@@ -19,7 +19,7 @@ int main() {
       if (id >= 8 && t != qg::xcd_tile(id - 8, total) + 1) { ++bad; printf("total %d id %d not contiguous\n", total, id); }
     }
   }
-  const qg::RoundCost costs[] = {{83, 56}, {92, 70}, {86, 62}, {80, 62}};
+  const qg::RoundCost costs[] = {{83, 56}, {92, 70}, {86, 62}, {80, 62}, {86, 71}};
   for (int64_t cus : {256, 304, 64})
     for (const qg::RoundCost& c : costs)
       for (int64_t m = 1; m <= 6000; m += 7)
