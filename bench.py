@@ -136,7 +136,7 @@ def traffic_probe(kind):
 
 
 QUANT_SHAPES = ((4608, 3072), (4608, 9216))   # the transformer linears' two activation sizes
-QUANT_KERNELS = ("k_amax_dense", "k_finalize", "k_quant_dense")
+QUANT_KERNELS = ("k_amax_units", "k_finalize", "k_quant_units")
 
 
 def quant_probe():
@@ -229,8 +229,8 @@ def quant_summary(fetch_dir, write_dir, trace_dir, out_md):
     for fname in ("FP8", "NVFP4"):
         for (m, k) in QUANT_SHAPES:
             n = m * k
-            alg = {"k_amax_dense": 2.0 * n, "k_finalize": 4096.0,
-                   "k_quant_dense": 2.0 * n + (n if fname == "FP8" else n / 2 + n / 16)}
+            alg = {"k_amax_units": 2.0 * n, "k_finalize": 4096.0,
+                   "k_quant_units": 2.0 * n + (n if fname == "FP8" else n / 2 + n / 16)}
             for kname in QUANT_KERNELS:
                 sl = slice(per_size * i + 1, per_size * i + per_size)   # the three timed calls
                 fb = sum(float(r["Counter_Value"]) for r in fk[kname][sl]) / 3 * 1024 / f_factor
