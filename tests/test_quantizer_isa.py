@@ -1,0 +1,41 @@
+"""What the compiler makes of the memory-bound quantizer kernels, read from the
+assembly of csrc/quantize.hip as the library is built: no GPU, and no timing."""
+import os
+import re
+import shutil
+import subprocess
+
+import pytest
+
+from paper_2609_21849_amd import build as qbuild
+
+pytestmark = pytest.mark.skipif(not (shutil.which("hipcc") or os.path.exists("/opt/rocm/bin/hipcc")),
+                                reason="hipcc not available")
+
+
+@pytest.fixture(scope="module")
+def kernels(tmp_path_factory):
+    """Mangled kernel name -> its instructions."""
+    out = str(tmp_path_factory.mktemp("isa") / "quantize.s")
+    subprocess.run([qbuild.HIPCC, *qbuild.COMMON, "--cuda-device-only", "-S", os.path.join(qbuild.CSRC, "quantize.hip"),
+                    "-o", out], check=True, capture_output=True)
+    found, name = {}, None
+    for line in open(out):
+        m = re.match(r"(_ZN2qg\w+):", line)
+        if m:
+            name = m.group(1)
+            found[name] = []
+        elif name and line.startswith("\t") and not line.startswith("\t."):
+            found[name].append(line.strip())
+            if line.strip().startswith("s_endpgm"):
+                name = None
+    return found
+
+
+def test_mx_rows_of_any_alignment_load_a_unit_at_once(kernels):
+    # a thread's eight bf16 elements: one 16-byte load, not eight 2-byte ones
+    mine = {n: k for n, k in kernels.items() if "10k_quant_mxI" in n}
+    assert len(mine) == 2
+    for name, code in mine.items():
+        loads = [i.split()[0] for i in code if i.startswith("global_load")]
+        assert loads == ["global_load_dwordx4"], (name, loads)
