@@ -670,147 +670,141 @@ __global__ void __launch_bounds__(256) k_quant_mx(const uint16_t* __restrict__ x
 
 // ---------------------------------------------------------------- dequant
 // out = fl(e4m3(q) * s), fl(fl(e2m1(q) * e4m3(s_b)) * s_t) or (MX) e * 2^(E - 127),
-// as fp32 or RNE bf16; one thread per 16 consecutive elements of the dense tensor.
+// as fp32 or RNE bf16; HBM-bound. One thread per 8 consecutive elements of the
+// dense tensor, so that the 16-byte stores of a wave lie next to each other (bf16)
+// or leave gaps that its next store fills (fp32). With 16 elements a thread they
+// were 32 and 64 bytes apart: 9216 x 3072 to fp32 36.7 us (MXFP4), 37.8 (MXFP8),
+// 36.8 (NVFP4), 45.3 (FP8), now 22.8, 24.1, 22.7 and 23.1 (5.5-6.1 TB/s); to bf16
+// 16.4, 19.5, 15.3 and 19.3, now 13.4, 15.4, 13.0 and 14.4.
 // Codes are decoded by the hardware conversions at unit scale (exact) and bf16
 // results rounded by v_cvt_pk_bf16_f32; a thread that could produce a NaN (a NaN
-// code or scale, an infinite scale) takes the integer decoders and the software
-// rounding, whose NaN bits are fixed. With those for every element (10-15 vector
-// instructions each) the kernels were VALU-bound: NVFP4 9216 x 3072 to bf16
-// 17.8 us -> 15.0 (72 MB).
-template <bool F32OUT, bool NANS>
-__device__ inline void store16(void* out, int64_t e, const float (&v)[16], int64_t cnt, bool vec) {
+// code or scale, an infinite scale) gives it the fixed bits of dec_e4m3 and
+// f32_to_bf16. VEC: 16-byte aligned output (a template argument: behind a run-time
+// one the compiler merged both forms into 4-byte stores, 71 us for NVFP4 to fp32).
+template <bool F32OUT, bool VEC, bool NANS>
+__device__ inline void store8(void* out, int64_t e, const float (&v)[8]) {
   if (F32OUT) {
     float* o = reinterpret_cast<float*>(out) + e;
-    if (vec && cnt == 16) {
-#pragma unroll
-      for (int i = 0; i < 4; ++i)
-        reinterpret_cast<float4*>(o)[i] = make_float4(v[4 * i], v[4 * i + 1], v[4 * i + 2], v[4 * i + 3]);
+    if (VEC) {
+      reinterpret_cast<float4*>(o)[0] = make_float4(v[0], v[1], v[2], v[3]);
+      reinterpret_cast<float4*>(o)[1] = make_float4(v[4], v[5], v[6], v[7]);
     } else {
-      for (int64_t i = 0; i < cnt; ++i) o[i] = v[i];
+#pragma unroll
+      for (int i = 0; i < 8; ++i) o[i] = v[i];
     }
   } else {
     uint16_t* o = reinterpret_cast<uint16_t*>(out) + e;
-    uint32_t w[8];
+    uint32_t w[4];
 #pragma unroll
-    for (int i = 0; i < 8; ++i)
+    for (int i = 0; i < 4; ++i)
       w[i] = NANS ? f32_to_bf16(v[2 * i]) | (f32_to_bf16(v[2 * i + 1]) << 16) : pk_bf16(v[2 * i], v[2 * i + 1]);
-    if (vec && cnt == 16) {
-      reinterpret_cast<uint4*>(o)[0] = make_uint4(w[0], w[1], w[2], w[3]);
-      reinterpret_cast<uint4*>(o)[1] = make_uint4(w[4], w[5], w[6], w[7]);
+    if (VEC) {
+      *reinterpret_cast<uint4*>(o) = make_uint4(w[0], w[1], w[2], w[3]);
     } else {
-      for (int64_t i = 0; i < cnt; ++i) o[i] = (uint16_t)(w[i >> 1] >> (16 * (i & 1)));
+#pragma unroll
+      for (int i = 0; i < 8; ++i) o[i] = (uint16_t)(w[i >> 1] >> (16 * (i & 1)));
     }
   }
 }
 
 __device__ inline bool finite(float f) { return (f2u(f) & 0x7F800000u) != 0x7F800000u; }
 
-// 16 E4M3 codes times s. A finite s and no NaN code (0x7F, 0xFF) leave no NaN.
+// 8 E4M3 codes times s. A finite s and no NaN code (0x7F, 0xFF) leave no NaN;
+// the NaN codes become the fp32 NaN of their sign.
 template <bool F32OUT>
-__device__ inline void dequant_e4m3x16(const uint32_t (&w)[4], float s, void* out, int64_t e, int64_t cnt, bool vec) {
-  uint32_t nan = 0;
+__device__ inline void dequant_e4m3x8(const uint2 c, float s, void* out, int64_t e) {
+  const uint32_t w[2] = {c.x, c.y};
+  const uint32_t nan = ((w[0] & 0x7F7F7F7Fu) + 0x01010101u) | ((w[1] & 0x7F7F7F7Fu) + 0x01010101u);
+  float v[8];
 #pragma unroll
-  for (int i = 0; i < 4; ++i) nan |= (w[i] & 0x7F7F7F7Fu) + 0x01010101u;
-  float v[16];
+  for (int i = 0; i < 2; ++i) {
+    const v2f a = __builtin_amdgcn_cvt_scalef32_pk_f32_fp8(w[i], 1.0f, false);
+    const v2f b = __builtin_amdgcn_cvt_scalef32_pk_f32_fp8(w[i], 1.0f, true);
+    v[4 * i] = a.x;
+    v[4 * i + 1] = a.y;
+    v[4 * i + 2] = b.x;
+    v[4 * i + 3] = b.y;
+  }
   if (finite(s) && (nan & 0x80808080u) == 0u) {
 #pragma unroll
-    for (int i = 0; i < 4; ++i) {
-      const v2f a = __builtin_amdgcn_cvt_scalef32_pk_f32_fp8(w[i], 1.0f, false);
-      const v2f b = __builtin_amdgcn_cvt_scalef32_pk_f32_fp8(w[i], 1.0f, true);
-      v[4 * i] = __fmul_rn(a.x, s);
-      v[4 * i + 1] = __fmul_rn(a.y, s);
-      v[4 * i + 2] = __fmul_rn(b.x, s);
-      v[4 * i + 3] = __fmul_rn(b.y, s);
-    }
-    store16<F32OUT, false>(out, e, v, cnt, vec);
+    for (int i = 0; i < 8; ++i) v[i] = __fmul_rn(v[i], s);
+    store8<F32OUT, true, false>(out, e, v);
   } else {
 #pragma unroll
-    for (int i = 0; i < 16; ++i) v[i] = __fmul_rn(dec_e4m3((w[i >> 2] >> (8 * (i & 3))) & 0xFFu), s);
-    store16<F32OUT, true>(out, e, v, cnt, vec);
+    for (int i = 0; i < 8; ++i) {
+      const uint32_t code = (w[i >> 2] >> (8 * (i & 3))) & 0xFFu;
+      v[i] = __fmul_rn((code & 0x7Fu) == 0x7Fu ? dec_e4m3(code) : v[i], s);
+    }
+    store8<F32OUT, true, true>(out, e, v);
   }
 }
 
-// 16 E2M1 codes times sb (the product exact), then times s_t.
-template <bool F32OUT>
-__device__ inline void dequant_e2m1x16(const uint2 c, float sb, float s_t, void* out, int64_t e, bool vec) {
-  const uint32_t w[2] = {c.x, c.y};
-  float v[16];
-  if (finite(sb) && finite(s_t)) {
+// 8 E2M1 codes times sb (the product exact), then times s_t.
+template <bool F32OUT, bool VEC>
+__device__ inline void dequant_e2m1x8(uint32_t w, float sb, float s_t, void* out, int64_t e) {
+  const v2f d[4] = {__builtin_amdgcn_cvt_scalef32_pk_f32_fp4(w, 1.0f, 0),
+                    __builtin_amdgcn_cvt_scalef32_pk_f32_fp4(w, 1.0f, 1),
+                    __builtin_amdgcn_cvt_scalef32_pk_f32_fp4(w, 1.0f, 2),
+                    __builtin_amdgcn_cvt_scalef32_pk_f32_fp4(w, 1.0f, 3)};
+  float v[8];
 #pragma unroll
-    for (int i = 0; i < 2; ++i) {
-      const v2f d[4] = {__builtin_amdgcn_cvt_scalef32_pk_f32_fp4(w[i], 1.0f, 0),
-                        __builtin_amdgcn_cvt_scalef32_pk_f32_fp4(w[i], 1.0f, 1),
-                        __builtin_amdgcn_cvt_scalef32_pk_f32_fp4(w[i], 1.0f, 2),
-                        __builtin_amdgcn_cvt_scalef32_pk_f32_fp4(w[i], 1.0f, 3)};
-#pragma unroll
-      for (int j = 0; j < 4; ++j) {
-        v[8 * i + 2 * j] = __fmul_rn(__fmul_rn(d[j].x, sb), s_t);
-        v[8 * i + 2 * j + 1] = __fmul_rn(__fmul_rn(d[j].y, sb), s_t);
-      }
-    }
-    store16<F32OUT, false>(out, e, v, 16, vec);
-  } else {
-#pragma unroll
-    for (int i = 0; i < 16; ++i)
-      v[i] = __fmul_rn(__fmul_rn(dec_e2m1((w[i >> 3] >> (4 * (i & 7))) & 0xFu), sb), s_t);
-    store16<F32OUT, true>(out, e, v, 16, vec);
+  for (int j = 0; j < 4; ++j) {
+    v[2 * j] = __fmul_rn(__fmul_rn(d[j].x, sb), s_t);
+    v[2 * j + 1] = __fmul_rn(__fmul_rn(d[j].y, sb), s_t);
   }
+  if (F32OUT || (finite(sb) && finite(s_t))) store8<F32OUT, VEC, false>(out, e, v);
+  else store8<F32OUT, VEC, true>(out, e, v);
 }
 
-template <bool F32OUT>
+// VEC: 8-byte aligned codes and a 16-byte aligned output.
+template <bool F32OUT, bool VEC>
 __global__ void __launch_bounds__(256) k_dequant_fp8(const uint8_t* __restrict__ q, int64_t n,
-                                                     const float* __restrict__ scale, void* out,
-                                                     bool vec) {
-  const int64_t e = ((int64_t)blockIdx.x * 256 + threadIdx.x) * 16;
-  if (e >= n) return;
-  const int64_t cnt = min((int64_t)16, n - e);
-  uint32_t w[4] = {0u, 0u, 0u, 0u};
-  if (vec && cnt == 16) {
-    const uint4 c = *reinterpret_cast<const uint4*>(q + e);
-    w[0] = c.x; w[1] = c.y; w[2] = c.z; w[3] = c.w;
-  } else {
-#pragma unroll
-    for (int i = 0; i < 16; ++i)
-      if (i < cnt) w[i >> 2] |= (uint32_t)q[e + i] << (8 * (i & 3));
+                                                     const float* __restrict__ scale, void* out) {
+  const int64_t e = ((int64_t)blockIdx.x * 256 + threadIdx.x) * 8;
+  if (VEC && e + 8 <= n) {
+    dequant_e4m3x8<F32OUT>(*reinterpret_cast<const uint2*>(q + e), *scale, out, e);
+    return;
   }
-  dequant_e4m3x16<F32OUT>(w, *scale, out, e, cnt, vec);
+  const int cnt = (int)min((int64_t)8, n - e);  // the last of a tensor, or unaligned
+  const float s = *scale;
+  for (int i = 0; i < cnt; ++i) {
+    const float v = __fmul_rn(dec_e4m3(q[e + i]), s);
+    if (F32OUT) reinterpret_cast<float*>(out)[e + i] = v;
+    else reinterpret_cast<uint16_t*>(out)[e + i] = (uint16_t)f32_to_bf16(v);
+  }
 }
 
-template <bool F32OUT>
+// Two threads per 16-element block (8-byte aligned codes). VEC: a 16-byte
+// aligned output.
+template <bool F32OUT, bool VEC>
 __global__ void __launch_bounds__(256) k_dequant_nvfp4(const uint8_t* __restrict__ q,
-                                                       const uint8_t* __restrict__ bscale,
-                                                       int64_t nblocks,
-                                                       const float* __restrict__ tscale,
-                                                       void* out, bool vec) {
-  const int64_t b = (int64_t)blockIdx.x * 256 + threadIdx.x;
-  if (b >= nblocks) return;
-  const uint2 c = *reinterpret_cast<const uint2*>(q + b * 8);
-  dequant_e2m1x16<F32OUT>(c, dec_e4m3(bscale[b]), *tscale, out, b * 16, vec);
+                                                       const uint8_t* __restrict__ bscale, int64_t n,
+                                                       const float* __restrict__ tscale, void* out) {
+  const int64_t u = (int64_t)blockIdx.x * 256 + threadIdx.x;
+  if (u * 8 >= n) return;
+  dequant_e2m1x8<F32OUT, VEC>(reinterpret_cast<const uint32_t*>(q)[u], dec_e4m3(bscale[u >> 1]), *tscale, out, u * 8);
 }
 
-// MX: two threads per 32-element block (codes aligned to 4 bytes for MXFP4, 8
-// for MXFP8; wide: to a thread's 8 or 16).
+// MX: four threads per 32-element block (codes aligned to a thread's: 4 bytes
+// for MXFP4, 8 for MXFP8).
 template <bool FP4, bool F32OUT>
 __global__ void __launch_bounds__(256) k_dequant_mx(const uint8_t* __restrict__ q, const uint8_t* __restrict__ sc,
-                                                    int64_t n, void* __restrict__ out, bool wide) {
-  const int64_t h = (int64_t)blockIdx.x * 256 + threadIdx.x;
-  if (h * 16 >= n) return;
-  const uint32_t e = sc[h >> 1];
+                                                    int64_t n, void* __restrict__ out) {
+  const int64_t u = (int64_t)blockIdx.x * 256 + threadIdx.x;
+  if (u * 8 >= n) return;
+  const uint32_t e = sc[u >> 2];
   // 2^(e - 127); code 255 is the E8M0 NaN (a block that held inf or NaN)
   const float scale = (e == 0u) ? u2f(0x00400000u) : (e == 255u) ? __builtin_nanf("") : u2f(e << 23);
-  if (FP4) {
-    const uint32_t* w = reinterpret_cast<const uint32_t*>(q) + 2 * h;
-    dequant_e2m1x16<F32OUT>(wide ? *reinterpret_cast<const uint2*>(w) : make_uint2(w[0], w[1]), scale, 1.0f, out, h * 16, true);
-  } else {
-    const uint2* p = reinterpret_cast<const uint2*>(q) + 2 * h;
-    const uint4 c = wide ? *reinterpret_cast<const uint4*>(p) : make_uint4(p[0].x, p[0].y, p[1].x, p[1].y);
-    const uint32_t w[4] = {c.x, c.y, c.z, c.w};
-    dequant_e4m3x16<F32OUT>(w, scale, out, h * 16, 16, true);
-  }
+  if (FP4) dequant_e2m1x8<F32OUT, true>(reinterpret_cast<const uint32_t*>(q)[u], scale, 1.0f, out, u * 8);
+  else dequant_e4m3x8<F32OUT>(reinterpret_cast<const uint2*>(q)[u], scale, out, u * 8);
 }
 
 // ---------------------------------------------------------------- launchers
 static inline unsigned grid_for(int64_t threads) { return (unsigned)((threads + 255) / 256); }
+
+// Elements of one launch of a kernel with eight or more a thread: HIP takes
+// fewer than 2^32 threads. A multiple of every format's block.
+constexpr int64_t kLaunchElements = int64_t(1) << 34;
 
 // Whether the unit kernels take rows of this tensor: 16-byte aligned units,
 // whole ones in every row, and (a slice) unit numbers below 2^31.
@@ -977,32 +971,33 @@ hipError_t launch_quantize(int fmt, const uint16_t* x, int64_t rows, int64_t col
 
 hipError_t launch_dequant(int fmt, const uint8_t* codes, const uint8_t* bscale, const float* tscale,
                           int64_t rows, int64_t cols, void* out, bool f32out, hipStream_t st) {
-  const int64_t n = rows * cols;
-  if (n == 0) return hipSuccess;
-  if (fmt == 3 || fmt == 4) {  // MX: whole blocks, 16-byte aligned output (checked by the caller)
-    const unsigned g = grid_for(n / 16);
-    const bool wide = reinterpret_cast<uintptr_t>(codes) % (fmt == 3 ? 8 : 16) == 0;
-    if (fmt == 3) {
-      if (f32out) hipLaunchKernelGGL((k_dequant_mx<true, true>), dim3(g), dim3(256), 0, st, codes, bscale, n, out, wide);
-      else hipLaunchKernelGGL((k_dequant_mx<true, false>), dim3(g), dim3(256), 0, st, codes, bscale, n, out, wide);
-    } else {
-      if (f32out) hipLaunchKernelGGL((k_dequant_mx<false, true>), dim3(g), dim3(256), 0, st, codes, bscale, n, out, wide);
-      else hipLaunchKernelGGL((k_dequant_mx<false, false>), dim3(g), dim3(256), 0, st, codes, bscale, n, out, wide);
+  if (rows == 0 || cols == 0) return hipSuccess;
+  // at most kLaunchElements a launch (whole blocks)
+  for (int64_t e0 = 0, total = rows * cols; e0 < total; e0 += kLaunchElements) {
+    const int64_t n = std::min(kLaunchElements, total - e0);
+    const uint8_t* q = codes + (fmt == 1 || fmt == 4 ? e0 : e0 / 2);
+    void* o = reinterpret_cast<uint8_t*>(out) + e0 * (f32out ? 4 : 2);
+    const dim3 g(grid_for((n + 7) / 8)), t(256);
+    if (fmt == 3 || fmt == 4) {  // whole blocks, 16-byte aligned output (checked by the caller)
+      const uint8_t* sc = bscale + e0 / 32;
+      if (fmt == 3 && f32out) hipLaunchKernelGGL((k_dequant_mx<true, true>), g, t, 0, st, q, sc, n, o);
+      else if (fmt == 3) hipLaunchKernelGGL((k_dequant_mx<true, false>), g, t, 0, st, q, sc, n, o);
+      else if (f32out) hipLaunchKernelGGL((k_dequant_mx<false, true>), g, t, 0, st, q, sc, n, o);
+      else hipLaunchKernelGGL((k_dequant_mx<false, false>), g, t, 0, st, q, sc, n, o);
+      continue;
     }
-    return hipGetLastError();
-  }
-  if (fmt == 1) {
-    const bool vec = (reinterpret_cast<uintptr_t>(codes) % 16 == 0) &&
-                     (reinterpret_cast<uintptr_t>(out) % 16 == 0);
-    const unsigned g = grid_for((n + 15) / 16);
-    if (f32out) hipLaunchKernelGGL(k_dequant_fp8<true>, dim3(g), dim3(256), 0, st, codes, n, tscale, out, vec);
-    else hipLaunchKernelGGL(k_dequant_fp8<false>, dim3(g), dim3(256), 0, st, codes, n, tscale, out, vec);
-  } else {
-    const int64_t nb = n / 16;
-    const unsigned g = grid_for(nb);
-    const bool vec = (reinterpret_cast<uintptr_t>(out) % 16 == 0);
-    if (f32out) hipLaunchKernelGGL(k_dequant_nvfp4<true>, dim3(g), dim3(256), 0, st, codes, bscale, nb, tscale, out, vec);
-    else hipLaunchKernelGGL(k_dequant_nvfp4<false>, dim3(g), dim3(256), 0, st, codes, bscale, nb, tscale, out, vec);
+    const bool vec = reinterpret_cast<uintptr_t>(out) % 16 == 0 && reinterpret_cast<uintptr_t>(codes) % 8 == 0;
+    const uint8_t* sc = bscale + e0 / 16;  // NVFP4
+#define QG_DEQUANT(F32, VEC)                                                                                      \
+  do {                                                                                                            \
+    if (fmt == 1) hipLaunchKernelGGL((k_dequant_fp8<F32, VEC>), g, t, 0, st, q, n, tscale, o);                    \
+    else hipLaunchKernelGGL((k_dequant_nvfp4<F32, VEC>), g, t, 0, st, q, sc, n, tscale, o);                       \
+  } while (0)
+    if (f32out && vec) QG_DEQUANT(true, true);
+    else if (f32out) QG_DEQUANT(true, false);
+    else if (vec) QG_DEQUANT(false, true);
+    else QG_DEQUANT(false, false);
+#undef QG_DEQUANT
   }
   return hipGetLastError();
 }

@@ -27,8 +27,8 @@ def kernels(tmp_path_factory):
             found[name] = []
         elif name and line.startswith("\t") and not line.startswith("\t."):
             found[name].append(line.strip())
-            if line.strip().startswith("s_endpgm"):
-                name = None
+        elif line.startswith(".Lfunc_end"):
+            name = None
     return found
 
 
@@ -39,3 +39,17 @@ def test_mx_rows_of_any_alignment_load_a_unit_at_once(kernels):
     for name, code in mine.items():
         loads = [i.split()[0] for i in code if i.startswith("global_load")]
         assert loads == ["global_load_dwordx4"], (name, loads)
+
+
+def test_dequantizers_store_adjacent_runs(kernels):
+    # an aligned output: a lane writes 8 elements, so one 16-byte store of bf16, two adjacent ones of fp32 (more
+    # elements a lane leave gaps between the lanes' pieces that no store of the same instruction fills)
+    wide = {n: k for n, k in kernels.items() if re.search(r"k_dequant_(mxILb[01]ELb([01])E|(fp8|nvfp4)ILb([01])ELb1E)", n)}
+    assert len(wide) == 8
+    for name, code in wide.items():
+        f32 = bool(re.search(r"k_dequant_(mxILb[01]ELb1E|(fp8|nvfp4)ILb1ELb1E)", name))
+        stores = [i for i in code if i.startswith("global_store_dwordx4")]
+        offsets = {int(m.group(1)) if (m := re.search(r"offset:(\d+)", i)) else 0 for i in stores}
+        assert offsets == ({0, 16} if f32 else {0}), (name, stores)
+        if "k_dequant_fp8" not in name:  # (FP8 tensors may end in single elements)
+            assert len(stores) == len([i for i in code if i.startswith("global_store")]), name
