@@ -389,6 +389,9 @@ __device__ inline void code_units8_nv_pair(const uint4 (&raw)[2], const int64_t 
 // 512 x 3072 2.7 -> 2.4, NVFP4 8.1 -> 7.3; chain 14.3 -> 14.0, 14.6 -> 14.2.
 // PLAIN: whole blocks and 16-byte aligned codes (NVFP4 always); behind run-time
 // branches in one kernel the FP8 case lost half of that (7.4 -> 8.2 us).
+// Otherwise whole 8-element units in 8-byte stores and the last 1 to 7 elements of
+// a dense tensor one by one (the whole last block element by element, in a loop,
+// held its wave up: static 1 x 1032 3.4 us, now 2.8; 63 x 1000 3.7, now 3.0).
 template <int FMT, int H, bool DENSE, bool PLAIN>
 __global__ void __launch_bounds__(256) k_quant_units(const uint16_t* __restrict__ x, int64_t n, UnitRows rows,
                                                      uint8_t* __restrict__ q, uint8_t* __restrict__ bscale,
@@ -414,16 +417,24 @@ __global__ void __launch_bounds__(256) k_quant_units(const uint16_t* __restrict_
       bscale[b] = (uint8_t)quant_nvfp4_words(w[h], q + 8 * b, s);
       continue;
     }
+    uint32_t c[4];
+    fp8_words(w[h], c, r);
     if (PLAIN) {
-      quant_fp8_words(w[h], 16, q + 16 * b, r, true);
-    } else if (left >= 16) {
-      uint32_t c[4];
-      fp8_words(w[h], c, r);
-      reinterpret_cast<uint2*>(q + 16 * b)[0] = make_uint2(c[0], c[1]);
-      reinterpret_cast<uint2*>(q + 16 * b)[1] = make_uint2(c[2], c[3]);
-    } else {  // the last block; a dense tensor's may hold part of a unit
-      if (DENSE) unit_load<false>(x + 16 * b, left, w[h]);
-      quant_fp8_words(w[h], left, q + 16 * b, r, false);
+      *reinterpret_cast<uint4*>(q + 16 * b) = make_uint4(c[0], c[1], c[2], c[3]);
+      continue;
+    }
+    if (left >= 8) reinterpret_cast<uint2*>(q + 16 * b)[0] = make_uint2(c[0], c[1]);
+    if (left >= 16) reinterpret_cast<uint2*>(q + 16 * b)[1] = make_uint2(c[2], c[3]);
+    if (DENSE && left < 16 && (left & 7) != 0) {  // the tensor ends in part of a unit
+      const int64_t e = 16 * b + (left & 8);
+      const int cnt = (int)(left & 7);
+      float y[8];
+#pragma unroll
+      for (int j = 0; j < 8; ++j) y[j] = (j < cnt) ? __fmul_rn(u2f((uint32_t)x[e + j] << 16), r) : 0.0f;
+      const uint32_t t[2] = {hw_e4m3x4(y), hw_e4m3x4(y + 4)};
+#pragma unroll
+      for (int j = 0; j < 7; ++j)
+        if (j < cnt) q[e + j] = (uint8_t)(t[j >> 2] >> (8 * (j & 3)));
     }
   }
 }

@@ -53,3 +53,16 @@ def test_dequantizers_store_adjacent_runs(kernels):
         assert offsets == ({0, 16} if f32 else {0}), (name, stores)
         if "k_dequant_fp8" not in name:  # (FP8 tensors may end in single elements)
             assert len(stores) == len([i for i in code if i.startswith("global_store")]), name
+
+
+def test_fp8_tensors_that_end_in_part_of_a_block(kernels):
+    # codes without 16-byte alignment, or rows times columns no multiple of 16: whole 8-element units in 8-byte stores;
+    # only the last 1 to 7 elements of a dense tensor one by one (a slice's rows are whole units)
+    for h in (1, 2):
+        code = {}
+        for dense in (0, 1):
+            (code[dense],) = [k for n, k in kernels.items() if "13k_quant_unitsILi1ELi%dELb%dELb0E" % (h, dense) in n]
+            ops = [i.split()[0] for i in code[dense]]
+            assert ops.count("global_store_dwordx2") == 2 * h, (h, dense)
+            single = [sum(o.startswith(p) for o in ops) for p in ("global_load_ushort", "global_store_byte")]
+            assert single == ([7 * h, 7 * h] if dense else [0, 0]), (h, dense, single)
