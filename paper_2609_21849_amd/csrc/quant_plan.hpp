@@ -1,8 +1,8 @@
 // quant_plan.hpp -- what host and device share of the quantizers' (quantize.hip)
 // addressing, checked by host-only tests over many sizes: the launch plan of
 // the two-launch dynamic quantizer (how many amax workgroups P leave their
-// maxima, into how many code regions G, and where region j begins), and the
-// rows of a column slice read in 16-byte units.
+// maxima, into how many code regions G, and where region j begins), the rows
+// of a column slice read in 16-byte units, and the pieces of very large tensors.
 #pragma once
 
 #include <hip/hip_runtime.h>
@@ -67,6 +67,25 @@ inline UnitRows unit_rows(int64_t cols, int64_t ldx) {  // cols % 8 == 0, ldx % 
   while ((int64_t(1) << (r.shift - 32)) < (int64_t)r.upr) ++r.shift;
   r.mul = ((uint64_t(1) << r.shift) + r.upr - 1) / r.upr;
   return r;
+}
+
+// A launch takes at most this many elements, eight or more a thread: from 2^32
+// threads on HIP launches only what is left of their number modulo 2^32 and
+// reports success (static FP8 of 2^36 elements and more left its codes unwritten),
+// and the units of a slice must number 2^31 at most. A multiple of every format's
+// block.
+constexpr int64_t kLaunchElements = int64_t(1) << 34;
+
+// fn(offset in x, offset in the dense codes, elements) for the pieces of a tensor
+// of rows `ldx` apart: runs of a dense tensor, whole rows of a slice.
+template <class F>
+inline void for_pieces(int64_t rows, int64_t cols, int64_t ldx, F fn) {
+  if (ldx == cols) {
+    for (int64_t e = 0, n = rows * cols; e < n; e += kLaunchElements) fn(e, e, std::min(kLaunchElements, n - e));
+    return;
+  }
+  const int64_t step = kLaunchElements / cols;
+  for (int64_t r = 0; r < rows; r += step) fn(r * ldx, r * cols, std::min(step, rows - r) * cols);
 }
 
 }  // namespace qg

@@ -813,15 +813,11 @@ __global__ void __launch_bounds__(256) k_dequant_mx(const uint8_t* __restrict__ 
 // ---------------------------------------------------------------- launchers
 static inline unsigned grid_for(int64_t threads) { return (unsigned)((threads + 255) / 256); }
 
-// Elements of one launch of a kernel with eight or more a thread: HIP takes
-// fewer than 2^32 threads. A multiple of every format's block.
-constexpr int64_t kLaunchElements = int64_t(1) << 34;
-
 // Whether the unit kernels take rows of this tensor: 16-byte aligned units,
-// whole ones in every row, and (a slice) unit numbers below 2^31.
-static inline bool unit_tensor(const uint16_t* x, int64_t rows, int64_t cols, int64_t ldx) {
+// whole ones in every row of a slice.
+static inline bool unit_tensor(const uint16_t* x, int64_t cols, int64_t ldx) {
   if (reinterpret_cast<uintptr_t>(x) % 16 != 0) return false;
-  return ldx == cols || (ldx % 8 == 0 && cols % 8 == 0 && rows <= (int64_t(1) << 31) / (cols / 8));
+  return ldx == cols || (ldx % 8 == 0 && cols % 8 == 0);
 }
 
 template <int H, bool DENSE>
@@ -844,21 +840,28 @@ static hipError_t launch_elements(int fmt, const uint16_t* x, int64_t rows, int6
                                   uint8_t* bscale, const float* tscale, bool chained, hipStream_t st) {
   if (rows == 0 || cols == 0) return hipSuccess;
   const bool contig = (ldx == cols);
-  const int64_t n = rows * cols;
-  if (unit_tensor(x, rows, cols, ldx) && reinterpret_cast<uintptr_t>(codes) % 8 == 0) {
+  if (unit_tensor(x, cols, ldx) && reinterpret_cast<uintptr_t>(codes) % 8 == 0) {
     const UnitRows ur = contig ? UnitRows() : unit_rows(cols, ldx);
-    if (contig && chained) launch_units<2, true>(fmt, x, n, ur, codes, bscale, tscale, st);
-    else if (contig) launch_units<1, true>(fmt, x, n, ur, codes, bscale, tscale, st);
-    else if (chained) launch_units<2, false>(fmt, x, n, ur, codes, bscale, tscale, st);
-    else launch_units<1, false>(fmt, x, n, ur, codes, bscale, tscale, st);
-  } else if (fmt == 1) {
-    const unsigned g = grid_for(contig ? (n + 15) / 16 : rows * ((cols + 15) / 16));
-    if (contig) hipLaunchKernelGGL((k_quant_fp8<true>), dim3(g), dim3(256), 0, st, x, rows, cols, ldx, codes, tscale);
-    else hipLaunchKernelGGL((k_quant_fp8<false>), dim3(g), dim3(256), 0, st, x, rows, cols, ldx, codes, tscale);
+    for_pieces(rows, cols, ldx, [&](int64_t src, int64_t e, int64_t cnt) {
+      uint8_t* q = codes + (fmt == 1 ? e : e / 2);
+      uint8_t* sc = fmt == 1 ? nullptr : bscale + e / 16;
+      if (contig && chained) launch_units<2, true>(fmt, x + src, cnt, ur, q, sc, tscale, st);
+      else if (contig) launch_units<1, true>(fmt, x + src, cnt, ur, q, sc, tscale, st);
+      else if (chained) launch_units<2, false>(fmt, x + src, cnt, ur, q, sc, tscale, st);
+      else launch_units<1, false>(fmt, x + src, cnt, ur, q, sc, tscale, st);
+    });
   } else {
-    const unsigned g = grid_for(rows * (cols / 16));
-    if (contig) hipLaunchKernelGGL((k_quant_nvfp4<true>), dim3(g), dim3(256), 0, st, x, rows, cols, ldx, codes, bscale, tscale);
-    else hipLaunchKernelGGL((k_quant_nvfp4<false>), dim3(g), dim3(256), 0, st, x, rows, cols, ldx, codes, bscale, tscale);
+    for_pieces(rows, cols, ldx, [&](int64_t src, int64_t e, int64_t cnt) {
+      const int64_t r = contig ? 1 : cnt / cols, c = contig ? cnt : cols;
+      const dim3 g(grid_for(r * ((c + 15) / 16))), t(256);
+      const uint16_t* p = x + src;
+      uint8_t* q = codes + (fmt == 1 ? e : e / 2);
+      uint8_t* sc = fmt == 1 ? nullptr : bscale + e / 16;
+      if (fmt == 1 && contig) hipLaunchKernelGGL((k_quant_fp8<true>), g, t, 0, st, p, r, c, c, q, tscale);
+      else if (fmt == 1) hipLaunchKernelGGL((k_quant_fp8<false>), g, t, 0, st, p, r, c, ldx, q, tscale);
+      else if (contig) hipLaunchKernelGGL((k_quant_nvfp4<true>), g, t, 0, st, p, r, c, c, q, sc, tscale);
+      else hipLaunchKernelGGL((k_quant_nvfp4<false>), g, t, 0, st, p, r, c, ldx, q, sc, tscale);
+    });
   }
   return hipGetLastError();
 }
@@ -873,24 +876,31 @@ template <bool FP4>
 static hipError_t launch_quantize_mx(const uint16_t* x, int64_t rows, int64_t cols, int64_t ldx,
                                      uint8_t* codes, uint8_t* scales, hipStream_t st) {
   if (rows == 0 || cols == 0) return hipSuccess;
-  const int64_t units = rows * (cols / 8);
-  if (!unit_tensor(x, rows, cols, ldx)) {
-    hipLaunchKernelGGL((k_quant_mx<FP4>), dim3(grid_for(units)), dim3(256), 0, st, x, rows, cols, ldx, codes, scales);
+  if (!unit_tensor(x, cols, ldx)) {
+    for_pieces(rows, cols, ldx, [&](int64_t src, int64_t e, int64_t cnt) {
+      const int64_t c = ldx == cols ? cnt : cols;
+      hipLaunchKernelGGL((k_quant_mx<FP4>), dim3(grid_for(cnt / 8)), dim3(256), 0, st, x + src, cnt / c, c,
+                         ldx == cols ? c : ldx, codes + (FP4 ? e / 2 : e), scales + e / 32);
+    });
     return hipGetLastError();
   }
   constexpr int H = 1;
   const bool plain = reinterpret_cast<uintptr_t>(codes) % (FP4 ? 8 : 16) == 0;
-  const int64_t halves = units / 2;
-  const dim3 g((unsigned)((halves + 256 * H - 1) / (256 * H)));
-  if (ldx == cols) {
-    const UnitRows ur;
-    if (plain) hipLaunchKernelGGL((k_quant_mx_units<FP4, H, true, true>), g, dim3(256), 0, st, x, halves, ur, codes, scales);
-    else hipLaunchKernelGGL((k_quant_mx_units<FP4, H, true, false>), g, dim3(256), 0, st, x, halves, ur, codes, scales);
-  } else {
-    const UnitRows ur = unit_rows(cols, ldx);
-    if (plain) hipLaunchKernelGGL((k_quant_mx_units<FP4, H, false, true>), g, dim3(256), 0, st, x, halves, ur, codes, scales);
-    else hipLaunchKernelGGL((k_quant_mx_units<FP4, H, false, false>), g, dim3(256), 0, st, x, halves, ur, codes, scales);
-  }
+  const UnitRows ur = ldx == cols ? UnitRows() : unit_rows(cols, ldx);
+  for_pieces(rows, cols, ldx, [&](int64_t src, int64_t e, int64_t cnt) {
+    const int64_t halves = cnt / 16;
+    const dim3 g((unsigned)((halves + 256 * H - 1) / (256 * H))), t(256);
+    const uint16_t* p = x + src;
+    uint8_t* q = codes + (FP4 ? e / 2 : e);
+    uint8_t* sc = scales + e / 32;
+    if (ldx == cols) {
+      if (plain) hipLaunchKernelGGL((k_quant_mx_units<FP4, H, true, true>), g, t, 0, st, p, halves, ur, q, sc);
+      else hipLaunchKernelGGL((k_quant_mx_units<FP4, H, true, false>), g, t, 0, st, p, halves, ur, q, sc);
+    } else {
+      if (plain) hipLaunchKernelGGL((k_quant_mx_units<FP4, H, false, true>), g, t, 0, st, p, halves, ur, q, sc);
+      else hipLaunchKernelGGL((k_quant_mx_units<FP4, H, false, false>), g, t, 0, st, p, halves, ur, q, sc);
+    }
+  });
   return hipGetLastError();
 }
 
@@ -935,7 +945,7 @@ hipError_t launch_quantize(int fmt, const uint16_t* x, int64_t rows, int64_t col
     return hipGetLastError();
   }
   const int64_t n = rows * cols;
-  const bool unit = unit_tensor(x, rows, cols, ldx);
+  const bool unit = unit_tensor(x, cols, ldx);
   const UnitRows ur = (unit && !contig) ? unit_rows(cols, ldx) : UnitRows();
   if (unit && reinterpret_cast<uintptr_t>(codes) % 8 == 0) {
     // two launches, the maxima handed over in every code region
@@ -953,15 +963,19 @@ hipError_t launch_quantize(int fmt, const uint16_t* x, int64_t rows, int64_t col
   }
   // amax: per-workgroup partial maxima are parked in the code buffer, which
   // the quantize kernel overwrites afterwards (stream order separates them).
-  // More than kSmallUnits units: the codes hold kAmaxGroups partials.
+  // More than kSmallUnits units: the codes hold a partial per 1024 16-byte units.
   {
     const uintptr_t base = (reinterpret_cast<uintptr_t>(codes) + 3) & ~uintptr_t(3);
     uint32_t* partial = reinterpret_cast<uint32_t*>(base);
-    int64_t gx, gy = 1;
+    int64_t gx = 0, gy = 1;
     if (unit && n % 8 == 0) {
-      gx = std::min<int64_t>((n / 8 + 1023) / 1024, kAmaxGroups);
-      if (contig) hipLaunchKernelGGL(k_amax_units<true>, dim3((unsigned)gx), dim3(256), 0, st, x, n / 8, ur, partial);
-      else hipLaunchKernelGGL(k_amax_units<false>, dim3((unsigned)gx), dim3(256), 0, st, x, n / 8, ur, partial);
+      for_pieces(rows, cols, ldx, [&](int64_t src, int64_t, int64_t cnt) {
+        const int64_t groups = std::min<int64_t>((cnt / 8 + 1023) / 1024, kAmaxGroups);
+        const dim3 g((unsigned)groups), t(256);
+        if (contig) hipLaunchKernelGGL(k_amax_units<true>, g, t, 0, st, x + src, cnt / 8, ur, partial + gx);
+        else hipLaunchKernelGGL(k_amax_units<false>, g, t, 0, st, x + src, cnt / 8, ur, partial + gx);
+        gx += groups;
+      });
     } else {
       const int64_t r_eff = contig ? 1 : rows, c_eff = contig ? n : cols;
       gy = std::min<int64_t>(r_eff, 1024);
@@ -983,9 +997,7 @@ hipError_t launch_quantize(int fmt, const uint16_t* x, int64_t rows, int64_t col
 hipError_t launch_dequant(int fmt, const uint8_t* codes, const uint8_t* bscale, const float* tscale,
                           int64_t rows, int64_t cols, void* out, bool f32out, hipStream_t st) {
   if (rows == 0 || cols == 0) return hipSuccess;
-  // at most kLaunchElements a launch (whole blocks)
-  for (int64_t e0 = 0, total = rows * cols; e0 < total; e0 += kLaunchElements) {
-    const int64_t n = std::min(kLaunchElements, total - e0);
+  for_pieces(rows, cols, cols, [&](int64_t, int64_t e0, int64_t n) {
     const uint8_t* q = codes + (fmt == 1 || fmt == 4 ? e0 : e0 / 2);
     void* o = reinterpret_cast<uint8_t*>(out) + e0 * (f32out ? 4 : 2);
     const dim3 g(grid_for((n + 7) / 8)), t(256);
@@ -995,7 +1007,7 @@ hipError_t launch_dequant(int fmt, const uint8_t* codes, const uint8_t* bscale, 
       else if (fmt == 3) hipLaunchKernelGGL((k_dequant_mx<true, false>), g, t, 0, st, q, sc, n, o);
       else if (f32out) hipLaunchKernelGGL((k_dequant_mx<false, true>), g, t, 0, st, q, sc, n, o);
       else hipLaunchKernelGGL((k_dequant_mx<false, false>), g, t, 0, st, q, sc, n, o);
-      continue;
+      return;
     }
     const bool vec = reinterpret_cast<uintptr_t>(out) % 16 == 0 && reinterpret_cast<uintptr_t>(codes) % 8 == 0;
     const uint8_t* sc = bscale + e0 / 16;  // NVFP4
@@ -1009,7 +1021,7 @@ hipError_t launch_dequant(int fmt, const uint8_t* codes, const uint8_t* bscale, 
     else if (vec) QG_DEQUANT(false, true);
     else QG_DEQUANT(false, false);
 #undef QG_DEQUANT
-  }
+  });
   return hipGetLastError();
 }
 
