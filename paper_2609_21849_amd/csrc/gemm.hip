@@ -3226,40 +3226,15 @@ hipError_t launch_gemm(int a_fmt, const void* a, const uint8_t* a_bscale, const 
       else hipLaunchKernelGGL((k_w4a16_stream<3, 8, 12>), dim3(grid), dim3(768), (size_t)xbytes, st, g);
       return hipGetLastError();
     }
-    // Past the ridge point with enough large tiles: the persistent W4A4-shaped
-    // kernel. From 21/32 of a round of 128 x 256 tiles (split-K against 128-row
-    // tiles, back to back: 500 x 9216 x 3072, 144 tiles, 50.5 / 53.6 us; 1280 x 4096 x 4096,
-    // 160, 66.1 / 69.2; 3500 x 1536 x 3072, 168, 57.6 / 53.0), or 3/8 of one of 256 x 256.
-    // Heights (256 rows -> chosen): 1024 x 6144 x 3072 68.4 -> 54.0 us (128), 2304 x 9216 x
-    // 3072 146.7 -> 128.8 (192), 1900 x 3072 x 1024 28.3 -> 21.3 (128).
-    const int64_t t256_n = (n + 255) / 256, cus = device_cus();
-    if (m > 128 && (8 * ((m + 255) / 256 * t256_n) >= 3 * cus || 32 * ((m + 127) / 128 * t256_n) >= 21 * cus))
-      return launch_large<MODE_W4A16>(g, cus, st);
-    // Split-K tilings. Up to 32 rows: one-panel workgroups, all chunks of a wave
-    // in one batch of loads only where that is one (1 x 3072 x 1024 4.4 -> 3.9 us
-    // with a chunk at a time; at K > 3072 that loses, 32 x 2048 x 6144 15.6 ->
-    // 17.3). Else the narrowest 32-row tile that gives every workgroup a CU of
-    // its own; past that 64-row tiles, which expand each weight once for two
-    // row blocks (the expansion is the bound there): 64 x 96 where those make
-    // one round that 64 x 64 tiles would overflow. 32 x 64 tiles of four waves,
-    // several workgroups per CU, stay for short reductions (256 x 3072 x 1024
-    // 8.5 us against 8.9) and where 64-row tiles would pad the rows by more than an
-    // eighth (200 x 9216 x 3072 30.3 against 34.0). Measured (GPU time from graph
-    // replays, 24 shapes, 21 tilings) against the earlier rule by M and N, with
-    // the 128 x 256 tile kernel it used past M = 1024: 64 x 3072 x 3072 10.9 -> 7.4
-    // us, 512 x 3072 x 3072 25.6 -> 21.2, 1024 x 3072 x 3072 47 -> 36, 2048 x 1024 x
-    // 3072 73 -> 27, 1148 x 352 x 2304 57 -> 11, 1446 x 1984 x 6016 140 -> 63.
-    const int64_t rows32 = (m + 31) / 32, rows64 = (m + 63) / 64, npan = (n + 31) / 32;
-    const int64_t t12 = rows32 * ((npan + 1) / 2), t22 = rows64 * ((npan + 1) / 2), t23 = rows64 * ((npan + 2) / 3);
-    if (m <= 32) {
-      if (k <= 3072) return run_w4a16_splitk<1, 1, 8, 1, false>(g, st);
-      return run_w4a16_splitk<1, 1, 8, 3, false>(g, st);
-    }
-    if (rows32 * npan <= cus) return run_w4a16_splitk<1, 1, 8, 3, true>(g, st);
-    if (k <= 1024 && t12 <= 2 * cus) return run_w4a16_splitk<1, 2, 4, 3, true>(g, st);
-    if (t12 <= cus) return run_w4a16_splitk<1, 2, 8, 3, true>(g, st);
-    if (16 * rows64 > 9 * rows32) return run_w4a16_splitk<1, 2, 4, 3, true>(g, st);
-    if (t22 > cus && t23 <= cus) return run_w4a16_splitk<2, 3, 4, 1, true>(g, st);
+    const int64_t cus = device_cus();
+    const SplitK p = plan_w4a16(m, n, k, cus);
+    if (p == SplitK{}) return launch_large<MODE_W4A16>(g, cus, st);
+    if (p == SplitK{1, 1, 8, 1}) return run_w4a16_splitk<1, 1, 8, 1, false>(g, st);
+    if (p == SplitK{1, 1, 8, 3} && m <= 32) return run_w4a16_splitk<1, 1, 8, 3, false>(g, st);
+    if (p == SplitK{1, 1, 8, 3}) return run_w4a16_splitk<1, 1, 8, 3, true>(g, st);
+    if (p == SplitK{1, 2, 4, 3}) return run_w4a16_splitk<1, 2, 4, 3, true>(g, st);
+    if (p == SplitK{1, 2, 8, 3}) return run_w4a16_splitk<1, 2, 8, 3, true>(g, st);
+    if (p == SplitK{2, 3, 4, 1}) return run_w4a16_splitk<2, 3, 4, 1, true>(g, st);
     return run_w4a16_splitk<2, 2, 4, 1, true>(g, st);
   }
 }

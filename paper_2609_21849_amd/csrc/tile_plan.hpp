@@ -1,5 +1,5 @@
-// tile_plan.hpp -- how the GEMMs (gemm.hip) cut the rows of the output into
-// tiles and in which order they take them, checked over many sizes without a GPU.
+// tile_plan.hpp -- how the GEMMs (gemm.hip) cut the output into tiles, in which
+// order they take them and where they share K instead, checked without a GPU.
 #pragma once
 
 #include <hip/hip_runtime.h>
@@ -48,6 +48,49 @@ inline TileRows plan_tile_rows(int64_t m, int64_t tiles_n, int64_t cus, RoundCos
     if (best.tm == 0 || c < best.cost) best = {tm, c};
   }
   return best;
+}
+
+// A tiling of a split-K kernel: tiles of 32 mt x 32 np outputs, nw waves sharing
+// the reduction, each with d 128-wide chunks in flight. {}: not a split-K kernel.
+struct SplitK {
+  int mt = 0, np = 0, nw = 0, d = 0;
+  constexpr bool operator==(const SplitK& o) const { return mt == o.mt && np == o.np && nw == o.nw && d == o.d; }
+};
+
+// W4A16 beside the two weight-pool kernels. {}: the persistent kernel, past the
+// ridge point with enough large tiles: from 21/32 of a round of 128 x 256 tiles
+// (split-K against 128-row tiles, back to back: 500 x 9216 x 3072, 144 tiles, 50.5 / 53.6
+// us; 1280 x 4096 x 4096, 160, 66.1 / 69.2; 3500 x 1536 x 3072, 168, 57.6 / 53.0), or 3/8 of
+// one of 256 x 256. Heights (256 rows -> chosen): 1024 x 6144 x 3072 68.4 -> 54.0 us (128),
+// 2304 x 9216 x 3072 146.7 -> 128.8 (192), 1900 x 3072 x 1024 28.3 -> 21.3 (128).
+// Split-K tilings. Up to 32 rows: one-panel workgroups, at K > 3072 with three
+// chunks of a wave in one batch of loads, else one at a time where the workgroups
+// all run at once or read few activations: 1 x 3072 x 1024 4.4 -> 3.9 us, 24 x 9216 x
+// 3072 13.2 -> 12.9, 24 x 90880 x 1024 30.9 -> 29.1; where more follow each other the
+// batch keeps more in flight (17 x 363520 x 3072 224 us against 308, 30 x 52944 x 2304
+// 37.7 against 46.0, 16 x 18432 x 3072 16.0 against 16.9, 32 x 9216 x 3072 15.3 against
+// 16.1; 32 x 2048 x 6144 15.6 against 17.3). Above 32 rows the narrowest 32-row tile
+// that gives every workgroup a CU of its own; past that 64-row tiles, which expand
+// each weight once for two row blocks (the expansion is the bound there): 64 x 96
+// where those make one round that 64 x 64 tiles would overflow. 32 x 64 tiles of
+// four waves, several workgroups per CU, stay for short reductions (256 x 3072 x
+// 1024 8.5 us against 8.9) and where 64-row tiles would pad the rows by more than
+// an eighth (200 x 9216 x 3072 30.3 against 34.0). Measured (GPU time from graph
+// replays, 24 shapes, 21 tilings) against a rule by M and N: 64 x 3072 x 3072 10.9 ->
+// 7.4 us, 512 x 3072 x 3072 25.6 -> 21.2, 1024 x 3072 x 3072 47 -> 36, 2048 x 1024 x 3072
+// 73 -> 27, 1148 x 352 x 2304 57 -> 11, 1446 x 1984 x 6016 140 -> 63.
+inline SplitK plan_w4a16(int64_t m, int64_t n, int64_t k, int64_t cus) {
+  const int64_t rows32 = (m + 31) / 32, rows64 = (m + 63) / 64, npan = (n + 31) / 32;
+  const int64_t tiles256 = (m + 255) / 256 * ((n + 255) / 256), tiles128 = (m + 127) / 128 * ((n + 255) / 256);
+  if (m > 128 && (8 * tiles256 >= 3 * cus || 32 * tiles128 >= 21 * cus)) return {};
+  const int64_t t12 = rows32 * ((npan + 1) / 2), t22 = rows64 * ((npan + 1) / 2), t23 = rows64 * ((npan + 2) / 3);
+  if (m <= 32) return {1, 1, 8, k <= 3072 && (npan <= cus || m * k <= (npan <= 2 * cus ? 72 : 24) * 1024) ? 1 : 3};
+  if (rows32 * npan <= cus) return {1, 1, 8, 3};
+  if (k <= 1024 && t12 <= 2 * cus) return {1, 2, 4, 3};
+  if (t12 <= cus) return {1, 2, 8, 3};
+  if (16 * rows64 > 9 * rows32) return {1, 2, 4, 3};
+  if (t22 > cus && t23 <= cus) return {2, 3, 4, 1};
+  return {2, 2, 4, 1};
 }
 
 }  // namespace qg
