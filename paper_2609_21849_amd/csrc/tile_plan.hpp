@@ -61,7 +61,10 @@ struct SplitK {
 // ridge point with enough large tiles: from 21/32 of a round of 128 x 256 tiles
 // (split-K against 128-row tiles, back to back: 500 x 9216 x 3072, 144 tiles, 50.5 / 53.6
 // us; 1280 x 4096 x 4096, 160, 66.1 / 69.2; 3500 x 1536 x 3072, 168, 57.6 / 53.0), or 3/8 of
-// one of 256 x 256. Heights (256 rows -> chosen): 1024 x 6144 x 3072 68.4 -> 54.0 us (128),
+// one of 256 x 256; up to K = 512, where the split's reduction is most of its
+// time, from 5/16 of a round of the former (7674 x 432 x 256, 120 tiles, 14.6 / 9.9; 1117
+// x 2112 x 384, 81, 12.4 / 11.3; 1643 x 1392 x 512, 78, 13.2 / 13.0; 1523 x 976 x 384, 48, 9.2 /
+// 11.2). Heights (256 rows -> chosen): 1024 x 6144 x 3072 68.4 -> 54.0 us (128),
 // 2304 x 9216 x 3072 146.7 -> 128.8 (192), 1900 x 3072 x 1024 28.3 -> 21.3 (128).
 // Split-K tilings. Up to 32 rows: one-panel workgroups, at K > 3072 with three
 // chunks of a wave in one batch of loads, else one at a time where the workgroups
@@ -82,7 +85,7 @@ struct SplitK {
 inline SplitK plan_w4a16(int64_t m, int64_t n, int64_t k, int64_t cus) {
   const int64_t rows32 = (m + 31) / 32, rows64 = (m + 63) / 64, npan = (n + 31) / 32;
   const int64_t tiles256 = (m + 255) / 256 * ((n + 255) / 256), tiles128 = (m + 127) / 128 * ((n + 255) / 256);
-  if (m > 128 && (8 * tiles256 >= 3 * cus || 32 * tiles128 >= 21 * cus)) return {};
+  if (m > 128 && (8 * tiles256 >= 3 * cus || 32 * tiles128 >= 21 * cus || (k <= 512 && 16 * tiles128 >= 5 * cus))) return {};
   const int64_t t12 = rows32 * ((npan + 1) / 2), t22 = rows64 * ((npan + 1) / 2), t23 = rows64 * ((npan + 2) / 3);
   if (m <= 32) return {1, 1, 8, k <= 3072 && (npan <= cus || m * k <= (npan <= 2 * cus ? 72 : 24) * 1024) ? 1 : 3};
   if (rows32 * npan <= cus) return {1, 1, 8, 3};
