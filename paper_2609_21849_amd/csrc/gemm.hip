@@ -3167,37 +3167,15 @@ hipError_t launch_gemm(int a_fmt, const void* a, const uint8_t* a_bscale, const 
     }
     return launch_large<MODE_FP8>(g, cus, st);
   } else if (a_fmt == 2) {
-    g.tiles_m = (g.m + 255) / 256;
-    g.tiles_n = (g.n + 255) / 256;
-    const int tiles = g.tiles_m * g.tiles_n;
-    // Below half a round of 256 x 256 tiles and 11/16 of a round of 128 x 256
-    // ones the split-K kernel is faster (back to back, split-K against 128-row
-    // tiles: 500 x 9216 x 3072, 144 tiles, 35.7 / 37.2 us; 1280 x 4096 x 4096, 160, 46.9 /
-    // 48.3; 640 x 9216 x 3072, 180, 42.6 / 38.4; 1900 x 3072 x 1024, 180, 21.3 / 16.8; 1024 x
-    // 6144 x 3072, 192, 44.3 / 40.1; 2300 x 3072 x 9216, 216, 164 / 113). The
-    // narrowest tile that gives every workgroup a CU of its own; past that 64 x
-    // 64 tiles of four waves, two workgroups per CU, so that one's reduction
-    // runs beside the other's loop. Measured (GPU time from graph replays,
-    // 24 shapes, 12 tilings: the best or within 3% of it everywhere) against
-    // the earlier 32 x 64 / 64 x 64 / 64 x 96 rule: 1 x 3072 x 1024 5.1 -> 3.8 us, 64 x
-    // 3072 x 3072 8.0 -> 5.8, 300 x 1024 x 3072 8.1 -> 6.9, 151 x 3520 x 5504 21.6 ->
-    // 14.8, 2048 x 1024 x 3072 25.0 -> 20.3, 1555 x 4512 x 3968 80 -> 69; 512 x 3072 x
-    // 3072 (64 x 96, one round) as before.
-    const int64_t tiles128 = (m + 127) / 128 * g.tiles_n;
-    if (m <= 128 || (2 * tiles < cus && 16 * tiles128 < 11 * cus)) {
-      const int64_t rows32 = (m + 31) / 32, rows64 = (m + 63) / 64;
-      if (rows32 * ((n + 31) / 32) <= cus) {
-        if ((k >> 7) >= 32) return run_splitk<MODE_NVFP4, 1, 1, 8, 1>(g, st);  // 44 x 352 x 7296 8.8 -> 8.2 us
-        return run_splitk<MODE_NVFP4, 1, 1, 4, 2>(g, st);
-      }
-      if (rows32 * ((n + 63) / 64) <= cus) {
-        if ((k >> 7) >= 32) return run_splitk<MODE_NVFP4, 1, 2, 8, 3>(g, st);  // 16 x 9216 x 9216 14.5 -> 13.5 us
-        return run_splitk<MODE_NVFP4, 1, 2, 8, 1>(g, st);
-      }
-      if (rows32 * ((n + 95) / 96) <= cus) return run_splitk<MODE_NVFP4, 1, 3, 8, 1>(g, st);
-      if (rows64 * ((n + 95) / 96) <= cus) return run_splitk<MODE_NVFP4, 2, 3, 8, 1>(g, st);
-      return run_splitk<MODE_NVFP4, 2, 2, 4, 2>(g, st);
-    }
+    const SplitK p = plan_nvfp4(m, n, k, cus);
+    if (p == SplitK{1, 1, 8, 1}) return run_splitk<MODE_NVFP4, 1, 1, 8, 1>(g, st);
+    if (p == SplitK{1, 1, 4, 2}) return run_splitk<MODE_NVFP4, 1, 1, 4, 2>(g, st);
+    if (p == SplitK{1, 2, 8, 3}) return run_splitk<MODE_NVFP4, 1, 2, 8, 3>(g, st);
+    if (p == SplitK{1, 2, 8, 1}) return run_splitk<MODE_NVFP4, 1, 2, 8, 1>(g, st);
+    if (p == SplitK{1, 3, 8, 1}) return run_splitk<MODE_NVFP4, 1, 3, 8, 1>(g, st);
+    if (p == SplitK{2, 2, 8, 1}) return run_splitk<MODE_NVFP4, 2, 2, 8, 1>(g, st);
+    if (p == SplitK{2, 3, 8, 1}) return run_splitk<MODE_NVFP4, 2, 3, 8, 1>(g, st);
+    if (p == SplitK{2, 2, 4, 2}) return run_splitk<MODE_NVFP4, 2, 2, 4, 2>(g, st);
     return launch_large<MODE_NVFP4>(g, cus, st);
   } else {
     const int64_t npan_all = (n + 31) / 32;

@@ -96,4 +96,29 @@ inline SplitK plan_w4a16(int64_t m, int64_t n, int64_t k, int64_t cus) {
   return {2, 2, 4, 1};
 }
 
+// NVFP4. {}: the persistent kernel. Below half a round of 256 x 256 tiles and 11/16
+// of a round of 128 x 256 ones the split-K kernel is faster (back to back, split-K
+// against 128-row tiles: 500 x 9216 x 3072, 144 tiles, 35.7 / 37.2 us; 1280 x 4096 x
+// 4096, 160, 46.9 / 48.3; 640 x 9216 x 3072, 180, 42.6 / 38.4; 1900 x 3072 x 1024, 180,
+// 21.3 / 16.8; 1024 x 6144 x 3072, 192, 44.3 / 40.1; 2300 x 3072 x 9216, 216, 164 / 113).
+// The narrowest tile that gives every workgroup a CU of its own (64 x 64 before 64
+// x 96: 1520 x 624 x 768 6.4 us against 8.0, 315 x 3056 x 11136 25.9 against 30.7);
+// past that 64 x 64 tiles of four waves, two workgroups per CU, so that one's
+// reduction runs beside the other's loop. Measured (GPU time from graph replays,
+// 24 shapes, 12 tilings) against a 32 x 64 / 64 x 64 / 64 x 96 rule: 1 x 3072 x 1024
+// 5.1 -> 3.8 us, 64 x 3072 x 3072 8.0 -> 5.8, 300 x 1024 x 3072 8.1 -> 6.9, 151 x 3520 x
+// 5504 21.6 -> 14.8, 2048 x 1024 x 3072 25.0 -> 20.3, 1555 x 4512 x 3968 80 -> 69.
+inline SplitK plan_nvfp4(int64_t m, int64_t n, int64_t k, int64_t cus) {
+  const int64_t rows32 = (m + 31) / 32, rows64 = (m + 63) / 64, chunks = k / 128;
+  const int64_t tiles256 = (m + 255) / 256 * ((n + 255) / 256), tiles128 = (m + 127) / 128 * ((n + 255) / 256);
+  if (m > 128 && (2 * tiles256 >= cus || 16 * tiles128 >= 11 * cus)) return {};
+  if (rows32 * ((n + 31) / 32) <= cus) return chunks >= 32 ? SplitK{1, 1, 8, 1} : SplitK{1, 1, 4, 2};  // 44 x 352 x 7296 8.8 -> 8.2 us
+  if (rows32 * ((n + 63) / 64) <= cus) return chunks >= 32 ? SplitK{1, 2, 8, 3} : SplitK{1, 2, 8, 1};  // 16 x 9216 x 9216 14.5 -> 13.5 us
+  if (rows32 * ((n + 95) / 96) <= cus) return {1, 3, 8, 1};
+  const int64_t t22 = rows64 * ((n + 63) / 64), t23 = rows64 * ((n + 95) / 96);
+  if (t22 <= cus) return {2, 2, 8, 1};
+  if (t23 <= cus) return {2, 3, 8, 1};
+  return {2, 2, 4, 2};
+}
+
 }  // namespace qg
