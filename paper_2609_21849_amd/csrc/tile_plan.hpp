@@ -104,7 +104,10 @@ inline SplitK plan_w4a16(int64_t m, int64_t n, int64_t k, int64_t cus) {
 // The narrowest tile that gives every workgroup a CU of its own (64 x 64 before 64
 // x 96: 1520 x 624 x 768 6.4 us against 8.0, 315 x 3056 x 11136 25.9 against 30.7);
 // past that 64 x 64 tiles of four waves, two workgroups per CU, so that one's
-// reduction runs beside the other's loop. Measured (GPU time from graph replays,
+// reduction runs beside the other's loop, except at long K, where that hides
+// little, 64 x 96 if they make no more rounds (4743 x 480 x 5120 35.3 us against 40.2,
+// 1173 x 3808 x 11392 104 against 115; at K = 2944 1896 x 1248 23.9 against 22.8).
+// Measured (GPU time from graph replays,
 // 24 shapes, 12 tilings) against a 32 x 64 / 64 x 64 / 64 x 96 rule: 1 x 3072 x 1024
 // 5.1 -> 3.8 us, 64 x 3072 x 3072 8.0 -> 5.8, 300 x 1024 x 3072 8.1 -> 6.9, 151 x 3520 x
 // 5504 21.6 -> 14.8, 2048 x 1024 x 3072 25.0 -> 20.3, 1555 x 4512 x 3968 80 -> 69.
@@ -118,6 +121,7 @@ inline SplitK plan_nvfp4(int64_t m, int64_t n, int64_t k, int64_t cus) {
   const int64_t t22 = rows64 * ((n + 63) / 64), t23 = rows64 * ((n + 95) / 96);
   if (t22 <= cus) return {2, 2, 8, 1};
   if (t23 <= cus) return {2, 3, 8, 1};
+  if (k >= 5120 && rows64 > 1 && (t23 + cus - 1) / cus <= (t22 + 2 * cus - 1) / (2 * cus)) return {2, 3, 8, 1};
   return {2, 2, 4, 2};
 }
 
