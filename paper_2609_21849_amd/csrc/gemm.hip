@@ -3055,28 +3055,15 @@ static hipError_t launch_large(const GemmArgs& g, int64_t cus, hipStream_t st) {
   return hipGetLastError();
 }
 
-// MXFP4 / MXFP8. Up to a round of 64 x 96 tiles on the CUs the split-K kernel,
-// above that the large tiles: those walk K serially, while a split-K tile's waves
-// share K and the operands' L2 traffic is all that bounds it. Inside the split-K
-// range the narrowest tile that still gives every workgroup a CU of its own.
-// Measured (GPU time from graph replays, 256 x 256 -> split-K; best of 16 tilings
-// within 8% everywhere): MXFP4 1 x 3072 x 1024 12.7 -> 2.8 us, 256 x 3072 x 3072 25.0 ->
-// 6.8, 500 x 3072 x 3072 38 -> 10.8; MXFP8 14.3 -> 3.1, 32.0 -> 10.3, 37.5 -> 15.0.
-// Two rounds of split-K tiles against 128-row large ones, calls back to back: 1024 x
-// 3072 x 3072 MXFP4 18.8 / 14.2 us, MXFP8 26.8 / 24.0; 256 x 9216 x 3072 18.3 / 13.7, 26.8 /
-// 24.1; 700 x 4096 x 9216 41.1 / 37.9, 64.8 / 67.2.
 template <int MODE>
 static hipError_t launch_mx(GemmArgs g, hipStream_t st) {
   const int64_t cus = device_cus();
-  const int64_t rows32 = (g.m + 31) / 32, rows64 = (g.m + 63) / 64;
-  if (rows32 * ((g.n + 31) / 32) <= cus) return run_splitk<MODE, 1, 1, 4, 2>(g, st);
-  if (rows32 * ((g.n + 63) / 64) <= cus) return run_splitk<MODE, 1, 2, 4, 2>(g, st);
-  if (rows32 * ((g.n + 95) / 96) <= cus) return run_splitk<MODE, 1, 3, 8, 1>(g, st);
-  const int64_t t6496 = rows64 * ((g.n + 95) / 96);
-  if (t6496 > cus && rows64 * ((g.n + 127) / 128) <= cus) return run_splitk<MODE, 2, 4, 8, 1>(g, st);
-  // (two rounds of them: only where K is short, or long in MXFP8)
-  if (t6496 <= cus || (t6496 <= 2 * cus && (g.k < 2048 || (MODE == MODE_MXFP8 && g.k > 6144))))
-    return run_splitk<MODE, 2, 3, 4, 2>(g, st);
+  const SplitK p = plan_mx(g.m, g.n, g.k, cus, MODE == MODE_MXFP8);
+  if (p == SplitK{1, 1, 4, 2}) return run_splitk<MODE, 1, 1, 4, 2>(g, st);
+  if (p == SplitK{1, 2, 4, 2}) return run_splitk<MODE, 1, 2, 4, 2>(g, st);
+  if (p == SplitK{1, 3, 8, 1}) return run_splitk<MODE, 1, 3, 8, 1>(g, st);
+  if (p == SplitK{2, 4, 8, 1}) return run_splitk<MODE, 2, 4, 8, 1>(g, st);
+  if (p == SplitK{2, 3, 4, 2}) return run_splitk<MODE, 2, 3, 4, 2>(g, st);
   return launch_large<MODE>(g, cus, st);
 }
 

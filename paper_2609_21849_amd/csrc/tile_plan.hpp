@@ -125,4 +125,28 @@ inline SplitK plan_nvfp4(int64_t m, int64_t n, int64_t k, int64_t cus) {
   return {2, 2, 4, 2};
 }
 
+// MXFP4 / MXFP8. Up to a round of 64 x 96 tiles on the CUs the split-K kernel,
+// above that the large tiles ({}): those walk K serially, while a split-K tile's
+// waves share K and the operands' L2 traffic is all that bounds it. Inside the
+// split-K range the narrowest tile that still gives every workgroup a CU of its own.
+// Measured (GPU time from graph replays, 256 x 256 -> split-K; best of 16 tilings
+// within 8% everywhere): MXFP4 1 x 3072 x 1024 12.7 -> 2.8 us, 256 x 3072 x 3072 25.0 ->
+// 6.8, 500 x 3072 x 3072 38 -> 10.8; MXFP8 14.3 -> 3.1, 32.0 -> 10.3, 37.5 -> 15.0.
+// Two rounds of split-K tiles against 128-row large ones: MXFP4 355 x 7664 x 256 10.5 /
+// 6.1 us, 166 x 16176 x 1536 14.1 / 10.1, 1024 x 3072 x 3072 18.8 / 14.2, 700 x 4096 x 9216
+// 41.1 / 37.9; MXFP8 1024 x 3072 x 512 14.4 / 8.1, 310 x 7008 x 1792 19.5 / 15.3, 1180 x 2224 x
+// 6144 48.3 / 48.1, but with long K MXFP8's split is level or better (12 shapes: 518 x
+// 4816 x 7680 56.2 / 57.3, 5262 x 496 x 8448 65.7 / 64.0, 406 x 6016 x 9472 64.0 / 67.5, 699 x 4016
+// x 11520 79.2 / 84.9, 968 x 2528 x 14848 102 / 107).
+inline SplitK plan_mx(int64_t m, int64_t n, int64_t k, int64_t cus, bool fp8) {
+  const int64_t rows32 = (m + 31) / 32, rows64 = (m + 63) / 64;
+  if (rows32 * ((n + 31) / 32) <= cus) return {1, 1, 4, 2};
+  if (rows32 * ((n + 63) / 64) <= cus) return {1, 2, 4, 2};
+  if (rows32 * ((n + 95) / 96) <= cus) return {1, 3, 8, 1};
+  const int64_t t23 = rows64 * ((n + 95) / 96);
+  if (t23 > cus && rows64 * ((n + 127) / 128) <= cus) return {2, 4, 8, 1};
+  if (t23 <= cus || (t23 <= 2 * cus && fp8 && k > 6144)) return {2, 3, 4, 2};
+  return {};
+}
+
 }  // namespace qg
