@@ -3099,44 +3099,14 @@ hipError_t launch_gemm(int a_fmt, const void* a, const uint8_t* a_bscale, const 
   if (a_fmt == 4) return launch_mx<MODE_MXFP8>(g, st);
   const int cus = device_cus();
   if (a_fmt == 1) {
-    g.tiles_m = (g.m + 255) / 256;
-    g.tiles_n = (g.n + 255) / 256;
-    const int tiles = g.tiles_m * g.tiles_n;
-    // Few tokens: the split-K kernel. FP8 operands need no expansion, so
-    // narrow tiles cost nothing extra: the narrowest 32-row tile (32 x 32 NP,
-    // NP = 1 .. 4) that still gives every workgroup a CU of its own, with
-    // eight waves and one chunk in flight each (NP = 2: four waves, two
-    // chunks); else 32 x 64 tiles while those number at most two per CU.
-    // Measured at M = 16 .. 1024, N, K in {256, 1024, 3072, 9216} (GPU time
-    // from graph replays): the best of five tilings within 2% at every shape
-    // (128 x 256 x 256 3.8 -> 3.2 us, 256 x 3072 x 1024 6.6 -> 5.7 us,
-    // 1024 x 1024 x 3072 11.9 -> 10.0 us; the 32 x 64 rule alone was 1.2-1.9x
-    // faster than the 64 x 128 kernel where K >= 3072).
-    if (m <= 1024) {
-      const int64_t rows32 = (m + 31) / 32;
-      if (rows32 * ((n + 31) / 32) <= cus) {
-        // at most four chunks (K <= 512): four waves (128 x 256 x 256: 3.2 -> 2.8 us)
-        if ((k >> 7) <= 4) return run_splitk<MODE_FP8, 1, 1, 4, 1>(g, st);
-        return run_splitk<MODE_FP8, 1, 1, 8, 1>(g, st);
-      }
-      if (rows32 * ((n + 63) / 64) <= cus) return run_splitk<MODE_FP8, 1, 2, 4, 2>(g, st);
-      if (rows32 * ((n + 95) / 96) <= cus) return run_splitk<MODE_FP8, 1, 3, 8, 1>(g, st);
-      if (rows32 * ((n + 127) / 128) <= cus) return run_splitk<MODE_FP8, 1, 4, 8, 1>(g, st);
-    }
-    const int64_t small_tiles = (int64_t)((m + 31) / 32) * ((n + 63) / 64);
-    if (small_tiles <= 2 * cus) return run_splitk<MODE_FP8, 1, 2, 4, 2>(g, st);
-    // one round of 64 x 96 split-K tiles at long K, where the 64 x 128 kernel
-    // below walks K in too few workgroups: 512 x 3072 x 3072 15.1 -> 14.0 us, 512 x
-    // 3072 x 9216 34.2 -> 29.4 (at 889 x 1584 x 1152 it loses, 8.8 -> 9.2)
-    if (k >= 2048 && (int64_t)((m + 63) / 64) * ((n + 95) / 96) <= cus)
-      return run_splitk<MODE_FP8, 2, 3, 4, 2>(g, st);
-    // Too few large tiles to fill the chip: the 64 x 128 kernel's many more
-    // workgroups win. Measured crossover: 3/8 of a 128 x 256 tile per CU (1024 x
-    // 3072 x 3072, 96 tiles, 20.7 us against 20.4; 700 x 4096 x 9216, 96, 49.2 against
-    // 50.6; 1500 x 3072 x 3072, 144, 28.4 against 21.2); below K = 1024 3/8 of a 256 x
-    // 256 tile.
-    if (m <= 128 || (k < 1024 ? 8 * tiles < 3 * cus : 8 * ((m + 127) / 128 * g.tiles_n) <= 3 * (int64_t)cus))
-      return run_fp8<1, 2>(g, st);
+    const SplitK p = plan_fp8(m, n, k, cus);
+    if (p == SplitK{1, 1, 4, 1}) return run_splitk<MODE_FP8, 1, 1, 4, 1>(g, st);
+    if (p == SplitK{1, 1, 8, 1}) return run_splitk<MODE_FP8, 1, 1, 8, 1>(g, st);
+    if (p == SplitK{1, 2, 4, 2}) return run_splitk<MODE_FP8, 1, 2, 4, 2>(g, st);
+    if (p == SplitK{1, 3, 8, 1}) return run_splitk<MODE_FP8, 1, 3, 8, 1>(g, st);
+    if (p == SplitK{1, 4, 8, 1}) return run_splitk<MODE_FP8, 1, 4, 8, 1>(g, st);
+    if (p == SplitK{2, 3, 4, 2}) return run_splitk<MODE_FP8, 2, 3, 4, 2>(g, st);
+    if (p == kFp8Tiles64) return run_fp8<1, 2>(g, st);
     // 288 x 192 tiles where their rounds take less than those of the 256-column
     // tiles (a full round 92 % of one of 256 x 256: 4608 x 3072 x 3072 36.7 us against
     // 37.7, 2800 x 9216 x 3072 71.1 against 76.1; but 2304 x 9216 x 3072 64.1 against
@@ -3145,7 +3115,7 @@ hipError_t launch_gemm(int a_fmt, const void* a, const uint8_t* a_bscale, const 
     const int t288_m = (int)((m + 287) / 288), t288_n = (int)((n + 191) / 192);
     const int64_t t288 = (int64_t)t288_m * t288_n;
     if (out_mode != OUT_NVFP4 &&
-        92 * rounds_cost(t288, cus) < plan_tile_rows(m, g.tiles_n, cus, kRoundCost<MODE_FP8>).cost) {
+        92 * rounds_cost(t288, cus) < plan_tile_rows(m, (n + 255) / 256, cus, kRoundCost<MODE_FP8>).cost) {
       g.tiles_m = t288_m;
       g.tiles_n = t288_n;
       const dim3 grid((unsigned)std::min<int64_t>(t288, cus));

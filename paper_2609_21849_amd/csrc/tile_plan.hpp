@@ -149,4 +149,47 @@ inline SplitK plan_mx(int64_t m, int64_t n, int64_t k, int64_t cus, bool fp8) {
   return {};
 }
 
+// FP8. {}: the persistent kernels of large tiles; kFp8Tiles64: the 64 x 128 tiles
+// of four waves (k_gemm_fp8), which share no K.
+// Few tokens: the split-K kernel. FP8 operands need no expansion, so
+// narrow tiles cost nothing extra: the narrowest 32-row tile (32 x 32 NP,
+// NP = 1 .. 4) that still gives every workgroup a CU of its own, with
+// eight waves and one chunk in flight each (NP = 2: four waves, two
+// chunks); else 32 x 64 tiles while those number at most two per CU.
+// Measured at M = 16 .. 1024, N, K in {256, 1024, 3072, 9216} (GPU time
+// from graph replays): the best of five tilings within 2% at every shape
+// (128 x 256 x 256 3.8 -> 3.2 us, 256 x 3072 x 1024 6.6 -> 5.7 us,
+// 1024 x 1024 x 3072 11.9 -> 10.0 us; the 32 x 64 rule alone was 1.2-1.9x
+// faster than the 64 x 128 kernel where K >= 3072).
+constexpr SplitK kFp8Tiles64 = {2, 4, 4, 0};
+
+inline SplitK plan_fp8(int64_t m, int64_t n, int64_t k, int64_t cus) {
+  const int64_t rows32 = (m + 31) / 32, rows64 = (m + 63) / 64, t12 = rows32 * ((n + 63) / 64);
+  if (m <= 1024) {
+    // (at most four chunks, K <= 512: four waves, 128 x 256 x 256 3.2 -> 2.8 us)
+    if (rows32 * ((n + 31) / 32) <= cus) return k <= 512 ? SplitK{1, 1, 4, 1} : SplitK{1, 1, 8, 1};
+    if (t12 <= cus) return {1, 2, 4, 2};
+    if (rows32 * ((n + 95) / 96) <= cus) return {1, 3, 8, 1};
+    if (rows32 * ((n + 127) / 128) <= cus) return {1, 4, 8, 1};
+  }
+  if (t12 <= 2 * cus) return {1, 2, 4, 2};
+  // one round of 64 x 96 split-K tiles at long K, where the 64 x 128 kernel
+  // below walks K in too few workgroups: 512 x 3072 x 3072 15.1 -> 14.0 us, 512 x
+  // 3072 x 9216 34.2 -> 29.4 (at 889 x 1584 x 1152 it loses, 8.8 -> 9.2)
+  if (k >= 2048 && rows64 * ((n + 95) / 96) <= cus) return {2, 3, 4, 2};
+  // Too few large tiles to fill the chip: the 64 x 128 kernel's many more
+  // workgroups win. Measured crossover: 3/8 of a 128 x 256 tile per CU (1024 x
+  // 3072 x 3072, 96 tiles, 20.7 us against 20.4; 700 x 4096 x 9216, 96, 49.2 against
+  // 50.6; 1500 x 3072 x 3072, 144, 28.4 against 21.2), and below K = 4608 as long as
+  // its workgroups are at most two per CU, which run at once (6351 x 528 x 1152,
+  // 500 workgroups, 11.2 us against 12.2; 4278 x 528 x 2432, 335, 17.5 against 19.0;
+  // 620 x 5360 x 4224, 420, 27.8 against 28.6; but 5668 x 704 x 2048, 534, 21.5 against
+  // 17.3, and 473 x 7808 x 6528, 488, 41.1 against 39.7); below K = 1024 3/8 of a
+  // 256 x 256 tile.
+  const int64_t tiles256 = (m + 255) / 256 * ((n + 255) / 256), tiles128 = (m + 127) / 128 * ((n + 255) / 256);
+  if (m <= 128 || (k < 1024 ? 8 * tiles256 < 3 * cus : 8 * tiles128 <= 3 * cus)) return kFp8Tiles64;
+  if (k >= 1024 && k < 4608 && rows64 * ((n + 127) / 128) <= 2 * cus) return kFp8Tiles64;
+  return {};
+}
+
 }  // namespace qg

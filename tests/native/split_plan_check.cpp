@@ -19,6 +19,7 @@ int main() {
     if (!strcmp(r.kind, "nvfp4")) p = qg::plan_nvfp4(r.m, r.n, r.k, 256);
     if (!strcmp(r.kind, "mxfp4")) p = qg::plan_mx(r.m, r.n, r.k, 256, false);
     if (!strcmp(r.kind, "mxfp8")) p = qg::plan_mx(r.m, r.n, r.k, 256, true);
+    if (!strcmp(r.kind, "fp8")) p = qg::plan_fp8(r.m, r.n, r.k, 256);
     if (!(p == r.want)) {
       ++bad;
       printf("%s %lld x %lld x %lld: %d %d %d %d, wanted %d %d %d %d\n", r.kind, (long long)r.m, (long long)r.n, (long long)r.k,
