@@ -499,10 +499,8 @@ __global__ void __launch_bounds__(64 * NW) k_gemm_splitk(GemmArgs g) {
   // compiler waits for every outstanding load)
   const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int r = lane & 31, gq = lane >> 5;
-  const int tiles = g.tiles_m * g.tiles_n;
-  const int t = xcd_tile((int)blockIdx.x, tiles);
-  const int bn = t / g.tiles_m, bm = t - bn * g.tiles_m;
-  const int m0 = bm * BM, n0 = bn * BN;
+  const TileAt at = split_tile((int)blockIdx.x, g.tiles_m, g.tiles_n, g.tiles_m * MT > g.tiles_n * NP);
+  const int m0 = at.bm * BM, n0 = at.bn * BN;
   const int kcn = g.k >> 7;
   const int npanels_w = (g.n + 31) >> 5;
 
