@@ -80,7 +80,9 @@ struct SplitK {
 // one of 256 x 256; up to K = 512, where the split's reduction is most of its
 // time, from 5/16 of a round of the former (7674 x 432 x 256, 120 tiles, 14.6 / 9.9; 1117
 // x 2112 x 384, 81, 12.4 / 11.3; 1643 x 1392 x 512, 78, 13.2 / 13.0; 1523 x 976 x 384, 48, 9.2 /
-// 11.2). Heights (256 rows -> chosen): 1024 x 6144 x 3072 68.4 -> 54.0 us (128),
+// 11.2). Not for 129 to 192 rows at long K, a third of whose 128-row tiles is padding
+// (150 x 21568 x 8192 97 us split, 129; 141 x 23488 x 3200 53.5, 55.0; 147 x 24080 x 1408
+// 31.5, 27.3). Heights (256 rows -> chosen): 1024 x 6144 x 3072 68.4 -> 54.0 us (128),
 // 2304 x 9216 x 3072 146.7 -> 128.8 (192), 1900 x 3072 x 1024 28.3 -> 21.3 (128).
 // Split-K tilings. Up to 32 rows: one-panel workgroups, at K > 3072 with three
 // chunks of a wave in one batch of loads, else one at a time where the workgroups
@@ -101,7 +103,9 @@ struct SplitK {
 inline SplitK plan_w4a16(int64_t m, int64_t n, int64_t k, int64_t cus) {
   const int64_t rows32 = (m + 31) / 32, rows64 = (m + 63) / 64, npan = (n + 31) / 32;
   const int64_t tiles256 = (m + 255) / 256 * ((n + 255) / 256), tiles128 = (m + 127) / 128 * ((n + 255) / 256);
-  if (m > 128 && (8 * tiles256 >= 3 * cus || 32 * tiles128 >= 21 * cus || (k <= 512 && 16 * tiles128 >= 5 * cus))) return {};
+  const bool padded = m <= 192 && k >= 3072;
+  if (m > 128 && (8 * tiles256 >= 3 * cus || (32 * tiles128 >= 21 * cus && !padded) || (k <= 512 && 16 * tiles128 >= 5 * cus)))
+    return {};
   const int64_t t12 = rows32 * ((npan + 1) / 2), t22 = rows64 * ((npan + 1) / 2), t23 = rows64 * ((npan + 2) / 3);
   if (m <= 32) return {1, 1, 8, k <= 3072 && (npan <= cus || m * k <= (npan <= 2 * cus ? 72 : 24) * 1024) ? 1 : 3};
   if (rows32 * npan <= cus) return {1, 1, 8, 3};
@@ -116,7 +120,9 @@ inline SplitK plan_w4a16(int64_t m, int64_t n, int64_t k, int64_t cus) {
 // of a round of 128 x 256 ones the split-K kernel is faster (back to back, split-K
 // against 128-row tiles: 500 x 9216 x 3072, 144 tiles, 35.7 / 37.2 us; 1280 x 4096 x
 // 4096, 160, 46.9 / 48.3; 640 x 9216 x 3072, 180, 42.6 / 38.4; 1900 x 3072 x 1024, 180,
-// 21.3 / 16.8; 1024 x 6144 x 3072, 192, 44.3 / 40.1; 2300 x 3072 x 9216, 216, 164 / 113).
+// 21.3 / 16.8; 1024 x 6144 x 3072, 192, 44.3 / 40.1; 2300 x 3072 x 9216, 216, 164 / 113),
+// and for 129 to 192 rows at long K, a third of whose 128-row tiles is padding (151 x
+// 27472 x 5376 66.5 / 72.9; 141 x 23488 x 3200 35.7 / 41.8; 168 x 25664 x 1152 22.4 / 20.6).
 // The narrowest tile that gives every workgroup a CU of its own (64 x 64 before 64
 // x 96: 1520 x 624 x 768 6.4 us against 8.0, 315 x 3056 x 11136 25.9 against 30.7);
 // past that 64 x 64 tiles of four waves, two workgroups per CU, so that one's
@@ -130,7 +136,7 @@ inline SplitK plan_w4a16(int64_t m, int64_t n, int64_t k, int64_t cus) {
 inline SplitK plan_nvfp4(int64_t m, int64_t n, int64_t k, int64_t cus) {
   const int64_t rows32 = (m + 31) / 32, rows64 = (m + 63) / 64, chunks = k / 128;
   const int64_t tiles256 = (m + 255) / 256 * ((n + 255) / 256), tiles128 = (m + 127) / 128 * ((n + 255) / 256);
-  if (m > 128 && (2 * tiles256 >= cus || 16 * tiles128 >= 11 * cus)) return {};
+  if (m > 128 && (2 * tiles256 >= cus || (16 * tiles128 >= 11 * cus && (m > 192 || k < 3072)))) return {};
   if (rows32 * ((n + 31) / 32) <= cus) return chunks >= 32 ? SplitK{1, 1, 8, 1} : SplitK{1, 1, 4, 2};  // 44 x 352 x 7296 8.8 -> 8.2 us
   if (rows32 * ((n + 63) / 64) <= cus) return chunks >= 32 ? SplitK{1, 2, 8, 3} : SplitK{1, 2, 8, 1};  // 16 x 9216 x 9216 14.5 -> 13.5 us
   if (rows32 * ((n + 95) / 96) <= cus) return {1, 3, 8, 1};
