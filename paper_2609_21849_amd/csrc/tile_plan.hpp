@@ -128,7 +128,8 @@ inline SplitK plan_w4a16(int64_t m, int64_t n, int64_t k, int64_t cus) {
 // past that 64 x 64 tiles of four waves, two workgroups per CU, so that one's
 // reduction runs beside the other's loop, except at long K, where that hides
 // little, 64 x 96 if they make no more rounds (4743 x 480 x 5120 35.3 us against 40.2,
-// 1173 x 3808 x 11392 104 against 115; at K = 2944 1896 x 1248 23.9 against 22.8).
+// 1173 x 3808 x 11392 104 against 115, 666 x 6128 x 4096 41.7 against 45.8; at K = 2944 1896 x
+// 1248 23.9 against 22.8).
 // Measured (GPU time from graph replays,
 // 24 shapes, 12 tilings) against a 32 x 64 / 64 x 64 / 64 x 96 rule: 1 x 3072 x 1024
 // 5.1 -> 3.8 us, 64 x 3072 x 3072 8.0 -> 5.8, 300 x 1024 x 3072 8.1 -> 6.9, 151 x 3520 x
@@ -143,7 +144,8 @@ inline SplitK plan_nvfp4(int64_t m, int64_t n, int64_t k, int64_t cus) {
   const int64_t t22 = rows64 * ((n + 63) / 64), t23 = rows64 * ((n + 95) / 96);
   if (t22 <= cus) return {2, 2, 8, 1};
   if (t23 <= cus) return {2, 3, 8, 1};
-  if (k >= 5120 && rows64 > 1 && (t23 + cus - 1) / cus <= (t22 + 2 * cus - 1) / (2 * cus)) return {2, 3, 8, 1};
+  const int64_t rounds22 = (t22 + 2 * cus - 1) / (2 * cus), rounds23 = (t23 + cus - 1) / cus;
+  if (k >= (rounds23 > 2 ? 4096 : 5120) && rows64 > 1 && rounds23 <= rounds22) return {2, 3, 8, 1};
   return {2, 2, 4, 2};
 }
 
