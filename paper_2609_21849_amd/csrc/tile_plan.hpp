@@ -103,9 +103,8 @@ struct SplitK {
 inline SplitK plan_w4a16(int64_t m, int64_t n, int64_t k, int64_t cus) {
   const int64_t rows32 = (m + 31) / 32, rows64 = (m + 63) / 64, npan = (n + 31) / 32;
   const int64_t tiles256 = (m + 255) / 256 * ((n + 255) / 256), tiles128 = (m + 127) / 128 * ((n + 255) / 256);
-  const bool padded = m <= 192 && k >= 3072;
-  if (m > 128 && (8 * tiles256 >= 3 * cus || (32 * tiles128 >= 21 * cus && !padded) || (k <= 512 && 16 * tiles128 >= 5 * cus)))
-    return {};
+  if (m > 128 && (8 * tiles256 >= 3 * cus || (k <= 512 && 16 * tiles128 >= 5 * cus))) return {};
+  if (m > 128 && 32 * tiles128 >= 21 * cus) return m <= 192 && k >= 3072 ? SplitK{2, 2, 4, 1} : SplitK{};
   const int64_t t12 = rows32 * ((npan + 1) / 2), t22 = rows64 * ((npan + 1) / 2), t23 = rows64 * ((npan + 2) / 3);
   if (m <= 32) return {1, 1, 8, k <= 3072 && (npan <= cus || m * k <= (npan <= 2 * cus ? 72 : 24) * 1024) ? 1 : 3};
   if (rows32 * npan <= cus) return {1, 1, 8, 3};
