@@ -918,17 +918,36 @@ inline bool out_staged(const GemmArgs& g) {
   return (base & 15) == 0 && ((g.ldy * esz) & 15) == 0;
 }
 
-// The lane or thread index as a value the compiler cannot trace back: what a
-// tile's prologue or epilogue derives from it is then computed there, and not
-// hoisted out of the loop over tiles and kept across the K loop, whose
-// accumulators and fragments fill the register file: it spilled, and every
-// reload from scratch in the prologue waited for the operand loads issued
-// before it. With this and the wave index in a scalar register (no spills in
-// most instances, where there were 21 to 103): MXFP4 4608 x 9216 x 3072 93 -> 75 us,
-// MXFP8 2800 x 9216 x 3072 83 -> 72, W4A4 2800 x 9216 x 3072 134 -> 128.
-__device__ __attribute__((always_inline)) inline int opaque_lane(int lane) {
-  asm volatile("" : "+v"(lane));
+// The lane index, computed where it is asked for (volatile: neither hoisted nor
+// shared), so that what a tile's prologue or epilogue derives from it is computed
+// there too, and not hoisted out of the loop over tiles and kept across the K loop,
+// whose accumulators and fragments fill the register file: what does not fit goes
+// to scratch, and a reload in the prologue waits for the loads issued before it and
+// for the stores of the tile before. With this, the wave index in a scalar register
+// and zero_tiles the staged instances spill 0 or 1 registers (MXFP8 with NVFP4 output
+// 5). Everything hoisted (21 to 103 spilled) against derived per tile from a kept
+// thread index (0 to 34): MXFP4 4608 x 9216 x 3072 93 -> 75 us, MXFP8 2800 x 9216 x 3072
+// 83 -> 72, W4A4 2800 x 9216 x 3072 134 -> 128; that against this: NVFP4 5532 x 18272 x
+// 256 87.8 -> 79.8, W4A16 4650 x 28448 x 256 121 -> 110, 7266 x 8192 x 256 59.1 -> 53.4.
+__device__ __attribute__((always_inline)) inline int fresh_lane() {
+  int lane;
+  asm volatile("v_mbcnt_lo_u32_b32 %0, -1, 0\n\tv_mbcnt_hi_u32_b32 %0, -1, %0" : "=v"(lane));
   return lane;
+}
+
+// Zero accumulators, made where they are asked for: as one constant on both ways
+// into the main loop (with and without an odd first chunk), 32 of them were kept in
+// scratch and reloaded for every tile of the 16-bit kernels.
+template <int TM>
+__device__ __attribute__((always_inline)) inline void zero_tiles(v16f (&acc)[TM][4]) {
+  float z;
+  asm volatile("v_mov_b32 %0, 0" : "=v"(z));
+#pragma unroll
+  for (int i = 0; i < TM; ++i)
+#pragma unroll
+    for (int j = 0; j < 4; ++j)
+#pragma unroll
+      for (int v = 0; v < 16; ++v) acc[i][j][v] = z;
 }
 
 // Four consecutive outputs in the stage's element type (out_mode: bf16, fp32
@@ -953,7 +972,7 @@ __device__ __attribute__((always_inline)) inline void store_staged_as(const Gemm
   constexpr int JN = OUT == OUT_F32 ? TN / 2 : TN;  // 32-column blocks staged at once
   constexpr int RB = 32 * JN * ESZ, PITCH = RB + 16, PPR = RB / 16, ROWS_PER_IT = 64 / PPR;
   static_assert(64 % PPR == 0 && TN % JN == 0 && PITCH <= 64 * TN + 16, "a wave reads whole rows per instruction");
-  lane = opaque_lane(lane);
+  lane = fresh_lane();
   uint8_t* wr = stage + (lane & 31) * PITCH + 4 * ESZ * (lane >> 5);
   const uint8_t* rd = stage + (lane / PPR) * PITCH + 16 * (lane % PPR);
   const int nl = nw + (16 / ESZ) * (lane % PPR), ml = mw + lane / PPR;
@@ -989,7 +1008,7 @@ __device__ __attribute__((always_inline)) inline void store_staged_nv(const Gemm
                                                                       float c) {
   static_assert(TN == 4, "64 code bytes and 8 block scales per row");
   constexpr int PITCH = 64 + 16;
-  lane = opaque_lane(lane);
+  lane = fresh_lane();
   const float st = *g.y_scale, d = nv_out_d(g);
   const int gq = lane >> 5;
   uint8_t* wr = stage + (lane & 31) * PITCH + 4 * gq;
@@ -1254,8 +1273,8 @@ __global__ void __launch_bounds__(256) k_gemm_fp8_direct(GemmArgs g) {
   };
 
   for (int tile = blockIdx.x; tile < total; tile += gridDim.x) {
-    tid = opaque_lane(threadIdx.x);
-    lane = tid & 63;
+    lane = fresh_lane();
+    tid = 64 * wave + lane;
     int bm, bn;
     tile_coords(tile, g.tiles_m, g.tiles_n, bm, bn);
     const int m0 = bm * (64 * TM), n0 = bn * 256;
@@ -1750,8 +1769,8 @@ __global__ void __launch_bounds__(256) k_gemm_mxfp8_direct(GemmArgs g) {
   };
 
   for (int tile = blockIdx.x; tile < total; tile += gridDim.x) {
-    tid = opaque_lane(threadIdx.x);
-    lane = tid & 63;
+    lane = fresh_lane();
+    tid = 64 * wave + lane;
     r = lane & 31;
     gq = lane >> 5;
     int bm, bn;
@@ -1984,8 +2003,8 @@ __global__ void __launch_bounds__(256) k_gemm_nvfp4_direct(GemmArgs g) {
   };
 
   for (int tile = blockIdx.x; tile < total; tile += gridDim.x) {
-    tid = opaque_lane(threadIdx.x);
-    lane = tid & 63;
+    lane = fresh_lane();
+    tid = 64 * wave + lane;
     r = lane & 31;
     gq = lane >> 5;
     int bm, bn;
@@ -2012,16 +2031,11 @@ __global__ void __launch_bounds__(256) k_gemm_nvfp4_direct(GemmArgs g) {
       ob[j] = in ? panel * (uint32_t)(kcn * 2048) + 16u * lane : OOB;
       osb[j] = in ? panel * (uint32_t)(kcn * 256) + 8u * r + 4u * gq : OOB;
     }
-#pragma unroll
-    for (int i = 0; i < TM; ++i)
-#pragma unroll
-      for (int j = 0; j < 4; ++j)
-#pragma unroll
-        for (int v = 0; v < 16; ++v) acc[i][j][v] = 0.0f;
 
     // An odd chunk count takes its first chunk unpipelined (see the W8A8 kernel).
     int kc = 0;
     if (kcn & 1) {
+      zero_tiles(acc);
       load_a(0);
       load_b(std::integral_constant<int, 0>(), 0);
       write_a_codes(smem, 0, TM);
@@ -2038,6 +2052,8 @@ __global__ void __launch_bounds__(256) k_gemm_nvfp4_direct(GemmArgs g) {
       }
       __syncthreads();
       kc = 1;
+    } else {
+      zero_tiles(acc);
     }
     if (kc < kcn) {
       load_a(kc);
@@ -2253,8 +2269,8 @@ __global__ void __launch_bounds__(256) k_gemm_mxfp4_direct(GemmArgs g) {
   };
 
   for (int tile = blockIdx.x; tile < total; tile += gridDim.x) {
-    tid = opaque_lane(threadIdx.x);
-    lane = tid & 63;
+    lane = fresh_lane();
+    tid = 64 * wave + lane;
     r = lane & 31;
     gq = lane >> 5;
     int bm, bn;
@@ -2381,12 +2397,7 @@ __global__ void __launch_bounds__(256) k_gemm_w4a16_direct(GemmArgs g) {
   // staging: thread tid copies piece c = tid % 16 of rows 16 i + tid / 16,
   // i = 0 .. 4 TM - 1; its LDS slots depend only on i % 2 (and i / 2 through the
   // panel, a constant offset)
-  const int cpc = tid & 15, s_c = cpc & 7, g_c = cpc >> 3, rlo = tid >> 4;
   uint32_t la_pair[2];
-#pragma unroll
-  for (int h = 0; h < 2; ++h)
-    la_pair[h] = (uint32_t)(s_c * 1024 + ((((16 * h + rlo) + 32 * g_c) ^ (s_c + 8 * g_c)) * 16));
-
   uint32_t oa[4 * TM], ob[4], osb[4];
   v4i ga[8];            // two staging quarters (register sets 0 and 1)
   v4i bc[2][4][2];      // weight codes [chunk parity][panel][half]
@@ -2503,13 +2514,17 @@ __global__ void __launch_bounds__(256) k_gemm_w4a16_direct(GemmArgs g) {
   };
 
   for (int tile = blockIdx.x; tile < total; tile += gridDim.x) {
-    tid = opaque_lane(threadIdx.x);
-    lane = tid & 63;
+    lane = fresh_lane();
+    tid = 64 * wave + lane;
     r = lane & 31;
     gq = lane >> 5;
     int bm, bn;
     tile_coords(tile, g.tiles_m, g.tiles_n, bm, bn);
     const int m0 = bm * (64 * TM), n0 = bn * 256;
+    const int cpc = tid & 15, s_c = cpc & 7, g_c = cpc >> 3, rlo = tid >> 4;
+#pragma unroll
+    for (int h = 0; h < 2; ++h)
+      la_pair[h] = (uint32_t)(s_c * 1024 + ((((16 * h + rlo) + 32 * g_c) ^ (s_c + 8 * g_c)) * 16));
 #pragma unroll
     for (int i = 0; i < 4 * TM; ++i) {
       const uint32_t row = (uint32_t)(m0 + 16 * i + rlo);
@@ -2522,16 +2537,11 @@ __global__ void __launch_bounds__(256) k_gemm_w4a16_direct(GemmArgs g) {
       ob[j] = in ? panel * (uint32_t)(kcn * 2048) + 16u * lane : OOB;
       osb[j] = in ? panel * (uint32_t)(kcn * 256) + 8u * r + 4u * gq : OOB;
     }
-#pragma unroll
-    for (int i = 0; i < TM; ++i)
-#pragma unroll
-      for (int j = 0; j < 4; ++j)
-#pragma unroll
-        for (int v = 0; v < 16; ++v) acc[i][j][v] = 0.0f;
 
     // An odd chunk count takes its first chunk unpipelined.
     int kc = 0;
     if (kcn & 1) {
+      zero_tiles(acc);
       load_b(std::integral_constant<int, 0>(), 0);
 #pragma unroll
       for (int q = 0; q < TM; ++q) {
@@ -2548,6 +2558,8 @@ __global__ void __launch_bounds__(256) k_gemm_w4a16_direct(GemmArgs g) {
       }
       __syncthreads();
       kc = 1;
+    } else {
+      zero_tiles(acc);
     }
     if (kc < kcn) {
       load_b(std::integral_constant<int, 0>(), kc);
