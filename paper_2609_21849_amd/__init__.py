@@ -10,7 +10,9 @@ A few helpers below (``quantize``, ``pack``, ``linear`` ...) allocate the
 output tensors with torch and then call the same entry points. The per-call
 ones (``quantize``, ``linear``, ``linear_fp8``) do so natively
 (``csrc/torch_binding.cpp``) for plain CUDA tensors that pass their checks;
-anything else takes the Python statements below, which raise what is wrong.
+anything else takes the Python statements below, which raise what is wrong, and
+so does everything where that extension was not built (with a warning: the
+kernels are the same, a call takes some microseconds more of host time).
 """
 from __future__ import annotations
 
@@ -100,6 +102,11 @@ def lib() -> ctypes.CDLL:
 _host = None
 
 
+class _NoNative:
+    """Stands in for the native helpers where they are not built: takes no call."""
+    quantize = linear = linear_fp8 = staticmethod(lambda *args: None)
+
+
 def _native():
     """The native helpers (_qgemm_torch.so, built beside the library)."""
     global _host
@@ -107,17 +114,20 @@ def _native():
         lib()
         import torch  # noqa: F401  (its libraries, before the extension that links them)
         try:
-            from . import _qgemm_torch
+            from . import _qgemm_torch as host
         except ImportError as e:
-            raise ImportError("_qgemm_torch.so is not built (run `python -m paper_2609_21849_amd.build` "
-                              "or __graft_entry__.build()): %s" % e) from e
-        _host = _qgemm_torch
+            import warnings
+            warnings.warn("_qgemm_torch.so is not available (%s): quantize, linear and linear_fp8 run through ctypes; "
+                          "`python -m paper_2609_21849_amd.build` builds it" % e, RuntimeWarning, stacklevel=3)
+            host = _NoNative
+        _host = host
     return _host
 
 
 def _handle(stream):
-    """None (the current stream) or the stream's handle."""
-    return stream if stream is None or isinstance(stream, int) else stream.cuda_stream
+    """The stream's handle; None (the current stream), handles and what is no
+    stream as they are."""
+    return getattr(stream, "cuda_stream", stream)
 
 
 def _p(t) -> int | None:

@@ -4,7 +4,8 @@
 
 Each .hip file is compiled to an object in parallel, then linked into
 paper_2609_21849_amd/libqgemm.so next to this file; csrc/torch_binding.cpp
-(host code only) becomes _qgemm_torch.so beside it, linked against it.
+(host code only) becomes _qgemm_torch.so beside it, linked against it. Without
+g++ or torch only the library is built, which the package can do with.
 """
 from __future__ import annotations
 
@@ -40,12 +41,23 @@ def sources() -> list[str]:
     return sorted(glob.glob(os.path.join(CSRC, "*.hip")))
 
 
+def binding_lacks() -> str | None:
+    """What is missing here to build the torch binding, or None."""
+    if shutil.which("g++") is None:
+        return "no g++"
+    try:
+        import torch  # noqa: F401
+    except ImportError as e:
+        return "no torch (%s)" % e
+    return None
+
+
 def _compile_binding() -> str:
     import torch
     inc = os.path.join(os.path.dirname(torch.__file__), "include")
     rocm = os.path.dirname(os.path.dirname(os.path.realpath(HIPCC)))
     obj = os.path.join(BUILD_DIR, "torch_binding.o")
-    cmd = [shutil.which("g++") or "g++", "-O2", "-std=c++17", "-fPIC", "-fvisibility=hidden", "-D__HIP_PLATFORM_AMD__=1",
+    cmd = [shutil.which("g++"), "-O2", "-std=c++17", "-fPIC", "-fvisibility=hidden", "-D__HIP_PLATFORM_AMD__=1",
            "-DUSE_ROCM", "-D_GLIBCXX_USE_CXX11_ABI=%d" % int(torch._C._GLIBCXX_USE_CXX11_ABI),
            "-I" + INCLUDE, "-isystem", inc, "-isystem", os.path.join(inc, "torch", "csrc", "api", "include"),
            "-isystem", sysconfig.get_paths()["include"], "-isystem", os.path.join(rocm, "include"),
@@ -69,27 +81,37 @@ def build(verbose: bool = False) -> str:
     os.makedirs(BUILD_DIR, exist_ok=True)
     srcs = sources()
     with ThreadPoolExecutor(max(1, min(len(srcs), os.cpu_count() or 1))) as ex:
-        binding = ex.submit(_compile_binding)
+        lacks = binding_lacks()
+        binding = None if lacks else ex.submit(_compile_binding)
         objs = list(ex.map(_compile, srcs))
-        binding_obj = binding.result()
+        binding_obj = binding.result() if binding else None
     tmp = LIB + ".tmp%d" % os.getpid()
     cmd = [HIPCC, "--offload-arch=" + ARCH, "-shared", "-fPIC", "-o", tmp, *objs]
     r = subprocess.run(cmd, capture_output=True, text=True)
     if r.returncode != 0:
         raise RuntimeError("link failed:\n%s" % r.stderr)
     os.replace(tmp, LIB)
+    if binding_obj is None:
+        if os.path.exists(BINDING):
+            os.remove(BINDING)  # of another build
+        print("torch binding not built: %s" % lacks, file=sys.stderr)
+    else:
+        _link_binding(binding_obj)
+    if verbose:
+        print("built", LIB)
+    return LIB
+
+
+def _link_binding(binding_obj: str) -> None:
     import torch
     tl = os.path.join(os.path.dirname(torch.__file__), "lib")
     tmp = BINDING + ".tmp%d" % os.getpid()
-    cmd = [shutil.which("g++") or "g++", "-shared", "-o", tmp, binding_obj, "-L" + HERE, "-l:libqgemm.so",
+    cmd = [shutil.which("g++"), "-shared", "-o", tmp, binding_obj, "-L" + HERE, "-l:libqgemm.so",
            "-Wl,-rpath,$ORIGIN", "-L" + tl, "-lc10", "-lc10_hip", "-ltorch_cpu", "-ltorch_python"]
     r = subprocess.run(cmd, capture_output=True, text=True)
     if r.returncode != 0:
         raise RuntimeError("link of the torch binding failed:\n%s" % r.stderr)
     os.replace(tmp, BINDING)
-    if verbose:
-        print("built", LIB)
-    return LIB
 
 
 if __name__ == "__main__":
