@@ -2990,18 +2990,24 @@ __global__ void __launch_bounds__(512, 4) k_w4a16_gemv(GemmArgs g) {
 }
 
 // k = 0: every output is zero (NVFP4: zero codes and zero block scales, one
-// thread per code byte).
+// thread per code byte at a time). A launch of 2^32 threads or more is cut off
+// without an error, so the grid is bounded and walks the outputs.
 __global__ void k_zero_rows(void* y, uint8_t* y_bscale, int64_t m, int64_t n, int64_t ldy, int out_mode) {
-  const int64_t t = (int64_t)blockIdx.x * 256 + threadIdx.x;
   const int64_t w = (out_mode == OUT_NVFP4) ? n / 2 : n;  // items per row
-  if (t >= m * w) return;
-  const int64_t r = t / w, c = t - r * w;
-  if (out_mode == OUT_F32) reinterpret_cast<float*>(y)[r * ldy + c] = 0.0f;
-  else if (out_mode == OUT_FP8) reinterpret_cast<uint8_t*>(y)[r * ldy + c] = 0;
-  else if (out_mode == OUT_NVFP4) {
-    reinterpret_cast<uint8_t*>(y)[r * (ldy / 2) + c] = 0;
-    if (c % 8 == 0) y_bscale[r * (ldy / 16) + c / 8] = 0;
-  } else reinterpret_cast<uint16_t*>(y)[r * ldy + c] = 0;
+  for (int64_t t = (int64_t)blockIdx.x * 256 + threadIdx.x; t < m * w; t += (int64_t)gridDim.x * 256) {
+    const int64_t r = t / w, c = t - r * w;
+    if (out_mode == OUT_F32) reinterpret_cast<float*>(y)[r * ldy + c] = 0.0f;
+    else if (out_mode == OUT_FP8) reinterpret_cast<uint8_t*>(y)[r * ldy + c] = 0;
+    else if (out_mode == OUT_NVFP4) {
+      reinterpret_cast<uint8_t*>(y)[r * (ldy / 2) + c] = 0;
+      if (c % 8 == 0) y_bscale[r * (ldy / 16) + c / 8] = 0;
+    } else reinterpret_cast<uint16_t*>(y)[r * ldy + c] = 0;
+  }
+}
+inline void zero_rows(void* y, uint8_t* y_bscale, int64_t m, int64_t n, int64_t ldy, int out_mode, hipStream_t st) {
+  const int64_t blocks = (m * n + 255) / 256;
+  hipLaunchKernelGGL(k_zero_rows, dim3((unsigned)(blocks < 65536 ? blocks : 65536)), dim3(256), 0, st, y, y_bscale, m,
+                     n, ldy, out_mode);
 }
 
 template <int MT, int NP, int NW, int D, bool XLDS>
@@ -3083,8 +3089,7 @@ hipError_t launch_gemm(int a_fmt, const void* a, const uint8_t* a_bscale, const 
                        hipStream_t st) {
   if (m == 0 || n == 0) return hipSuccess;
   if (k == 0) {
-    hipLaunchKernelGGL(k_zero_rows, dim3((unsigned)((m * n + 255) / 256)), dim3(256), 0, st, y, y_bscale, m, n, ldy,
-                       out_mode);
+    zero_rows(y, y_bscale, m, n, ldy, out_mode, st);
     return hipGetLastError();
   }
   const int w_fmt = (a_fmt == 1 || a_fmt == 3 || a_fmt == 4) ? a_fmt : 2;
@@ -3204,9 +3209,7 @@ hipError_t launch_linear_fp8(const uint16_t* x, int64_t ldx, float* a_tscale, co
                              int64_t n, int64_t k, void* y, int64_t ldy, int out_mode, hipStream_t st) {
   if (m == 0 || n == 0 || k == 0) {
     hipLaunchKernelGGL(k_fp8_scale_only, dim3(1), dim3(256), 0, st, x, m, k, ldx, a_tscale);
-    if (m > 0 && n > 0)
-      hipLaunchKernelGGL(k_zero_rows, dim3((unsigned)((m * n + 255) / 256)), dim3(256), 0, st, y, nullptr, m, n,
-                         ldy, out_mode);
+    if (m > 0 && n > 0) zero_rows(y, nullptr, m, n, ldy, out_mode, st);
     return hipGetLastError();
   }
   GemmArgs g;
