@@ -230,6 +230,10 @@ qg_status qg_unpack_weights(qg_format fmt, const void *packed, size_t packed_byt
  * accumulation (deq' = decoded codes times block scales; the tensor scales
  * are applied once at the end; MX has none), then rounded to y_dtype. Accuracy contract:
  * |y - y_exact| <= 1e-3 * sum_k |a w| plus the rounding of y to y_dtype.
+ * The order in which the products are added follows from the tiling, which
+ * is chosen from the formats and m, n, k: equal calls give equal bits, but the
+ * same activation row in batches of different m may give outputs that differ
+ * by that order (in all formats, within the contract above).
  * Shapes: m, n, k >= 0; n % 16 == 0; k % 128 == 0; lda >= k, ldy >= n.
  * Operands are addressed with 32-bit byte offsets: the activation extent
  * ((m - 1) * lda + k elements), NVFP4 activation scales and the packed

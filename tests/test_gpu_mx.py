@@ -181,7 +181,8 @@ def test_mx_gemm_zero_rows_and_blocks(fmt):
 
 @pytest.mark.parametrize("fmt", [MXFP4, MXFP8])
 def test_mx_gemm_row_independent_of_batch(fmt):
-    # the same activation row gives bit-identical outputs whatever the batch
+    # the same activation row gives bit-identical outputs in batches whose tilings
+    # add up K alike (here four waves of a split-K tile in both)
     n, k = 512, 1024
     x = synth.normal_bf16(600, k, 1.0, 13, 0)
     w = synth.normal_bf16(n, k, 0.02, 13, 1)
@@ -190,6 +191,24 @@ def test_mx_gemm_row_independent_of_batch(fmt):
     assert torch.equal(y_all[299:300], y_one)
     y_again = run_mx_linear(x, w, q.QG_OUT_F32, check_codes=False, fmt=fmt)
     assert torch.equal(y_all, y_again)
+
+
+@pytest.mark.parametrize("fmt", [MXFP4, MXFP8])
+@pytest.mark.parametrize("n,k,few,many", [(2000, 1024, 40, 777),     # four waves -> eight (64 x 128 tiles)
+                                          (3072, 1024, 40, 1089)])   # four waves -> the large tiles' serial K
+def test_mx_gemm_row_across_tilings(fmt, n, k, few, many):
+    # across a change of the K split the fp32 sums are added in another order: both
+    # stay within 1e-3 sum|a w| of the exact value, so within twice that of each
+    # other; equal calls give equal bits
+    x = synth.normal_bf16(many, k, 1.0, 16, 0)
+    w = synth.normal_bf16(n, k, 0.02, 16, 1)
+    y_many = run_mx_linear(x, w, q.QG_OUT_F32, check_codes=False, fmt=fmt)
+    y_few = run_mx_linear(x[:few], w, q.QG_OUT_F32, check_codes=False, fmt=fmt)
+    xd, wd = (q.dequantize(q.quantize(to_dev_bf16(v), fmt), q.QG_OUT_F32) for v in (x[:few], w))
+    bound = 2e-3 * (xd.double().abs() @ wd.double().abs().t())
+    assert bool(((y_many[:few].double() - y_few.double()).abs() <= bound).all())
+    assert torch.equal(y_many, run_mx_linear(x, w, q.QG_OUT_F32, check_codes=False, fmt=fmt))
+    assert torch.equal(y_few, run_mx_linear(x[:few], w, q.QG_OUT_F32, check_codes=False, fmt=fmt))
 
 
 def _sample(m, n, count, seed):
