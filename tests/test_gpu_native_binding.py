@@ -78,6 +78,61 @@ def test_linear_forms(monkeypatch, kind, out):
             assert torch.equal(y, q.linear(a, packed, fmt, 48, out_dtype=out)) and not buf[:, 48:].any()
 
 
+def test_the_native_helpers_run():
+    assert q._native().__name__ == "paper_2609_21849_amd._qgemm_torch"
+
+
+def _late_input(op):
+    """(the tensor that a producer fills late, its contents, the call)."""
+    x = to_dev_bf16(synth.normal_bf16(64, 512, 1.0, 7, 0))
+    if op.startswith("quantize"):
+        fmt = q.QG_FMT_NVFP4 if op == "quantize nvfp4" else q.QG_FMT_FP8_E4M3
+        return x, x.clone(), lambda **kw: q.quantize(x, fmt, **kw)
+    wfmt = q.QG_FMT_NVFP4 if op == "linear w4a16" else q.QG_FMT_FP8_E4M3
+    packed = q.pack(q.quantize(to_dev_bf16(synth.normal_bf16(256, 512, 0.02, 7, 1)), wfmt))
+    if op == "linear_fp8":
+        return x, x.clone(), lambda **kw: q.linear_fp8(x, packed, 256, **kw)
+    if op == "linear w4a16":
+        return x, x.clone(), lambda **kw: q.linear(x, packed, wfmt, 256, **kw)
+    a = q.quantize(x, wfmt)
+    return a.codes, a.codes.clone(), lambda **kw: q.linear(a, packed, wfmt, 256, **kw)
+
+
+@pytest.mark.parametrize("op", ["quantize fp8", "quantize nvfp4", "linear fp8", "linear w4a16", "linear_fp8"])
+@pytest.mark.parametrize("how", ["current", "handle", "stream"])
+@pytest.mark.parametrize("native", [True, False])
+def test_calls_run_on_the_stream_they_name(monkeypatch, op, how, native):
+    """The input is filled on the side stream, behind some milliseconds of copies:
+    a call that went to any other stream would read the zeros that are there
+    before (the producer is still running when the call has returned)."""
+    if not native:
+        monkeypatch.setattr(q, "_host", _Off)
+    late, value, call = _late_input(op)
+    side, done = torch.cuda.Stream(), torch.cuda.Event()
+    work = torch.empty((2, 1 << 28), dtype=torch.float32, device=DEV)       # 1 GiB each
+    work.zero_()
+    want = call()
+    torch.cuda.synchronize()
+    for _ in range(2):                                  # the first also loads what runs
+        late.zero_()
+        torch.cuda.synchronize()
+        with torch.cuda.stream(side):
+            for _ in range(24):
+                work[0].copy_(work[1])
+            late.copy_(value)
+            done.record(side)
+            if how == "current":
+                got = call()
+        if how == "handle":
+            got = call(stream=side.cuda_stream)
+        elif how == "stream":
+            got = call(stream=side)
+        running = not done.query()
+        torch.cuda.synchronize()
+        _same(got, want)
+    assert running
+
+
 def test_refusals_are_the_same(monkeypatch):
     x = to_dev_bf16(synth.normal_bf16(8, 256, 1.0, 5, 0))
     packed = q.pack(q.quantize(to_dev_bf16(synth.normal_bf16(32, 256, 0.02, 5, 1)), 1))
