@@ -4,10 +4,11 @@ Rows of the activations and of the weights are scaled down by 2^-12 ...
 2^-35 (one factor per row, cycling), so that, against a tensor scale set by
 the rows left at full size, their block scales run through normal, subnormal
 (codes 1..7, k * 2^-9) and zero (code 0) E4M3 values. Every kernel that
-decodes block scales is driven through such operands at a workload shape:
-the persistent 256 x 256 W4A4 kernel (transformer linear), the small-token
-W4A4 kernels (512 x 3072 x 3072), and the W4A16 split-K, few-row streaming,
-one-row matrix-vector and large-M kernels. Outputs are checked against the
+decodes block scales is driven through such operands: the persistent W4A4
+kernel (transformer linear), the split-K W4A4 kernel (512 x 3072 x 3072 and few
+rows), and the W4A16 split-K (32- and 64-row tiles), few-row streaming,
+one-row matrix-vector and large-tile kernels (each height of its tiles), the
+shapes as a device of 256 CUs dispatches them. Outputs are checked against the
 oracle: fp32 outputs with the literal bound |y - y_ref| <= 1e-3 sum|a w|,
 bf16 outputs with the rounding window (a correct rounding of a value within
 that bound: the shrunken rows keep only a few nonzero terms, where the bf16
@@ -57,9 +58,9 @@ def run(kind, x, w, out):
     return y
 
 
-@pytest.mark.parametrize("m,n,k,label", [(4608, 3072, 3072, "256x256 kernel, transformer attn-out"),
-                                         (512, 3072, 3072, "small-token kernel, 512x3072x3072"),
-                                         (96, 1024, 3072, "small-token kernel, few rows")])
+@pytest.mark.parametrize("m,n,k,label", [(4608, 3072, 3072, "256-row tiles, transformer attn-out"),
+                                         (512, 3072, 3072, "split-K, 64 x 96 tiles"),
+                                         (96, 1024, 3072, "split-K, 32 x 32 tiles")])
 @pytest.mark.parametrize("out", [q.QG_OUT_F32, q.QG_OUT_BF16])
 def test_w4a4_subnormal_and_zero_block_scales(m, n, k, label, out):
     log("w4a4 edge scales %s %dx%dx%d out=%d" % (label, m, n, k, out))
@@ -82,11 +83,16 @@ def test_w4a4_subnormal_and_zero_block_scales(m, n, k, label, out):
     assert not torch.any(y[torch.as_tensor(zero_rows, device=y.device)]).item()
 
 
-@pytest.mark.parametrize("m,n,k,label", [(256, 3072, 1024, "split-K, two panels per workgroup"),
-                                         (16, 1024, 3072, "split-K, direct activation fragments"),
+@pytest.mark.parametrize("m,n,k,label", [(256, 3072, 1024, "split-K, 32 x 64 tiles"),
+                                         (16, 1024, 3072, "split-K, few rows"),
                                          (16, 70016, 1024, "few-row streaming kernel"),
                                          (1, 70016, 1024, "one-row matrix-vector kernel"),
-                                         (1100, 512, 1024, "large-M kernel")])
+                                         (1100, 512, 1024, "split-K, 32 x 64 tiles, many rows"),
+                                         (500, 3072, 1152, "split-K, 64 x 96 tiles"),
+                                         (2050, 336, 1152, "split-K, 64 x 64 tiles"),
+                                         (1900, 4112, 256, "large tiles, 128 rows"),
+                                         (1230, 8208, 256, "large tiles, 192 rows"),
+                                         (2420, 5136, 256, "large tiles, 256 rows")])
 @pytest.mark.parametrize("out", [q.QG_OUT_F32, q.QG_OUT_BF16])
 def test_w4a16_subnormal_and_zero_block_scales(m, n, k, label, out):
     log("w4a16 edge scales %s %dx%dx%d out=%d" % (label, m, n, k, out))

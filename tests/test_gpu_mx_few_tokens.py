@@ -1,6 +1,6 @@
 """The MX GEMM's split-K tilings (few tokens) against the CPU oracle: each
 tiling that the dispatch picks on a 256-CU device, the sizes on either side of
-the change to 256 x 256 tiles, ragged rows and columns, odd and even chunk
+the change to large tiles, ragged rows and columns, odd and even chunk
 counts per wave, and the quantized outputs of its reduction epilogue."""
 import numpy as np
 import pytest
@@ -20,8 +20,9 @@ SHAPES = [(1, 16, 256), (33, 48, 512),          # 32 x 32 tiles
           (256, 3056, 256),                     # 32 x 96
           (500, 3072, 1280),                    # 64 x 96, one round
           (777, 2000, 512),                     # 64 x 128
-          (1001, 3008, 256),                    # 64 x 96, two rounds
-          (1089, 3072, 256)]                    # 256 x 256
+          (1001, 3008, 256),                    # large tiles, 128 x 256
+          (1089, 3072, 256),                    # large tiles, 128 x 256
+          (700, 3008, 6400)]                    # MXFP8: 64 x 96, two rounds; MXFP4: large tiles
 
 
 def _operands(m, n, k, fmt, seed):

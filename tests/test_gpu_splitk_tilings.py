@@ -18,14 +18,18 @@ CASES = [("nvfp4", 33, 48, 384), ("nvfp4", 33, 48, 4224),               # 32 x 3
          ("nvfp4", 300, 1008, 384), ("nvfp4", 40, 4112, 4224),          # 32 x 64, short and long K
          ("nvfp4", 256, 3056, 128),                                     # 32 x 96
          ("nvfp4", 500, 3072, 256),                                     # 64 x 96
-         ("nvfp4", 1001, 3008, 128),                                    # 64 x 64
+         ("nvfp4", 1001, 3008, 128),                                    # 64 x 64, two a CU
+         ("nvfp4", 593, 1392, 512),                                     # 64 x 64, eight waves, one a CU
+         ("nvfp4", 1273, 1968, 5248),                                   # 64 x 96, several rounds
          ("w4a16", 1, 48, 3072), ("w4a16", 31, 8240, 3200),             # few rows
          ("w4a16", 40, 48, 3200),                                       # 32 x 32
          ("w4a16", 250, 3056, 1024),                                    # 32 x 64, four waves
          ("w4a16", 300, 1008, 1152),                                    # 32 x 64, eight waves
          ("w4a16", 200, 9200, 1152),                                    # 32 x 64 for the row padding
          ("w4a16", 500, 3072, 1152),                                    # 64 x 96
-         ("w4a16", 1100, 2000, 256), ("w4a16", 2050, 336, 256),         # 64 x 64
+         ("w4a16", 1100, 2000, 256), ("w4a16", 2050, 336, 1152),        # 64 x 64
+         ("w4a16", 2050, 336, 256),                                     # 32 x 64, four waves, many rows
+         ("w4a16", 150, 21568, 3072),                                   # 64 x 64 for the large tiles' padding
          ("fp8", 500, 3072, 2048), ("fp8", 449, 3008, 2176)]            # 64 x 96
 
 

@@ -16,8 +16,9 @@ pytestmark = pytest.mark.gpu
 
 FMTS = {"fp8": q.QG_FMT_FP8_E4M3, "nvfp4": q.QG_FMT_NVFP4, "mxfp4": q.QG_FMT_MXFP4, "mxfp8": q.QG_FMT_MXFP8,
         "w4a16": q.QG_FMT_NVFP4}
-# ragged: the last row tile holds 108 (256-row tiles) or 172 (288-row) rows, the
-# last column tile 16; the last fp8 shape fills whole 256 x 256 tiles
+# on 256 CUs 1900 x 4112 takes tiles of 128 x 256, ragged in both directions: the
+# last row tile holds 108 rows, the last column tile 16 (the taller tiles: see
+# test_gpu_tile_heights.py); the second fp8 shape fills whole 256 x 256 tiles
 CASES = [("fp8", 1900, 4112, 256), ("fp8", 2048, 8192, 128), ("nvfp4", 1900, 4112, 128), ("nvfp4", 1900, 4112, 256),
          ("mxfp4", 1900, 4112, 256), ("mxfp8", 1900, 4112, 256), ("w4a16", 1900, 4112, 256)]
 
