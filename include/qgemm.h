@@ -109,9 +109,10 @@ typedef enum qg_out_dtype {
  *   tensor_scale  out: one fp32 decode scale; must be NULL for the MX formats.
  *   A tensor of at most 3072 units of 16 elements (units per row:
  *   ceil(cols / 16)) is quantized by one launch, whose workgroups each
- *   reduce the whole tensor and code their share of it. A dense one
- *   (ldx == cols, 16-byte aligned x, 8-byte aligned codes, rows * cols a
- *   multiple of 8) of at most 3 Mi elements takes two launches: the first
+ *   reduce the whole tensor and code their share of it. One of at most 3 Mi
+ *   elements that is read and coded in whole 8-element units (16-byte aligned
+ *   x and 8-byte aligned codes; ldx == cols and rows * cols a multiple of 8, or
+ *   cols and ldx multiples of 8) takes two launches: the first
  *   leaves its partial maxima in `codes`, the second reduces them and writes
  *   the codes over them. Any other tensor-wide max is reduced in two kernels
  *   whose partial results are parked in `codes` the same way, then a third

@@ -1091,7 +1091,7 @@ inline int epilogue_of(const GemmArgs& g) { return out_staged(g) ? g.out_mode : 
       QG_LAUNCH_EPI_NO_NVFP4(KERNEL, grid, st, g __VA_OPT__(, ) __VA_ARGS__);                                     \
   } while (0)
 
-// Activation staging shared by the 256 x 256 FP8 kernels: 256 rows x one
+// Activation staging of the FP8 large tiles (shown for 256 rows): the rows x one
 // 128-byte chunk, read row-contiguously (8 lanes per row) and stored in LDS
 // as 8 panels of 4 KiB. Piece c (bytes 16c .. 16c+15 of the row's chunk)
 // belongs to step s = c / 4, lane half g = (c / 2) % 2 and register half
@@ -1354,7 +1354,7 @@ __global__ void __launch_bounds__(256) k_gemm_fp8_direct(GemmArgs g) {
 //                 CPU).
 // Output: lane l of block (i, j) holds Y[m0 + 16 i + l % 16][n0 + 16 j +
 // 4 (l / 16) + e], four consecutive outputs of a row. bf16, fp32 and FP8
-// outputs; the NVFP4 output keeps the 256 x 256 kernel.
+// outputs; the NVFP4 output keeps k_gemm_fp8_direct.
 struct AStage288 {
   static constexpr int RA = 9;  // 16-byte pieces per thread per chunk
   uint32_t oa[RA], la[RA];
@@ -1815,7 +1815,7 @@ __global__ void __launch_bounds__(256) k_gemm_mxfp8_direct(GemmArgs g) {
 
 // ---------------------------------------------------------------- W4A4 (NVFP4), large token counts
 
-// W4A4 on 256 x 256 tiles, four wavefronts (one per SIMD) of 128 x 128 =
+// W4A4 on tiles of up to 256 x 256, four wavefronts (one per SIMD) of 128 x 128 =
 // 4 x 4 MFMA tiles of 32 x 32 -- the largest wave tile, which minimises the
 // operand expansion per MFMA: each lane expands 8 fragments of 8 elements per
 // 16-wide step for 16 MFMAs. Per 128-wide chunk: 128 v_mfma_f32_32x32x16_f16
@@ -2081,8 +2081,8 @@ __global__ void __launch_bounds__(256) k_gemm_nvfp4_direct(GemmArgs g) {
 // E2M1 codes (16 bytes: lanes 0-31 reduction elements 0-31 of the step,
 // lanes 32-63 elements 32-63) and one E8M0 scale byte for them -- exactly
 // one MX block -- so the format runs at the fp4 matrix rate with no operand
-// expansion at all. Same tiles and waves as k_gemm_fp8_direct (256 x 256,
-// four waves of 128 x 128, persistent grid, staged epilogue); the reduction
+// expansion at all. Same tiles and waves as k_gemm_fp8_direct (64 TM x 256,
+// four waves of 32 TM x 128, persistent grid, staged epilogue); the reduction
 // advances in chunks of 256 (4 MFMA steps of 64, 64 MFMAs of 32 cycles per
 // wave per chunk):
 //   weights     : one 1 KiB code image per panel and step, loaded straight
@@ -2347,7 +2347,7 @@ __global__ void __launch_bounds__(256) k_gemm_mxfp4_direct(GemmArgs g) {
 
 // ---------------------------------------------------------------- W4A16, large token counts
 // W4A16 (bf16 activations, NVFP4 weights) past the ridge point: the tile and
-// wave layout of the W4A4 kernel (256 x 256 tiles, four waves of 128 x 128,
+// wave layout of the W4A4 kernel (tiles of 64 TM x 256, four waves of 32 TM x 128,
 // persistent grid), on v_mfma_f32_32x32x16_bf16.
 //   weights     : codes and E4M3 block scales straight from the packed buffer
 //                 into registers one chunk ahead (as in k_gemm_nvfp4_direct);

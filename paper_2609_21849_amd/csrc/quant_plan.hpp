@@ -32,7 +32,7 @@ struct SlotsPlan {
   int64_t G;  // code regions = quantize workgroups; 0: the plan does not apply
 };
 
-// Plan for a dense tensor of n elements (n % 8 == 0), code bytes per unit
+// Plan for a tensor of n elements in whole units (n % 8 == 0), code bytes per unit
 // cb = 8 (FP8) or 4 (NVFP4): every region's codes must hold the P slots.
 inline SlotsPlan slots_plan(int64_t n, int cb) {
   if (n <= 0 || n % 8 != 0 || n > kSlotsMaxElements) return {0, 0};

@@ -8,8 +8,9 @@
 //
 // A tensor-wide scale needs the tensor-wide max before any element can be
 // coded. A small tensor (at most 3072 units of 16 elements) is quantized in
-// one launch (k_quant_small); a dense one of at most 3 Mi elements in two
-// (k_amax_slots, k_quant_dense_slots: the maxima handed over inside the code
+// one launch (k_quant_small); one of at most 3 Mi elements whose rows are 16-byte
+// aligned and whole 8-element units (dense, or a column slice) in two
+// (k_amax_slots, k_quant_slots: the maxima handed over inside the code
 // buffer); any other is a short chain on the caller's stream:
 //   k_amax_units / : max |x| as an integer max of bf16 magnitude bits (the
 //   k_amax_partial   bit pattern of a non-negative value orders like the
@@ -318,7 +319,7 @@ __global__ void __launch_bounds__(1024) k_quant_small(const uint16_t* __restrict
   }
 }
 
-// ---------------------------------------------------------------- dense tensors
+// ---------------------------------------------------------------- whole units, aligned rows
 // FP8 codes of one whole 16-byte unit (8 consecutive elements, index u)
 // held in `raw`: one 8-byte store, gated by `in`.
 __device__ inline void code_unit8_fp8(const uint4 raw, int64_t u, bool in, uint8_t* __restrict__ q, float r) {
@@ -439,11 +440,11 @@ __global__ void __launch_bounds__(256) k_quant_units(const uint16_t* __restrict_
   }
 }
 
-// ---------------------------------------------------------------- dense, two launches
-// Dynamic quantization of a dense tensor without the one-workgroup finalize
-// kernel. k_amax_slots leaves each of its P workgroup maxima not in one
+// ---------------------------------------------------------------- two launches
+// Dynamic quantization without the one-workgroup finalize kernel, of a dense
+// tensor or of aligned rows of whole units (DENSE false). k_amax_slots leaves each of its P workgroup maxima not in one
 // place but in every code region of the quantize launch (slot i among the
-// first 4 P bytes of each region); each workgroup of k_quant_dense_slots
+// first 4 P bytes of each region); each workgroup of k_quant_slots
 // reduces the P maxima found at the start of its own region to the tensor
 // scale before any of its codes overwrite them. No workgroup reads what
 // another writes within a launch, so stream order between the two launches
@@ -491,7 +492,7 @@ __global__ void __launch_bounds__(256) k_amax_slots(const uint16_t* __restrict__
 // Each wave codes runs of 64 consecutive units (one 16-byte load per lane,
 // four per lane in flight); rounds of 1024 units until the region ends.
 template <int FMT, bool DENSE>
-__global__ void __launch_bounds__(256) k_quant_dense_slots(const uint16_t* __restrict__ x, int64_t units, UnitRows rows,
+__global__ void __launch_bounds__(256) k_quant_slots(const uint16_t* __restrict__ x, int64_t units, UnitRows rows,
                                                            uint8_t* __restrict__ q, uint8_t* __restrict__ bscale,
                                                            float* __restrict__ tscale, int P) {
   constexpr int H = 4;
@@ -909,7 +910,7 @@ static void launch_slots(const uint16_t* x, int64_t units, const UnitRows& ur, u
                          float* tscale, const SlotsPlan& plan, hipStream_t st) {
   hipLaunchKernelGGL((k_amax_slots<kSlotsAmaxLoads, DENSE>), dim3((unsigned)plan.P), dim3(256), 0, st, x, units, ur,
                      codes, FMT == 1 ? 8 : 4, (int)plan.G);
-  hipLaunchKernelGGL((k_quant_dense_slots<FMT, DENSE>), dim3((unsigned)plan.G), dim3(256), 0, st, x, units, ur, codes,
+  hipLaunchKernelGGL((k_quant_slots<FMT, DENSE>), dim3((unsigned)plan.G), dim3(256), 0, st, x, units, ur, codes,
                      bscale, tscale, (int)plan.P);
 }
 

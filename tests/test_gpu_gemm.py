@@ -204,7 +204,7 @@ def test_dit_linear_sampled(kind, name):
 def test_mid_m_linear_sampled(kind, m, n, k):
     # token counts between the small-M shapes and the transformer's (ragged
     # ones among them), on both sides of the tile-count thresholds that pick
-    # the 64 x 128 kernels (FP8, W4A4) over the persistent 256 x 256 ones, and
+    # few-token kernels (FP8 64 x 128 tiles, split-K) over the large tiles, and
     # FP8 split-K tilings 32 x 128 (1000 x 1008, nine chunks over eight waves)
     # and 32 x 96 (250 x 2992, six chunks: two waves without one)
     log("%s mid-m %dx%dx%d" % (kind, m, n, k))
@@ -239,7 +239,7 @@ def test_fp8_whole_round_tiles_sampled(m, n, k, out):
                                        (4321, 3056, 640, q.QG_OUT_BF16), (4321, 3056, 640, q.QG_OUT_F32),
                                        (1000, 8208, 640, q.QG_OUT_BF16)])
 def test_nvfp4_ragged_large_sampled(m, n, k, out):
-    # the persistent 256 x 256 W4A4 kernel at ragged sizes: rows and columns
+    # the persistent W4A4 kernel (256-row tiles, 192 at 1000 rows) at ragged sizes: rows and columns
     # that leave the last tile row and tile column part-filled (4321, 4600,
     # 1000 rows; 3056, 9200, 8208 columns, a part-filled last weight panel),
     # an odd number of 128-wide chunks (K = 1152, 640), bf16 and fp32
@@ -303,8 +303,8 @@ def test_w4a16_one_row_wide_weight(out):
 @pytest.mark.parametrize("m,n,k,out", [(256, 65536, 1024, q.QG_OUT_BF16), (300, 16400, 1152, q.QG_OUT_F32),
                                        (4608, 3072, 3072, q.QG_OUT_BF16), (1000, 8208, 640, q.QG_OUT_BF16)])
 def test_w4a16_many_tiles_sampled(m, n, k, out):
-    # W4A16 past the ridge point with enough 256 x 256 tiles for the
-    # persistent kernel: a pool-like wide weight, ragged rows and columns
+    # W4A16 past the ridge point with enough large tiles for the persistent
+    # kernel (all three heights): a pool-like wide weight, ragged rows and columns
     # (300, 1000 rows; 16400, 8208 columns), odd chunk counts (K = 1152, 640),
     # bf16 and fp32 outputs; heavy-tailed activations with subnormal and zero
     # blocks in some rows

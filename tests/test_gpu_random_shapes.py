@@ -77,8 +77,8 @@ def _edge_samples(m, n, count, seed):
 @pytest.mark.parametrize("kind", ["fp8", "nvfp4", "w4a16"])
 @pytest.mark.parametrize("m,n,k", _large_shapes(2027, 6))
 def test_random_large_shape_parity(kind, m, n, k):
-    # the many-token kernels (256 x 256, 288 x 192, 64 x 128 tiles and the
-    # W4A16 direct kernel) at ragged sizes, on sampled outputs at tile edges
+    # the many-token kernels (large tiles, FP8 288 x 192 and 64 x 128 ones, and
+    # split-K in several rounds) at ragged sizes, on sampled outputs at tile edges
     log("random large shape kind=%s m=%d n=%d k=%d" % (kind, m, n, k))
     seed = (m * 131 + n * 17 + k) % 1000
     x = synth.normal_bf16(m, k, 1.0, seed, 0, outlier_frac=0.002, outlier_gain=30.0)
