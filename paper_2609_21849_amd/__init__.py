@@ -127,7 +127,7 @@ def _native():
 def _handle(stream):
     """The stream's handle; None (the current stream), handles and what is no
     stream as they are."""
-    return getattr(stream, "cuda_stream", stream)
+    return None if stream is None else getattr(stream, "cuda_stream", stream)
 
 
 def _p(t) -> int | None:
