@@ -150,7 +150,7 @@ inline SplitK plan_nvfp4(int64_t m, int64_t n, int64_t k, int64_t cus) {
 
 // MXFP4 / MXFP8. Up to a round of 64 x 96 tiles on the CUs the split-K kernel,
 // above that the large tiles ({}): those walk K serially, while a split-K tile's
-// waves share K and the operands' L2 traffic is all that bounds it. Inside the
+// waves share K (and are bound by their L1 requests). Inside the
 // split-K range the narrowest tile that still gives every workgroup a CU of its own.
 // Measured (GPU time from graph replays, 256 x 256 -> split-K; best of 16 tilings
 // within 8% everywhere): MXFP4 1 x 3072 x 1024 12.7 -> 2.8 us, 256 x 3072 x 3072 25.0 ->
